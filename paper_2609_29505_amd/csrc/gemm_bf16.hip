@@ -1,22 +1,21 @@
 // Branch GEMMs of the active units in bf16: C = A . B^T on the CDNA4 matrix cores
 // (v_mfma_f32_32x32x16_bf16, fp32 accumulation) with the unit's epilogue fused.
 //
-// Main loop.  Block tiles up to 256 x 256 with eight waves, two per SIMD, 64-deep k tiles
-// (128-byte operand rows, one L2 line each).  Global -> LDS goes through registers:
-// buffer_load_dwordx4 into VGPRs (the buffer descriptor's range check returns zeros for
-// rows past the matrix, so ragged M and N need no clamping), then ds_write_b128 to an
-// XOR-swizzled position so that the 16-byte fragment reads of 16 consecutive rows cover
-// the 64 banks once.  The registers are a third pipeline stage next to the two LDS stages,
-// and the register -> LDS writes and the next loads are spread one part at a time between
-// the MFMAs, so neither the texture unit nor the LDS sees a burst while the MFMA pipes
-// run.  Measured on gfx950: issuing a whole tile of loads at once (directly to LDS or to
-// registers) left the load and MFMA phases serialised at ~35 % of peak.
+// Two kernels share the epilogue: gemm_pp_kernel, 256-row block tiles whose operands go straight
+// into LDS and whose wave groups alternate between loading and MFMAs, and gemm_bf16_kernel, 128-row
+// tiles for products too small to fill the chip with 256-row ones.
 //
-// Epilogue.  The fp32 accumulator tile goes through LDS in row chunks (one wave row at a
-// time); every thread then handles four consecutive columns of a row, so stores are
-// vectorised and coalesced and paired columns (gate/up of a gated MLP, the rotary pairs
-// (i, i + dh/2) of a head) are read from LDS whatever the wave layout.  V^T columns of a
-// head projection are written by a column-major pass (consecutive tokens per thread).
+// 128-row kernel.  Eight waves, two per SIMD, 64-deep k tiles (128-byte operand rows, one L2 line
+// each).  Global -> LDS goes through registers: buffer_load_dwordx4 into VGPRs (the buffer
+// descriptor's range check returns zeros for rows past the matrix, so ragged M and N need no
+// clamping), then ds_write_b128 to an XOR-swizzled position so that the 16-byte fragment reads of
+// 16 consecutive rows cover the 64 banks once.  The registers are a third pipeline stage next to
+// the two LDS stages, and the register -> LDS writes and the next loads are spread one part at a
+// time between the MFMAs, so neither the texture unit nor the LDS sees a burst while the MFMA
+// pipes run.
+//
+// Epilogue.  Straight from the accumulators: the loader orders the weight rows so that what a
+// store or a pair of columns needs sits in one lane (see the epilogue).
 #include <type_traits>
 #include <utility>
 
@@ -67,29 +66,37 @@ struct TileCfg {
     static constexpr int A_BYTES = BM * ROWB, B_BYTES = BN * ROWB;
     static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
     static constexpr int KSTEPS = BK / 16;
-    static constexpr int EPR = WGM * 32;                 // epilogue chunk: one MFMA row block per wave row
-    static constexpr int EPS = BN + 8;                   // fp32 row stride of the staged chunk
-    static constexpr int EPI_BYTES = (EPR * EPS + BN) * 4;  // + one row of bias columns
-    static constexpr int LDS_BYTES = STAGE_BYTES * STAGES > EPI_BYTES ? STAGE_BYTES * STAGES : EPI_BYTES;
+    // tile row of the first row of wave row wm's MFMA row block i
+    __device__ static __forceinline__ int block_row(int wm, int i) { return wm * WM + i * 32; }
+    static constexpr int LDS_BYTES = STAGE_BYTES * STAGES;
     static_assert(TM >= 1 && TN >= 1 && WM % 32 == 0 && WN % 32 == 0, "wave tile");
     static_assert(BK == 64, "128-byte operand rows: one L2 line per row and chunk-swizzled LDS rows");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
-    static_assert((4 * EPS) % 64 == 32, "conflict-free accumulator staging");
 };
 
 // --------------------------------------------------------------------------- epilogue
 //
-// Every item loop below has a compile-time trip count and runs in two phases, all loads
-// (LDS values, bias, gate, h, delta) first and all stores after: a loop that alternated a
-// global store with the next load made the compiler wait for each store's completion
-// before reusing its registers, one memory round trip per item.
+// Straight from the accumulators, without LDS or a barrier.  In the MFMA output layout lane l holds
+// column l % 32 of a 32 x 32 block and, in registers 4 q .. 4 q + 3, its rows 8 q + 4 (l / 32) +
+// 0..3.  Which product column a block column stands for is the loader's choice (it picks the weight
+// row for each LDS row), and it is made so that a lane's values of one row are neighbours
+// (tile_col): two blocks side by side give a lane columns 2 l and 2 l + 1.  The pairs of a rotary
+// head and the gate and up columns of a gated MLP then meet in one lane, four consecutive tokens of
+// a V^T row are four registers, and a transpose of the four rows within a quad of lanes (DPP) leaves
+// each lane eight neighbouring columns of one row: 16-byte stores that fill whole 128-byte lines.
+//
+// Every batch of rows loads its global operands (h, delta, gate) before its first store: a loop
+// that alternates them waits for each store (vmcnt counts both).
+//
+// An epilogue's cost beyond its bytes is what a launch with K = 64 shows (8192 rows, 256 x 256
+// tiles): staged through LDS in 128-row chunks 28.9 us plain, 42.7 GELU(erf), 21.5 residual (1024
+// columns), 56.5 GEGLU; this one 24.1, 34.8, 19.9 and 48.4.
 
 __device__ __forceinline__ void store_bf16x4(bf16* dst, const float v[4]) {
     bf16x4 s;
     s[0] = f2bf(v[0]); s[1] = f2bf(v[1]); s[2] = f2bf(v[2]); s[3] = f2bf(v[3]);
     *(bf16x4*)dst = s;
 }
-__device__ __forceinline__ f32x4 ld4(const float* p) { return *(const f32x4*)p; }
 
 template <int ACT>
 __device__ __forceinline__ float act_fn(float x) {
@@ -103,281 +110,407 @@ __device__ __forceinline__ float act_fn(float x) {
 template <class Fn>
 __device__ __forceinline__ void with_act(int act, Fn&& f) {
     switch (act) {
-        case ACT_GELU_ERF: f(std::integral_constant<int, ACT_GELU_ERF>{}); break;
-        case ACT_GELU_TANH: f(std::integral_constant<int, ACT_GELU_TANH>{}); break;
-        case ACT_SILU: f(std::integral_constant<int, ACT_SILU>{}); break;
-        default: f(std::integral_constant<int, ACT_NONE>{}); break;
+        case ACT_GELU_ERF: f(IntC<ACT_GELU_ERF>{}); break;
+        case ACT_GELU_TANH: f(IntC<ACT_GELU_TANH>{}); break;
+        case ACT_SILU: f(IntC<ACT_SILU>{}); break;
+        default: f(IntC<ACT_NONE>{}); break;
     }
 }
 
-// Stage the accumulator tile in LDS one MFMA row block per wave row at a time, then store
-// it with the epilogue of ep.kind.  Every thread keeps the same four columns for all its
-// items (NT is a multiple of the items per row), and the tile's bias columns sit in an LDS
-// row of their own, so the q/k/v, activation and gated epilogues issue no global loads.
+// Column (of a wave's TN x 32) of lane column l in MFMA block j: blocks are taken in pairs whose
+// columns interleave; a last single block keeps its order.
+template <int TN>
+__device__ __forceinline__ int tile_col(int j, int l) {
+    return j < TN / 2 * 2 ? j / 2 * 64 + 2 * l + (j & 1) : j * 32 + l;
+}
+// Gated products: hidden column (of a wave's TN x 16) of lane column l in block j, and whether it
+// is the up half.  Gate block j pairs with up block j + (TN + 1) / 2; the middle block of an odd TN
+// holds 16 gate columns and then their 16 up columns.
+template <int TN>
+__device__ __forceinline__ int gated_col(int j, int l, bool& up) {
+    constexpr int H = TN / 2, UP = (TN + 1) / 2;
+    if (TN % 2 && j == H) { up = l >= 16; return H * 32 + (l & 15); }
+    up = j >= UP;
+    return (up ? j - UP : j) * 32 + l;
+}
+
+// Weight row of LDS row r of column tile tn (every kernel's B loader)
 template <class C>
-__device__ __forceinline__ void epilogue(f32x16 (&acc)[C::TM][C::TN], char* lds, const GemmArgs& g,
-                                         const EpiParams& ep, int m0, int tn, int wm, int wn0, int split) {
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int lrow = lane & 31, lhalf = lane >> 5;
-    // Thread t handles rows r0(t) + u * RPT of its columns.  When the items of a row do not
-    // divide the block (192-column tiles), the threads past the last whole pass have no items
-    // (r0 = EPR) and a thread's last items may fall past the chunk (EX* false: checked).
-    constexpr int RI = C::BN / 4;                        // four-column items per row
-    constexpr int RPT = C::NT / RI;                      // chunk rows per pass of the block
-    constexpr int PER = (C::EPR + RPT - 1) / RPT;        // items per thread per chunk
-    constexpr bool EXA = C::NT % RI == 0 && C::EPR % RPT == 0;
-    constexpr int RIG = RI / 2, RPTG = C::NT / RIG, PERG = (C::EPR + RPTG - 1) / RPTG;  // gated: gate half
-    constexpr bool EXG = C::NT % RIG == 0 && C::EPR % RPTG == 0;
-    constexpr int EB = PER < 4 ? PER : 4;                // residual items per load group
-    float* st = (float*)lds;
-    float* sbias = st + C::EPR * C::EPS;                 // the tile's bias columns
-    const int n0 = tn * C::BN;
-    const bool gated = ep.kind == EP_GATED;
-    const bool rope = ep.kind == EP_HEADS && ep.rope;
-    const int vstart = ep.kind == EP_HEADS ? (2 - ep.which0) * ep.d : 0;  // first v^T product column
-    __syncthreads();  // every wave is done with the stage buffers
-    for (int c = tid; c < C::BN; c += C::NT) {
-        float b = 0.f;
-        if (ep.bias && split == 0) {
-            if (gated) b = ep.bias[c < C::BN / 2 ? tn * (C::BN / 2) + c : ep.F + tn * (C::BN / 2) + c - C::BN / 2];
-            else if (n0 + c < g.N) b = ep.bias[rope ? rope_row(n0 + c, ep.dh, vstart) : n0 + c];
-        }
-        sbias[c] = b;
+__device__ __forceinline__ long weight_row(const EpiParams& ep, int F, int tn, int r) {
+    const int w = r / C::WN, x = r - w * C::WN, j = x >> 5, l = x & 31;
+    if (ep.kind == EP_GATED) {
+        bool up;
+        const int c = gated_col<C::TN>(j, l, up);
+        return (long)tn * (C::BN / 2) + w * (C::WN / 2) + c + (up ? F : 0);
     }
-    // operand pointers and the token split held in registers before any store (a pointer
-    // picked from the argument block later would be a memory load, and waiting for it
-    // would wait for every store issued before)
-    bf16* const qptr = (bf16*)ep.q;
-    bf16* const kptr = (bf16*)ep.k;
+    const long n = (long)tn * C::BN + w * C::WN + tile_col<C::TN>(j, l);
+    if (ep.kind == EP_HEADS && ep.rope) return rope_row(n, ep.dh, (long)(2 - ep.which0) * ep.d);
+    return n;
+}
+
+// 4 x 4 transpose of 32-bit values within each quad of lanes: v[k] of lane q becomes v[q] of lane k
+// (DPP quad permutes; every lane of the quad active).
+__device__ __forceinline__ uint32_t quad_xor1(uint32_t x) { return __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true); }
+__device__ __forceinline__ uint32_t quad_xor2(uint32_t x) { return __builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true); }
+__device__ __forceinline__ void quad_transpose(uint32_t (&v)[4], int l) {
+    const bool o1 = l & 1, o2 = l & 2;
+    uint32_t a[4];
+#pragma unroll
+    for (int k = 0; k < 4; k += 2) {
+        const uint32_t x = quad_xor1(v[k + 1]), y = quad_xor1(v[k]);
+        a[k] = o1 ? x : v[k];
+        a[k + 1] = o1 ? v[k + 1] : y;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const uint32_t x = quad_xor2(a[k + 2]), y = quad_xor2(a[k]);
+        v[k] = o2 ? x : a[k];
+        v[k + 2] = o2 ? a[k + 2] : y;
+    }
+}
+__device__ __forceinline__ uint32_t pack_bf16(float x, float y) {
+    bf16x2 s;
+    s[0] = f2bf(x);
+    s[1] = f2bf(y);
+    return __builtin_bit_cast(uint32_t, s);
+}
+
+template <class C>
+__device__ __forceinline__ void epilogue(f32x16 (&acc)[C::TM][C::TN], const GemmArgs& g, const EpiParams& ep, int m0,
+                                         int tn, int wm, int wn, int split) {
+    constexpr int TM = C::TM, TN = C::TN;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // nothing derived from it is computed before the main loop
+    const int l = tid & 31, lhalf = (tid >> 5) & 1, lq = l & 3;
+    // first of the four rows of registers 4 q .. 4 q + 3 of MFMA block i
+    auto row_of = [&](int i, int q) { return m0 + C::block_row(wm, i) + lhalf * 4 + q * 8; };
     // sample of a row: floor((row + 0.5) / ntok) in fp32 is exact while row < 2^21
     const float rntok = 1.0f / (float)ep.ntok;
     auto sample_of = [&](int row) { return (int)(((float)row + 0.5f) * rntok); };
-    const int c = (tid % RI) * 4, rr0 = tid < RI * RPT ? tid / RI : C::EPR;  // columns, first row
-    const int cg = (tid % RIG) * 4, rrg0 = tid < RIG * RPTG ? tid / RIG : C::EPR;  // gated
-    const int n = n0 + c;
-    // q/k columns without rotation: projection, head and dims of this thread's columns
-    int proj = 0, hh = 0, j = 0;
-    if (ep.kind == EP_HEADS && n < g.N && n < vstart) {
-        proj = ep.which0 + n / ep.d;
-        const int nn = n - (proj - ep.which0) * ep.d;
-        hh = nn / ep.dh;
-        j = nn - hh * ep.dh;
-    }
-    // rotary q/k columns (pairs adjacent, see rope_row): a thread owns eight consecutive
-    // columns, i.e. the four rotary pairs of dims pj .. pj+3 and pj+dh/2 .. pj+dh/2+3 of head
-    // ph (one head: dh % 8 == 0), so one sine/cosine serves both dims of a pair; invt holds
-    // the pairs' inverse frequencies in turns per token.  Tiles may hold columns of q and k,
-    // or of k and v (v columns go through the V^T path below).
-    constexpr int RIP = C::BN / 8, RPTP = C::NT / RIP, PERP = (C::EPR + RPTP - 1) / RPTP;
-    constexpr bool EXP = C::NT % RIP == 0 && C::EPR % RPTP == 0;
-    const int pc = (tid % RIP) * 8;  // first tile column of the thread's pairs
-    const bool rope_thread = rope && n0 + pc < vstart && n0 + pc < g.N;
-    const bool rope_tile = rope && n0 < vstart;
-    const int rrp0 = tid < RIP * RPTP ? tid / RIP : C::EPR;
-    int ph = 0, pj = 0;
-    float invt[4] = {0.f, 0.f, 0.f, 0.f};
-    bf16* pbase = qptr;
-    if (rope_thread) {
-        const int pn = n0 + pc;
-        const int pproj = ep.which0 + pn / ep.d;
-        const int nn = pn - (pproj - ep.which0) * ep.d;
-        ph = nn / ep.dh;
-        pj = (nn - ph * ep.dh) / 2;
-        pbase = pproj == 0 ? qptr : kptr;
+    // bf16 values o[u] of rows row0 + u, u < 4, column c of this lane -> after a quad transpose the
+    // lane holds row row0 + l % 4 and four columns of its quad, from c - l % 4 on (dst: that place)
+    auto quad_single = [&](const float (&o)[4]) {
+        uint32_t v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-            invt[q] = exp2f(-(2.0f * (float)(pj + q) / (float)ep.dh) * ep.rope_log2_theta) * 0.159154943091895336f;
-    }
-    // V^T columns straight from the accumulators: in the MFMA output layout lane l holds
-    // column l % 32 of a 32 x 32 block and, for register group q, rows q * 8 + (l / 32) * 4
-    // + 0..3, i.e. four consecutive tokens of one V^T row (d % 32 == 0: a block is all V or
-    // none)
-    if (ep.kind == EP_HEADS) {
-        bf16* vt = (bf16*)ep.vt;
+        for (int u = 0; u < 4; ++u) v[u] = __float_as_uint(o[u]);
+        quad_transpose(v, l);
+        return u32x2{pack_bf16(__uint_as_float(v[0]), __uint_as_float(v[1])),
+                     pack_bf16(__uint_as_float(v[2]), __uint_as_float(v[3]))};
+    };
+
+    if (ep.kind == EP_GATED) {
+        const int F = ep.F, c0 = tn * (C::BN / 2) + wn * (C::WN / 2);
+        float b[TN];
 #pragma unroll
-        for (int jj = 0; jj < C::TN; ++jj) {
-            const int nb = n0 + wn0 + jj * 32;  // first product column of the block
-            if (nb < vstart || nb >= g.N) continue;
-            const int nv = nb + lrow - vstart;
-            const int vh = nv / ep.dh, vj = nv - vh * ep.dh;
-            const float bv = ep.bias ? ep.bias[nb + lrow] : 0.f;
+        for (int j = 0; j < TN; ++j) {
+            bool up;
+            const int c = gated_col<TN>(j, l, up);
+            b[j] = ep.bias ? ep.bias[c0 + c + (up ? F : 0)] : 0.f;
+        }
+        with_act(ep.act, [&](auto actc) {
+            constexpr int ACT = decltype(actc)::value;
 #pragma unroll
-            for (int i = 0; i < C::TM; ++i)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int row0 = m0 + wm * C::WM + i * 32 + q * 8 + lhalf * 4;
-                    if (row0 >= g.M) continue;
-                    const int bs0 = sample_of(row0), tok0 = row0 - bs0 * ep.ntok;
-                    float o[4];
+                    const int row = row_of(i, q) + lq;
+                    bf16* const out = (bf16*)ep.out + (long)row * ep.ldo + c0 + (l & ~3);
+                    constexpr int H = TN / 2;
+                    // gate block j pairs with up block j + (TN + 1) / 2
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) o[u] = acc[i][jj][q * 4 + u] + bv;
-                    if (tok0 % 4 == 0 && tok0 + 3 < ep.ntok && row0 + 3 < g.M) {
-                        store_bf16x4(vt + (((long)bs0 * ep.H + vh) * ep.dh + vj) * ep.np + tok0, o);
-                    } else {
+                    for (int j = 0; j < H; ++j) {
+                        constexpr int UP = (TN + 1) / 2;
+                        float o[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            o[u] = act_fn<ACT>(acc[i][j][q * 4 + u] + b[j]) * (acc[i][UP + j][q * 4 + u] + b[UP + j]);
+                        const u32x2 s = quad_single(o);
+                        if (row < g.M) *(u32x2*)(out + j * 32) = s;
+                    }
+                    if constexpr (TN % 2) {
+                        // lanes 0..15 of the middle block hold gate columns, 16..31 their up columns
+                        float o[4];
+#pragma unroll
                         for (int u = 0; u < 4; ++u) {
-                            const int row = row0 + u;
-                            if (row >= g.M) break;
-                            const int bs = sample_of(row), tok = row - bs * ep.ntok;
-                            vt[(((long)bs * ep.H + vh) * ep.dh + vj) * ep.np + tok] = f2bf(o[u]);
+                            const float x = acc[i][H][q * 4 + u] + b[H];
+                            const float y = __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), 0x401F));  // l ^ 16
+                            o[u] = act_fn<ACT>(x) * y;
                         }
+                        const u32x2 s = quad_single(o);
+                        if (l < 16 && row < g.M) *(u32x2*)(out + H * 32) = s;
                     }
                 }
-        }
+        });
+        return;
     }
-    // chunk ch holds MFMA row block ch of every wave row, so each wave's accumulators die
-    // chunk by chunk; chunk row rr is tile row (rr / 32) * WM + ch * 32 + rr % 32
-#pragma unroll 1
-    for (int ch = 0; ch < C::TM; ++ch) {
-        // static register indices: the chunk loop itself is not unrolled
+
+    // column groups: a pair of neighbouring columns from blocks j, j + 1 (V = 2), or one column of a
+    // last single block (V = 1)
+    const int nw = tn * C::BN + wn * C::WN;  // the wave's first product column
+    auto groups = [&](auto&& f) {
+        if constexpr (TN >= 2) f(IntC<0>{}, IntC<2>{}, nw + 2 * l);
+        if constexpr (TN >= 4) f(IntC<2>{}, IntC<2>{}, nw + 64 + 2 * l);
+        if constexpr (TN % 2) f(IntC<TN - 1>{}, IntC<1>{}, nw + (TN - 1) * 32 + l);
+    };
+    // rows row0 .. row0 + 3 of a group's columns n .. n + V - 1 as bf16: one store of the quad's 4 V
+    // columns of row row0 + l % 4 at dst (a pointer to column n - V (l % 4) of that row); cols: how
+    // many of them exist (a multiple of 4; <= 0: none)
+    auto store_quad = [&](auto vc, bf16* dst, const float (*o)[decltype(vc)::value], int cols) {
+        constexpr int V = decltype(vc)::value;
+        if constexpr (V == 2) {
+            uint32_t v[4];
 #pragma unroll
-        for (int i = 0; i < C::TM; ++i) {
-            if (i != ch) continue;
-#pragma unroll
-            for (int jj = 0; jj < C::TN; ++jj)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = wm * 32 + (r >> 2) * 8 + lhalf * 4 + (r & 3);
-                    st[row * C::EPS + wn0 + jj * 32 + lrow] = acc[i][jj][r];
-                }
+            for (int u = 0; u < 4; ++u) v[u] = pack_bf16(o[u][0], o[u][1]);
+            quad_transpose(v, l);
+            if (cols >= 8) *(u32x4*)dst = u32x4{v[0], v[1], v[2], v[3]};
+            else if (cols >= 4) *(u32x2*)dst = u32x2{v[0], v[1]};
+        } else {
+            const float t[4] = {o[0][0], o[1][0], o[2][0], o[3][0]};
+            const u32x2 s = quad_single(t);
+            if (cols >= 4) *(u32x2*)dst = s;
         }
-        __syncthreads();
-        auto grow = [&](int rr) { return m0 + (rr >> 5) * C::WM + ch * 32 + (rr & 31); };
-        if (ep.kind == EP_GATED) {
-            const f32x4 bg = ld4(sbias + cg), bu = ld4(sbias + C::BN / 2 + cg);
+    };
+
+    if (ep.kind == EP_ACT) {
+        groups([&](auto jc, auto vc, int n) {
+            constexpr int J = decltype(jc)::value, V = decltype(vc)::value;
+            float b[V];
+#pragma unroll
+            for (int v = 0; v < V; ++v) b[v] = ep.bias && n < g.N ? ep.bias[n + v] : 0.f;
+            const int nq = n - V * lq;
             with_act(ep.act, [&](auto actc) {
                 constexpr int ACT = decltype(actc)::value;
-#pragma unroll 2
-                for (int u = 0; u < PERG; ++u) {
-                    const int rr = rrg0 + u * RPTG, row = grow(rr);
-                    if (!EXG && rr >= C::EPR) continue;
-                    const f32x4 gv = ld4(st + rr * C::EPS + cg), uv = ld4(st + rr * C::EPS + C::BN / 2 + cg);
-                    if (row >= g.M) continue;
-                    float o[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) o[q] = act_fn<ACT>(gv[q] + bg[q]) * (uv[q] + bu[q]);
-                    store_bf16x4((bf16*)ep.out + (long)row * ep.ldo + tn * (C::BN / 2) + cg, o);
-                }
-            });
-        } else if (ep.kind == EP_ACT) {
-            const f32x4 bb = ld4(sbias + c);
-            with_act(ep.act, [&](auto actc) {
-                constexpr int ACT = decltype(actc)::value;
-#pragma unroll 2
-                for (int u = 0; u < PER; ++u) {
-                    const int rr = rr0 + u * RPT, row = grow(rr);
-                    if (!EXA && rr >= C::EPR) continue;
-                    const f32x4 v = ld4(st + rr * C::EPS + c);
-                    if (row >= g.M || n >= g.N) continue;
-                    const f32x4 rb = ep.rowbias ? ld4(ep.rowbias + (long)sample_of(row) * ep.rowbias_ld + n)
-                                                : f32x4{0.f, 0.f, 0.f, 0.f};
-                    float o[4];
+                for (int i = 0; i < TM; ++i) {
+                    float rb[V] = {};
+                    int bs = -1;  // sample whose row bias rb holds (rows rise: it changes rarely)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) o[q] = act_fn<ACT>((v[q] + bb[q]) + rb[q]);
-                    store_bf16x4((bf16*)ep.out + (long)row * ep.ldo + n, o);
-                }
-            });
-        } else if (ep.kind == EP_RESID || ep.kind == EP_SKIP || ep.kind == EP_PARTIAL) {
-            // EP_RESID: v = (acc + bias) [* gate]; h += v; delta = v | delta += v; hcopy = bf16(h)
-            // EP_SKIP:  h = acc + bias [+ cached delta]; hcopy = bf16(h)
-            // EP_PARTIAL: part s = acc (+ bias in range 0), as EP_SKIP into h + s * part_stride
-            // The global operands of a group of EB items are loaded before any of its stores.
-            const bool resid = ep.kind == EP_RESID;
-            const bool rd_delta = resid ? ep.delta_mode == 2 : ep.kind == EP_SKIP && ep.delta_mode == 1;
-            float* const hdst = ep.kind == EP_PARTIAL ? ep.h + (long)split * ep.part_stride : ep.h;
-            const f32x4 bb = ld4(sbias + c);
-            const int nl = min(n, g.N - 4);  // load column (N % 4 == 0)
-#pragma unroll 1
-            for (int u0 = 0; u0 < PER; u0 += EB) {
-                f32x4 hv[EB], dv[EB], gt[EB];
+                    for (int q = 0; q < 4; ++q) {
+                        const int row0 = row_of(i, q);
+                        float o[4][V];
 #pragma unroll
-                for (int w = 0; w < EB; ++w) {
-                    // clamped row and column: every load stays inside the operands
-                    const int row = min(grow(rr0 + (u0 + w) * RPT), g.M - 1);
-                    const long idx = (long)row * ep.d + nl;
-                    hv[w] = resid ? ld4(ep.h + idx) : f32x4{0.f, 0.f, 0.f, 0.f};
-                    dv[w] = rd_delta ? ld4(ep.delta + idx) : f32x4{0.f, 0.f, 0.f, 0.f};
-                    gt[w] = ep.gate ? ld4(ep.gate + (long)sample_of(row) * ep.gate_ld + nl) : f32x4{1.f, 1.f, 1.f, 1.f};
-                }
+                        for (int u = 0; u < 4; ++u) {
+                            if (ACT == ACT_NONE && ep.rowbias) {
+                                const int s = sample_of(min(row0 + u, g.M - 1));
+                                if (s != bs && n < g.N)
 #pragma unroll
-                for (int w = 0; w < EB; ++w) {
-                    const int rr = rr0 + (u0 + w) * RPT, row = grow(rr);
-                    if (!EXA && rr >= C::EPR) continue;  // also items u0 + w >= PER
-                    const f32x4 v = ld4(st + rr * C::EPS + c);
-                    if (row >= g.M || n >= g.N) continue;
-                    const long idx = (long)row * ep.d + n;
-                    float x[4], hn[4];
-                    if (resid) {
-                        float dn[4];
+                                    for (int v = 0; v < V; ++v) rb[v] = ep.rowbias[(long)s * ep.rowbias_ld + n + v];
+                                bs = s;
+                            }
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            x[q] = v[q] + bb[q];
-                            if (ep.gate) x[q] *= gt[w][q];
-                            hn[q] = hv[w][q] + x[q];
-                            dn[q] = dv[w][q] + x[q];
+                            for (int v = 0; v < V; ++v) o[u][v] = act_fn<ACT>((acc[i][J + v][q * 4 + u] + b[v]) + rb[v]);
                         }
-                        *(f32x4*)(ep.h + idx) = f32x4{hn[0], hn[1], hn[2], hn[3]};
-                        if (ep.delta_mode == 1) *(f32x4*)(ep.delta + idx) = f32x4{x[0], x[1], x[2], x[3]};
-                        else if (ep.delta_mode == 2) *(f32x4*)(ep.delta + idx) = f32x4{dn[0], dn[1], dn[2], dn[3]};
-                    } else {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            hn[q] = v[q] + bb[q];
-                            if (rd_delta) hn[q] = hn[q] + dv[w][q];
-                        }
-                        *(f32x4*)(hdst + idx) = f32x4{hn[0], hn[1], hn[2], hn[3]};
+                        const int row = row0 + lq;
+                        store_quad(vc, (bf16*)ep.out + (long)row * ep.ldo + nq, o, row < g.M ? g.N - nq : 0);
                     }
-                    if (ep.hcopy) store_bf16x4((bf16*)ep.hcopy + idx, hn);
                 }
+            });
+        });
+    } else if (ep.kind == EP_HEADS) {
+        const int vstart = (2 - ep.which0) * ep.d;  // first v^T product column
+        bf16* const qptr = (bf16*)ep.q;
+        bf16* const kptr = (bf16*)ep.k;
+        bf16* const vt = (bf16*)ep.vt;
+        groups([&](auto jc, auto vc, int n) {
+            constexpr int J = decltype(jc)::value, V = decltype(vc)::value;
+            if (n >= g.N) return;
+            if (n >= vstart) {
+                // V^T: four consecutive tokens of a row per store
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    const int nv = n + v - vstart, vh = nv / ep.dh, vj = nv - vh * ep.dh;
+                    const float bv = ep.bias ? ep.bias[n + v] : 0.f;
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const int row0 = row_of(i, q);
+                            if (row0 >= g.M) continue;
+                            const int bs0 = sample_of(row0), tok0 = row0 - bs0 * ep.ntok;
+                            float o[4];
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) o[u] = acc[i][J + v][q * 4 + u] + bv;
+                            if (tok0 % 4 == 0 && tok0 + 3 < ep.ntok && row0 + 3 < g.M) {
+                                store_bf16x4(vt + (((long)bs0 * ep.H + vh) * ep.dh + vj) * ep.np + tok0, o);
+                            } else {
+#pragma unroll
+                                for (int u = 0; u < 4; ++u) {
+                                    const int row = row0 + u;
+                                    if (row >= g.M) break;
+                                    const int bs = sample_of(row), tok = row - bs * ep.ntok;
+                                    vt[(((long)bs * ep.H + vh) * ep.dh + vj) * ep.np + tok] = f2bf(o[u]);
+                                }
+                            }
+                        }
+                }
+                return;
             }
-        } else if (rope_tile) {
-            // rotation of each pair by the token's angle: hardware sine/cosine (v_sin_f32 /
-            // v_cos_f32 take turns) of the fractional turn; the turn count carries ~1e-4 rad of
-            // fp32 rounding at 1024 tokens, far below the bf16 resolution of the output
-            const int hd = ep.dh / 2;
-            const f32x4 ba = ld4(sbias + pc), bb = ld4(sbias + pc + 4);
-#pragma unroll 2
-            for (int u = 0; u < PERP; ++u) {
-                const int rr = rrp0 + u * RPTP, row = grow(rr);
-                if (!EXP && rr >= C::EPR) continue;
-                const f32x4 va = ld4(st + rr * C::EPS + pc), vb = ld4(st + rr * C::EPS + pc + 4);
-                if (row >= g.M || !rope_thread) continue;
-                const int bs = sample_of(row), tok = row - bs * ep.ntok;
-                // columns pc + 2q and pc + 2q + 1 hold dims pj + q and pj + q + dh/2
-                const float x1[4] = {va[0] + ba[0], va[2] + ba[2], vb[0] + bb[0], vb[2] + bb[2]};
-                const float x2[4] = {va[1] + ba[1], va[3] + ba[3], vb[1] + bb[1], vb[3] + bb[3]};
-                float o1[4], o2[4];
+            // q / k columns.  Quads of lanes share one head: d, vstart and dh are multiples of 8 (or
+            // dh of 4 only, whose columns are stored one by one below)
+            const int proj = ep.which0 + n / ep.d, nn = n - (proj - ep.which0) * ep.d;
+            const int hh = nn / ep.dh, j = nn - hh * ep.dh;
+            bf16* const base = (proj == 0 ? qptr : kptr) + (long)hh * ep.np * ep.dh;
+            const long bstride = (long)ep.H * ep.np * ep.dh;
+            if (!ep.rope) {
+                float b[V];
+#pragma unroll
+                for (int v = 0; v < V; ++v) b[v] = ep.bias ? ep.bias[n + v] : 0.f;
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int row0 = row_of(i, q);
+                        float o[4][V];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+#pragma unroll
+                            for (int v = 0; v < V; ++v) o[u][v] = acc[i][J + v][q * 4 + u] + b[v];
+                        if (ep.dh % 8 == 0) {
+                            const int row = row0 + lq, bs = sample_of(row), tok = row - bs * ep.ntok;
+                            store_quad(vc, base + bs * bstride + (long)tok * ep.dh + j - V * lq, o, row < g.M ? 8 : 0);
+                        } else {
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                const int row = row0 + u, bs = sample_of(row), tok = row - bs * ep.ntok;
+                                if (row >= g.M) break;
+#pragma unroll
+                                for (int v = 0; v < V; ++v) base[bs * bstride + (long)tok * ep.dh + j + v] = f2bf(o[u][v]);
+                            }
+                        }
+                    }
+                return;
+            }
+            // rotary columns (pairs adjacent, see rope_row): product columns 2 p and 2 p + 1 of a
+            // head hold dims p and p + dh/2.  A group of two is a whole pair; in a single block the
+            // pair's other column is in lane l ^ 1.  The angle is the fractional turn of token x
+            // inverse frequency (v_sin_f32 / v_cos_f32 take turns); the turn count carries ~1e-4 rad
+            // of fp32 rounding at 1024 tokens, far below the bf16 resolution of the output
+            const int hd = ep.dh / 2, pj = j / 2;
+            float b[V];
+#pragma unroll
+            for (int v = 0; v < V; ++v) b[v] = ep.bias ? ep.bias[rope_row(n + v, ep.dh, vstart)] : 0.f;
+            const float invt = exp2f(-(2.0f * (float)pj / (float)ep.dh) * ep.rope_log2_theta) * 0.159154943091895336f;
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const float t = (float)tok * invt[q];
-                    const float f = t - rintf(t);
-                    const float sn = __builtin_amdgcn_sinf(f), cs = __builtin_amdgcn_cosf(f);
-                    o1[q] = x1[q] * cs - x2[q] * sn;
-                    o2[q] = x2[q] * cs + x1[q] * sn;
-                }
-                bf16* const dst = pbase + (((long)bs * ep.H + ph) * ep.np + tok) * ep.dh + pj;
-                store_bf16x4(dst, o1);
-                store_bf16x4(dst + hd, o2);
-            }
-        } else if (ep.kind == EP_HEADS) {
-            // q/k columns without rotation, row-major (a thread stores four dims of one token)
-            if (n < g.N && n < vstart) {
-                const f32x4 bb = ld4(sbias + c);
-                bf16* const base = proj == 0 ? qptr : kptr;
-#pragma unroll 2
-                for (int u = 0; u < PER; ++u) {
-                    const int rr = rr0 + u * RPT, row = grow(rr);
-                    if (!EXA && rr >= C::EPR) continue;
-                    const f32x4 v = ld4(st + rr * C::EPS + c);
-                    if (row >= g.M) continue;
-                    const int bs = sample_of(row), tok = row - bs * ep.ntok;
-                    float o[4];
+                    const int row0 = row_of(i, q);
+                    float o1[4], o2[4];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) o[q] = v[q] + bb[q];
-                    store_bf16x4(base + (((long)bs * ep.H + hh) * ep.np + tok) * ep.dh + j, o);
+                    for (int u = 0; u < 4; ++u) {
+                        const int bs = sample_of(row0 + u), tok = row0 + u - bs * ep.ntok;
+                        const float t = (float)tok * invt;
+                        const float f = t - rintf(t);
+                        const float sn = __builtin_amdgcn_sinf(f), cs = __builtin_amdgcn_cosf(f);
+                        const float x = acc[i][J][q * 4 + u] + b[0];
+                        if constexpr (V == 2) {
+                            const float x2 = acc[i][J + 1][q * 4 + u] + b[1];
+                            o1[u] = x * cs - x2 * sn;
+                            o2[u] = x2 * cs + x * sn;
+                        } else {
+                            const float y = __uint_as_float(quad_xor1(__float_as_uint(x)));
+                            o1[u] = (l & 1) ? x * cs + y * sn : x * cs - y * sn;
+                        }
+                    }
+                    if constexpr (V == 2) {
+                        // four neighbouring pairs of token row0 + l % 4: dims p .. p + 3 and their partners
+                        const u32x2 s1 = quad_single(o1), s2 = quad_single(o2);
+                        const int row = row0 + lq, bs = sample_of(row), tok = row - bs * ep.ntok;
+                        bf16* const dst = base + bs * bstride + (long)tok * ep.dh + pj - lq;
+                        if (row < g.M) {
+                            *(u32x2*)dst = s1;
+                            *(u32x2*)(dst + hd) = s2;
+                        }
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const int row = row0 + u, bs = sample_of(row), tok = row - bs * ep.ntok;
+                            if (row < g.M) base[bs * bstride + (long)tok * ep.dh + pj + ((l & 1) ? hd : 0)] = f2bf(o1[u]);
+                        }
+                    }
                 }
-            }
-        }
-        __syncthreads();
+        });
+    } else {
+        // EP_RESID: v = (acc + bias) [* gate]; h += v; delta = v | delta += v; hcopy = bf16(h)
+        // EP_SKIP:  h = acc + bias [+ cached delta]; hcopy = bf16(h)
+        // EP_PARTIAL: part s = acc (+ bias in range 0), as EP_SKIP into h + s * part_stride
+        // Lane pairs (V = 2) or quads (V = 1) exchange rows, so a lane handles four neighbouring
+        // columns of a row: two rows per lane and register group (V = 2), or one (V = 1).
+        const bool resid = ep.kind == EP_RESID;
+        const bool rd_delta = resid ? ep.delta_mode == 2 : ep.kind == EP_SKIP && ep.delta_mode == 1;
+        float* const hdst = ep.kind == EP_PARTIAL ? ep.h + (long)split * ep.part_stride : ep.h;
+        groups([&](auto jc, auto vc, int n) {
+            constexpr int J = decltype(jc)::value, V = decltype(vc)::value;
+            constexpr int RL = V;                     // rows per lane and register group
+            constexpr int QB = 2;                     // register groups per load batch
+            const int n4 = V == 2 ? n - 2 * (l & 1) : n - lq;  // first of the lane's four columns
+            const int nl = min(n4, g.N - 4);          // clamped: every load stays inside
+            float b[V];
+#pragma unroll
+            for (int v = 0; v < V; ++v) b[v] = ep.bias && split == 0 && n < g.N ? ep.bias[n + v] : 0.f;
+            // row of the lane's w-th row in register group q of block i
+            auto lane_row = [&](int i, int q, int w) { return row_of(i, q) + (V == 2 ? 2 * w + (l & 1) : lq); };
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int q0 = 0; q0 < 4; q0 += QB) {
+                    f32x4 hv[QB][RL], dv[QB][RL], gt[QB][RL];
+#pragma unroll
+                    for (int q = 0; q < QB; ++q)
+#pragma unroll
+                        for (int w = 0; w < RL; ++w) {
+                            const int row = min(lane_row(i, q0 + q, w), g.M - 1);
+                            const long idx = (long)row * ep.d + nl;
+                            hv[q][w] = resid ? *(const f32x4*)(ep.h + idx) : f32x4{0.f, 0.f, 0.f, 0.f};
+                            dv[q][w] = rd_delta ? *(const f32x4*)(ep.delta + idx) : f32x4{0.f, 0.f, 0.f, 0.f};
+                            gt[q][w] = ep.gate ? *(const f32x4*)(ep.gate + (long)sample_of(row) * ep.gate_ld + nl)
+                                               : f32x4{1.f, 1.f, 1.f, 1.f};
+                        }
+#pragma unroll
+                    for (int q = 0; q < QB; ++q) {
+                        f32x4 x[RL];
+                        if constexpr (V == 2) {
+                            // rows 2 w (even lanes) and 2 w + 1 (odd lanes): own pair and the neighbour's
+#pragma unroll
+                            for (int w = 0; w < 2; ++w) {
+                                const int r = (q0 + q) * 4 + 2 * w;
+#pragma unroll
+                                for (int v = 0; v < 2; ++v) {
+                                    const float e = acc[i][J + v][r] + b[v], o = acc[i][J + v][r + 1] + b[v];
+                                    const float pe = __uint_as_float(quad_xor1(__float_as_uint(e)));
+                                    const float po = __uint_as_float(quad_xor1(__float_as_uint(o)));
+                                    x[w][v] = (l & 1) ? po : e;
+                                    x[w][2 + v] = (l & 1) ? o : pe;
+                                }
+                            }
+                        } else {
+                            uint32_t t[4];
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) t[u] = __float_as_uint(acc[i][J][(q0 + q) * 4 + u] + b[0]);
+                            quad_transpose(t, l);
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) x[0][u] = __uint_as_float(t[u]);
+                        }
+#pragma unroll
+                        for (int w = 0; w < RL; ++w) {
+                            const int row = lane_row(i, q0 + q, w);
+                            if (row >= g.M || n4 >= g.N) continue;
+                            const long idx = (long)row * ep.d + n4;
+                            f32x4 xx = x[w], hn;
+                            if (ep.gate) xx = xx * gt[q][w];
+                            const f32x4 dn = dv[q][w] + xx;
+                            hn = resid ? hv[q][w] + xx : rd_delta ? dn : xx;
+                            *(f32x4*)(hdst + idx) = hn;
+                            if (resid && ep.delta_mode == 1) *(f32x4*)(ep.delta + idx) = xx;
+                            if (resid && ep.delta_mode == 2) *(f32x4*)(ep.delta + idx) = dn;
+                            if (ep.hcopy) {
+                                const float t[4] = {hn[0], hn[1], hn[2], hn[3]};
+                                store_bf16x4((bf16*)ep.hcopy + idx, t);
+                            }
+                        }
+                    }
+                }
+        });
     }
 }
 
@@ -392,21 +525,17 @@ __device__ __forceinline__ void epilogue(f32x16 (&acc)[C::TM][C::TN], char* lds,
 // the period's MFMAs (part p after MFMA slot p * SLOTS / PARTS), so neither the texture
 // unit nor the LDS sees a burst and both SIMD waves keep issuing MFMAs.
 
-template <class C, bool CONV, bool SPLIT>
+template <class C, bool CONV>
 __global__ __launch_bounds__(C::NT, C::OCC) void gemm_bf16_kernel(GemmArgs g, EpiParams ep) {
     static_assert(C::STAGES == 2, "two LDS stages plus the register stage");
     __shared__ __attribute__((aligned(1024))) char lds[C::LDS_BYTES];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool gated = ep.kind == EP_GATED;
     const int nt_m = (g.M - g.m_begin + C::BM - 1) / C::BM;
     const int nt_n = (g.N + C::BN - 1) / C::BN;
-    // split K: workgroup b takes K range b / T of tile b % T (T tiles); a range's workgroups
-    // keep the tile order of an unsplit launch
-    const int split = SPLIT ? (int)blockIdx.x / (nt_m * nt_n) : 0;
     int tm, tn;
-    tile_at(tile_position((int)blockIdx.x - split * nt_m * nt_n, nt_m * nt_n), nt_m, nt_n, g.band, tm, tn);
+    tile_at(tile_position((int)blockIdx.x, nt_m * nt_n), nt_m, nt_n, g.band, tm, tn);
     const int m0 = g.m_begin + tm * C::BM;
     const int F = g.N / 2;
 
@@ -441,12 +570,7 @@ __global__ __launch_bounds__(C::NT, C::OCC) void gemm_bf16_kernel(GemmArgs g, Ep
     }
 #pragma unroll
     for (int p = 0; p < BP; ++p) {
-        const int r = vr + p * RPP;
-        long gr;
-        if (gated) gr = r < C::BN / 2 ? (long)tn * (C::BN / 2) + r : (long)F + tn * (C::BN / 2) + (r - C::BN / 2);
-        else if (ep.kind == EP_HEADS && ep.rope) gr = rope_row((long)tn * C::BN + r, ep.dh, (long)(2 - ep.which0) * ep.d);
-        else gr = (long)tn * C::BN + r;
-        goff[AP + p] = (unsigned)(gr * g.ldb * 2 + vc * 16);
+        goff[AP + p] = (unsigned)(weight_row<C>(ep, F, tn, vr + p * RPP) * g.ldb * 2 + vc * 16);
     }
     char* const lw = lds + vr * C::ROWB + ((vc ^ ((vr / C::RPB) % C::CH)) << 4);
     // register slot s holds the k tiles t with t % RD == s (s is a compile-time constant at
@@ -454,8 +578,7 @@ __global__ __launch_bounds__(C::NT, C::OCC) void gemm_bf16_kernel(GemmArgs g, Ep
     // buffer (sizes stay below OOB), so the descriptor's range check fails.  The main loop
     // therefore runs whole trips without a branch, the padding tiles add zero products, and
     // the compiler sees the same outstanding loads on every trip.
-    const int KT = (SPLIT ? g.K / g.ksplit : g.K) / C::BK;
-    const int kbase = SPLIT ? split * (g.K / g.ksplit) : 0;  // first column of the workgroup's K range
+    const int KT = g.K / C::BK;
     constexpr unsigned OOB = 0xFFFFFF00u;
     u32x4 vreg[C::RD][PARTS];
     auto gload = [&](int kt, int s, int p) {
@@ -475,9 +598,9 @@ __global__ __launch_bounds__(C::NT, C::OCC) void gemm_bf16_kernel(GemmArgs g, Ep
         } else if (p < AP) {
             const bool second = g.A1 && k0 >= g.K0;
             vreg[s][p] = __builtin_amdgcn_raw_buffer_load_b128(second ? ra1 : ra0, in ? goff[p] : OOB,
-                                                               in ? (second ? (k0 - g.K0) * 2 : (kbase + k0) * 2) : 0, 0);
+                                                               in ? (second ? (k0 - g.K0) * 2 : k0 * 2) : 0, 0);
         } else {
-            vreg[s][p] = __builtin_amdgcn_raw_buffer_load_b128(rb, in ? goff[p] : OOB, in ? (kbase + k0) * 2 : 0, 0);
+            vreg[s][p] = __builtin_amdgcn_raw_buffer_load_b128(rb, in ? goff[p] : OOB, in ? k0 * 2 : 0, 0);
         }
     };
     // stage and part are compile-time constants at every call
@@ -583,22 +706,261 @@ __global__ __launch_bounds__(C::NT, C::OCC) void gemm_bf16_kernel(GemmArgs g, Ep
     static_assert(C::KSTEPS % 2 == 0, "fragment ring");
     constexpr int TRIP = C::RD % 2 ? 2 * C::RD : C::RD;  // whole register rings and LDS stage pairs
     for (int kt = 0; kt < KT; kt += TRIP) static_for<TRIP>([&](auto jc) { iter(kt + decltype(jc)::value, jc); });
-    epilogue<C>(acc, lds, g, ep, m0, tn, wm, wn0, split);
+    epilogue<C>(acc, g, ep, m0, tn, wm, wn, 0);
+}
+
+// --------------------------------------------------------------------------- 256-row kernel
+//
+// 256 x BN block tiles, eight waves, 64-deep k tiles.  Operands go from global memory straight
+// into LDS (buffer_load ... lds, 16 bytes a lane: no staging registers, no ds_write issue); the
+// XOR swizzle of a row's chunks is applied to the lanes' global addresses, since a wave's LDS
+// destination is contiguous.  The waves form two groups (one wave of each per SIMD) that run the
+// same phases half a phase apart: while one group issues its MFMAs the other reads its fragments
+// and issues loads, so each SIMD always has one wave in the matrix cores.
+//
+// A k tile is two phases.  Phase 0 reads the fragments of A rows [0, 128) and of all of B, phase
+// 1 those of A rows [128, 256); a phase's LDS regions are free once both groups have read them, so
+// they are refilled two k tiles ahead, one to two tiles before they are read (128 KB of LDS at
+// BN = 256 keep ~1.5 tiles in flight).  Each wave waits for its own loads by count (vmcnt), one
+// phase before the data is read, and the barrier in between makes that true of every wave.
+//
+// What bounds it: the matrix cores' power.  On the 8192^3 product the loop runs at 1830 TFLOP/s on
+// zero operands and 1350 on Gaussian ones (hipBLASLt: 1440); the register-staged loop it replaced
+// reached 1220-1245 there.  Same run, plain bf16 store, 256 x 256 tiles, before -> after:
+// 8192 x 10240 x 1280 241 -> 201 us, 1024 x 24576 x 4096 222 -> 182, 8192 x 4608 x 1152 116 -> 90,
+// 8192 x 1280 x 5120 121 -> 102.  With the epilogues (one op in a loop, weights cold): GELU(tanh)
+// 8192 x 4608 x 1152 107 -> 93 us, GELU(erf) 8256 x 4096 x 1024 104 -> 92, GEGLU 8192 x 10240 x 1280
+// 213 -> 196, residual 8192 x 1280 x 5120 106 -> 97, 3 x 3 convolution 8192 x 1280 channels 237 -> 211;
+// in a whole step the clock falls with the power drawn and half of that remains.  Two workgroups of 128 x 256 per CU instead (epilogues overlapped)
+// ran at 1030 on 8192^3: they move 1.5x the operand bytes.
+
+template <int BN_, int WGM_, int WGN_>
+struct PPCfg {
+    static constexpr int BM = 256, BN = BN_, WGM = WGM_, WGN = WGN_, NT = 512, NW = 8;
+    static constexpr int RW = 128 / WGM;                 // a wave's rows of each 128-row half
+    static constexpr int CB = RW / 32, TM = 2 * CB;      // MFMA row blocks per half, per wave
+    static constexpr int WN = BN / WGN, TN = WN / 32;
+    static constexpr int BP = BN / 64, BL = BP / 2;      // B parts (64 rows) per tile; those loaded in phase 1
+    static constexpr int A_HALF = 16384, A_STAGE = 32768, B_STAGE = BN * 128, B_LDS = 2 * A_STAGE;
+    static constexpr int LDS_BYTES = B_LDS + 2 * B_STAGE;
+    __device__ static __forceinline__ int block_row(int wm, int i) { return (i / CB) * 128 + wm * RW + (i % CB) * 32; }
+    static_assert(WGM * WGN == NW && RW % 32 == 0 && WN % 32 == 0 && BN % 64 == 0, "wave tile");
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS");
+};
+
+// 16 bytes a lane from buffer r at voff + soff to LDS byte address lds + 16 lane (voff out of the
+// descriptor's range: zeros).  Counted in vmcnt; the caller waits.  m0 (the LDS address) is used by
+// nothing else in these kernels.
+__device__ __forceinline__ void dma16(unsigned lds, unsigned voff, u32x4 r, unsigned soff) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 :: "s"(lds), "v"(voff), "s"(r), "s"(__builtin_amdgcn_readfirstlane(soff)) : "memory");
+}
+template <int N>
+__device__ __forceinline__ void vm_wait() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// workgroup barrier without the waits of __syncthreads (outstanding loads stay in flight)
+__device__ __forceinline__ void raw_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+// buffer descriptor as four scalars (nothing is in range when bytes = 0)
+__device__ __forceinline__ u32x4 buf_desc(const void* base, unsigned bytes) {
+    const uint64_t p = (uint64_t)base;
+    u32x4 r;
+    r[0] = __builtin_amdgcn_readfirstlane((unsigned)p);
+    r[1] = __builtin_amdgcn_readfirstlane((unsigned)(p >> 32));
+    r[2] = bytes;
+    r[3] = 0x00020000;
+    return r;
+}
+
+template <class C, bool CONV, bool SPLIT>
+__global__ __launch_bounds__(C::NT, 2) void gemm_pp_kernel(GemmArgs g, EpiParams ep) {
+    __shared__ __attribute__((aligned(1024))) char lds[C::LDS_BYTES];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nt_m = (g.M - g.m_begin + C::BM - 1) / C::BM;
+    const int nt_n = (g.N + C::BN - 1) / C::BN;
+    // split K: workgroup b takes K range b / T of tile b % T (T tiles)
+    const int split = SPLIT ? (int)blockIdx.x / (nt_m * nt_n) : 0;
+    int tm, tn;
+    tile_at(tile_position((int)blockIdx.x - split * nt_m * nt_n, nt_m * nt_n), nt_m, nt_n, g.band, tm, tn);
+    const int m0 = g.m_begin + tm * C::BM;
+    const int F = g.N / 2;
+    const int KT = (SPLIT ? g.K / g.ksplit : g.K) / 64;
+    const int kbase = SPLIT ? split * (g.K / g.ksplit) : 0;
+    const unsigned bytesA = (unsigned)((long)g.M * g.lda0 * 2), bytesB = (unsigned)((long)g.N * g.ldb * 2);
+    constexpr unsigned OOB = 0xFFFFFF00u;
+
+    // Load part p of an operand tile: rows 64 p + 8 wave + lane / 8, the 16-byte chunk of the row
+    // that belongs at LDS position lane % 8.  A parts 0, 1 are the first half's rows.
+    const int prow = wave * 8 + (lane >> 3);
+    const int pch = ((lane & 7) ^ ((prow >> 1) & 7)) * 16;  // swizzle key of the row: 64-row parts keep it
+    unsigned aoff[4], boff[C::BP];  // both A sources share the row pitch
+    int gpos[CONV ? 4 : 1];         // convolution: grid position (y << 16 | x) of the A row
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const int row = m0 + p * 64 + prow;
+        aoff[p] = (unsigned)((long)row * g.lda0 * 2 + pch);
+        if constexpr (CONV) {
+            const int side = g.conv_side, pix = row % (side * side), y = pix / side;
+            gpos[p] = (y << 16) | (pix - y * side);
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < C::BP; ++p) {
+        boff[p] = (unsigned)(weight_row<C>(ep, F, tn, p * 64 + prow) * g.ldb * 2 + pch);
+    }
+    const unsigned lw = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds + wave * 1024;
+    // k tile t's half h of A into stage t % 2 (stage and part numbers are compile-time constants
+    // at every call); tiles at or past K load nothing but still count
+    auto load_a = [&](int t, int stage, int h) {
+        const bool in = t < KT;
+        const int k0 = t * 64;
+        const unsigned l = lw + stage * C::A_STAGE + h * C::A_HALF;
+        if constexpr (CONV) {
+            // the k tile lies inside one tap (conv_c % 64 == 0): shift the row by the tap's grid
+            // offset, or load zeros (an out-of-range offset) where it leaves the grid
+            const int tap = k0 / g.conv_c, c0 = k0 - tap * g.conv_c;
+            const int ky = tap / 3, dy = ky - 1, dx = tap - ky * 3 - 1;
+            const int shift = (dy * g.conv_side + dx) * (int)g.lda0 * 2;
+            const u32x4 r = buf_desc(g.A0, bytesA);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int yy = (gpos[h * 2 + i] >> 16) + dy, xx = (gpos[h * 2 + i] & 0xFFFF) + dx;
+                const bool ok = in && (unsigned)yy < (unsigned)g.conv_side && (unsigned)xx < (unsigned)g.conv_side;
+                dma16(l + i * 8192, ok ? (unsigned)((int)aoff[h * 2 + i] + shift) : OOB, r, in ? c0 * 2 : 0);
+            }
+        } else {
+            const bool second = g.A1 && k0 >= g.K0;
+            const u32x4 r = buf_desc(second ? g.A1 : g.A0, in ? bytesA : 0);
+            const unsigned so = in ? (second ? (k0 - g.K0) * 2 : (kbase + k0) * 2) : 0;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) dma16(l + i * 8192, aoff[h * 2 + i], r, so);
+        }
+    };
+    auto load_b = [&](int t, int stage, auto from, auto to) {
+        const bool in = t < KT;
+        const u32x4 r = buf_desc(g.B, in ? bytesB : 0);
+#pragma unroll
+        for (int p = decltype(from)::value; p < decltype(to)::value; ++p)
+            dma16(lw + C::B_LDS + stage * C::B_STAGE + p * 8192, boff[p], r, in ? (kbase + t * 64) * 2 : 0);
+    };
+
+    const int wm = wave / C::WGN, wn = wave % C::WGN, wn0 = wn * C::WN;
+    const int lrow = lane & 31, lhalf = lane >> 5;
+    const char *fa[4], *fb[4];  // fragment addresses of the four 16-deep k steps
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int sw = ((q * 2 + lhalf) ^ ((lrow >> 1) & 7)) << 4;
+        fa[q] = lds + (wm * C::RW + lrow) * 128 + sw;
+        fb[q] = lds + C::B_LDS + (wn0 + lrow) * 128 + sw;
+    }
+    f32x16 acc[C::TM][C::TN];
+#pragma unroll
+    for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+        for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    bf16x8 af[C::CB][4], bfr[C::TN][4];
+    auto read_a = [&](int stage, int h) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int i = 0; i < C::CB; ++i)
+                af[i][q] = *(const bf16x8*)(fa[q] + stage * C::A_STAGE + h * C::A_HALF + i * 4096);
+    };
+    auto read_b = [&](int stage) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int j = 0; j < C::TN; ++j) bfr[j][q] = *(const bf16x8*)(fb[q] + stage * C::B_STAGE + j * 4096);
+    };
+    auto mfmas = [&](int h) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int i = 0; i < C::CB; ++i)
+#pragma unroll
+                for (int j = 0; j < C::TN; ++j)
+                    acc[h * C::CB + i][j] =
+                        __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i][q], bfr[j][q], acc[h * C::CB + i][j], 0, 0, 0);
+    };
+    // end of a phase's reads: the fragments are in registers before the other group may refill
+    auto turn = [&] {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        raw_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr IntC<0> B0{};
+    constexpr IntC<C::BL> BM_{};
+    constexpr IntC<C::BP> B1{};
+    // load order per tile: A half 0 and the first BL B parts (phase 1 of tile t - 2), the other B
+    // parts and A half 1 (phase 0 of tile t - 1).  Before phase 1 of tile t is read, at most the
+    // loads issued after its A half 1 may be outstanding: phase 1 of t - 1 (2 + BL) and phase 0
+    // of t (BP - BL + 2); before phase 0 of tile t: its A half 1 (2) and phase 1 of t - 1 (2 + BL).
+    constexpr int W0 = C::BP + 4, W1 = C::BL + 4;
+    load_a(0, 0, 0);
+    load_b(0, 0, B0, B1);
+    load_a(0, 0, 1);
+    load_a(1, 1, 0);
+    load_b(1, 1, B0, BM_);
+    vm_wait<W1>();
+    raw_barrier();
+    const bool late = wave >= 4;  // the second group runs half a phase behind
+    if (late) raw_barrier();
+    auto tile = [&](int t, auto sc) {
+        constexpr int s = decltype(sc)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        read_b(s);
+        read_a(s, 0);
+        load_b(t + 1, s ^ 1, BM_, B1);
+        load_a(t + 1, s ^ 1, 1);
+        vm_wait<W0>();
+        turn();
+        mfmas(0);
+        __builtin_amdgcn_sched_barrier(0);
+        raw_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        read_a(s, 1);
+        load_a(t + 2, s, 0);
+        load_b(t + 2, s, B0, BM_);
+        vm_wait<W1>();
+        turn();
+        mfmas(1);
+        __builtin_amdgcn_sched_barrier(0);
+        raw_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int t = 0; t < KT; t += 2) {
+        tile(t, IntC<0>{});
+        if (t + 1 < KT) tile(t + 1, IntC<1>{});
+    }
+    if (!late) raw_barrier();
+    vm_wait<0>();
+    // the epilogue's arguments are read again here, through an address the compiler cannot see
+    // through, instead of holding their scalars (and what follows from them) across the main loop
+    const char __attribute__((address_space(4)))* args =
+        (const char __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    constexpr int EP_AT = (sizeof(GemmArgs) + alignof(EpiParams) - 1) / alignof(EpiParams) * alignof(EpiParams);
+    epilogue<C>(acc, *(const GemmArgs*)(const char*)args, *(const EpiParams*)(const char*)(args + EP_AT), m0, tn, wm, wn,
+                split);
 }
 
 // --------------------------------------------------------------------------- dispatch
 
 namespace {
-// block tiles (BM, BN); eight waves, 64-deep k tiles, two LDS stages plus RD register slots.
-// Two slots on the smaller tiles: with weights streamed from HBM, one period of a 128 x 128
-// tile is too short for a load to arrive (LLaDA O and W2: -17 % time with two slots); the
-// 256 x 256 tile has a period twice as long and no registers to spare.  (Four waves of
-// 128 x 128, one per SIMD, measured 10-20 % slower on every branch shape.)
-using T256x256 = TileCfg<256, 256, 4, 2, 64, 2, 2, 1>;  // 64 x 128 wave tiles
-using T256x128 = TileCfg<256, 128, 4, 2, 64, 2, 2, 2>;  // 64 x 64
+// block tiles (BM, BN), eight waves, 64-deep k tiles.  The 128-row tiles have two LDS stages plus
+// two register slots: with weights streamed from HBM, one period of a 128 x 128 tile is too short
+// for a load to arrive (LLaDA O and W2: -17 % time with two slots instead of one).
+using T256x256 = PPCfg<256, 2, 4>;                      // 128 x 64 wave tiles
+using T256x192 = PPCfg<192, 4, 2>;                      // 64 x 96
+using T256x128 = PPCfg<128, 4, 2>;                      // 64 x 64
 using T128x256 = TileCfg<128, 256, 2, 4, 64, 2, 2, 2>;  // 64 x 64
 using T128x128 = TileCfg<128, 128, 2, 4, 64, 2, 2, 2>;  // 64 x 32
-using T256x192 = TileCfg<256, 192, 4, 2, 64, 2, 2, 2>;  // 64 x 96
 
 struct Shape { int bm, bn; double rate; };
 // tile id -> block shape and its per-CU throughput relative to 256 x 256 (measured on the
@@ -699,7 +1061,7 @@ bool gemm_bf16_shape_ok(const GemmArgs& g, const EpiParams& e, int tile) {
             g.M % area || g.conv_side >= (1 << 15))
             return false;
     }
-    if (!aligned(e.rowbias, 16) || e.rowbias_ld % 4) return false;
+    if (!aligned(e.rowbias, 16) || e.rowbias_ld % 4 || (e.rowbias && e.act != ACT_NONE)) return false;
     if (g.K % 64 || (g.A1 && (g.K0 % 64 || g.lda1 != g.lda0))) return false;
     if (g.N % 4 || g.lda0 % 8 || (g.A1 && g.lda1 % 8) || g.ldb % 8) return false;  // 16-byte rows
     if (e.kind == EP_GATED && (g.N % s.bn || e.ldo % 4)) return false;
@@ -724,8 +1086,11 @@ static hipError_t run_tile(const GemmArgs& g, const EpiParams& e, hipStream_t st
     const int nt_m = (g.M - g.m_begin + C::BM - 1) / C::BM, nt_n = (g.N + C::BN - 1) / C::BN;
     GemmArgs ga = g;
     ga.band = tile_band(nt_m, nt_n, C::BM, C::BN);
-    hipLaunchKernelGGL((gemm_bf16_kernel<C, CONV, SPLIT>), dim3(nt_m * nt_n * (SPLIT ? g.ksplit : 1)), dim3(C::NT), 0,
-                       st, ga, e);
+    if constexpr (C::BM == 256)
+        hipLaunchKernelGGL((gemm_pp_kernel<C, CONV, SPLIT>), dim3(nt_m * nt_n * (SPLIT ? g.ksplit : 1)), dim3(C::NT), 0,
+                           st, ga, e);
+    else
+        hipLaunchKernelGGL((gemm_bf16_kernel<C, CONV>), dim3(nt_m * nt_n), dim3(C::NT), 0, st, ga, e);
     return hipGetLastError();
 }
 

@@ -441,3 +441,25 @@ def test_heads_kv_only(P, tile, rope):
     for g, r in ((got_k, Kr), (got_v, Vr)):
         assert np.isfinite(g).all()
         assert np.max(np.abs(g - r)) <= 2 ** -7 * np.max(np.abs(r))
+
+
+@pytest.mark.parametrize("tile", TILES)
+@pytest.mark.parametrize("H,dh", [(16, 12), (8, 24)])
+def test_heads_short_dims(P, tile, H, dh):
+    """Head dims that are multiples of 4 only (stored column by column) or smaller than one
+    lane group's 32 columns; two samples of 70 tokens (rows of a tile from both)."""
+    rng = np.random.default_rng(H + dh + tile)
+    B, N, d = 2, 70, H * dh
+    np_ = -(-N // 64) * 64
+    A = synth.store(rng.standard_normal((B * N, d)), "bf16")
+    W = synth.store(rng.standard_normal((3 * d, d)) / np.sqrt(d), "bf16")
+    b = synth.representable(0.1 * rng.standard_normal(3 * d), "bf16")
+    q, k, vt = empty((B * H, np_, dh), "bf16"), empty((B * H, np_, dh), "bf16"), empty((B * H, dh, np_), "bf16")
+    P.op_heads(dev(A), dev(W), q, k, vt, 3, 0, N, H, dh, bias=dev(b), tile=tile)
+    z = decode(A, "bf16") @ decode(W, "bf16").T + b
+    got = [host(q).reshape(B, H, np_, dh)[:, :, :N], host(k).reshape(B, H, np_, dh)[:, :, :N],
+           host(vt).reshape(B, H, dh, np_)[:, :, :, :N].transpose(0, 1, 3, 2)]
+    for i, g in enumerate(got):
+        r = om.heads(z[:, i * d:(i + 1) * d].reshape(B, N, d), H)
+        assert np.isfinite(g).all()
+        assert np.max(np.abs(g - r)) <= 2 ** -7 * np.max(np.abs(r))
