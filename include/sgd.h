@@ -188,16 +188,15 @@ int32_t sgd_s_min_default(int32_t T);
 int sgd_budget_layer_steps(int32_t pct, int32_t L, int32_t T, int64_t* n_star);
 
 /* Device scratch that sgd_schedule_build / sgd_matrix_stats need for `workers` concurrent
- * matrices (fp64 Gram of the short side plus tridiagonal work arrays per worker), for the
- * largest scored matrix of `units`.  The caller allocates it (256-byte aligned) and passes
+ * matrices (fp64 Gram of the short side plus tridiagonal work arrays per worker, at least 4 MiB
+ * each), for the largest scored matrix of `units`.  The caller allocates it (256-byte aligned) and passes
  * it in; the library allocates no device memory. */
 int sgd_schedule_workspace_bytes(const sgd_unit* units, int32_t L, int32_t workers, size_t* bytes);
 
 /* Alg. 1: score every matrix of every unit on the GPU (fp64 Gram of the short side,
- * Householder tridiagonalisation, host implicit-QL eigenvalues), then set lifetimes.
- * Offline, once per model.  As many matrices are scored at once as the workspace holds
- * worker slots (at most 16, each with its own host thread and stream); the workspace must
- * hold at least one.  units may be NULL for SGD_RULE_DEPTH and SGD_RULE_RANDOM (then L
+ * Householder tridiagonalisation, the k largest eigenvalues by bisection), then set lifetimes.
+ * Offline, once per model.  As many matrices are scored at once as the workspace holds, in
+ * batches on hip_stream; the workspace must hold at least one.  units may be NULL for SGD_RULE_DEPTH and SGD_RULE_RANDOM (then L
  * alone sizes the schedule and nothing runs on the GPU).  Synchronises hip_stream before
  * returning.  Errors: SGD_E_ARG, SGD_E_DTYPE, SGD_E_BUDGET, SGD_E_NUMERIC, SGD_E_HIP. */
 int sgd_schedule_build(const sgd_unit* units, int32_t L, const sgd_sched_params* params, void* workspace,

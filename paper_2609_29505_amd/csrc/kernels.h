@@ -152,12 +152,32 @@ hipError_t launch_sumsq(const float* x, const float* y, float* copy, int B, int 
 hipError_t launch_sumsq_finish(const double* partial, int count, double* out, hipStream_t st);
 
 // ---------------------------------------------------------------- spectra (fp64)
-// G = X^T X (trans = 0, X rows x cols, G cols x cols) or X X^T (trans = 1, G rows x rows)
-hipError_t launch_gram(int dtype, const void* X, long rows, long cols, int trans, double* G, hipStream_t st);
-// Householder tridiagonalisation of the symmetric n x n matrix A (destroyed).  diag[n],
-// offd[n-1] receive the tridiagonal; work holds 5n + 8 doubles.
-hipError_t launch_tridiagonalize(double* A, int n, double* diag, double* offd, double* work,
-                                 hipStream_t st);
-hipError_t launch_diag_copy(const double* A, int n, double* out, hipStream_t st);
+// One scored matrix of a batch: X rows x cols; its Gram matrix is X^T X (trans = 0, n = cols) or
+// X X^T (trans = 1, n = rows); k eigenvalues are wanted; tile0 is the first of its tiles in the
+// Gram launch.
+struct SpectralJob {
+    const void* X;
+    int64_t rows, cols;
+    int32_t trans, dtype, n, k, tile0, pad;
+};
+// A batch in device memory: job b's Gram matrix and work vectors (5 nmax + 8 doubles) in slot b,
+// its results (diagonal, off-diagonal, Gram diagonal, eigenvalues: nmax doubles each) in outs.
+struct SpectralBatch {
+    const SpectralJob* jobs;
+    double* outs;
+    double* slots;
+    long slot;  // doubles
+    int nmax, count;
+    __host__ __device__ double* out(int b) const { return outs + 4 * (long)nmax * b; }
+    __host__ __device__ double* gram(int b) const { return slots + slot * b; }
+    __host__ __device__ double* work(int b) const { return slots + slot * (b + 1) - (5 * (long)nmax + 8); }
+};
+// row pitch of an n x n Gram matrix (even: 16-byte rows)
+__host__ __device__ inline int spectral_lda(int n) { return (n + 1) & ~1; }
+// largest short side whose three work vectors fit the LDS (160 KB); a batch lies on one side of it
+constexpr int kSpectralMax = 6600;
+// Gram matrices, tridiagonal forms and largest eigenvalues of a batch (host_jobs: the host's copy of
+// sb.jobs)
+hipError_t launch_spectra(const SpectralBatch& sb, const SpectralJob* host_jobs, hipStream_t st);
 
 }  // namespace sgd

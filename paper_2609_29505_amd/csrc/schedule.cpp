@@ -1,9 +1,8 @@
 // Schedule construction (Alg. 1, Sec. 4.1) behind sgd_schedule_build.
 //
-// Per scored matrix W (m x n, d = min(m, n)): the fp64 Gram matrix of the short side on
-// the GPU, its Householder tridiagonal form on the GPU, and the eigenvalues of that
-// tridiagonal matrix on the host (implicit symmetric QR with Wilkinson shift, Golub & Van
-// Loan Sec. 8.3).  The eigenvalues are the squared singular values sigma_i^2, from which
+// Per scored matrix W (m x n, d = min(m, n)), all on the GPU and for many matrices at once: the
+// fp64 Gram matrix of the short side, its Householder tridiagonal form and the k largest
+// eigenvalues of that form by bisection.  They are squared singular values sigma_i^2, from which
 //   E_k = sum_{i<=k} sigma_i^2, k = min(d, max(1, floor(d/10)))
 //   SCR_eta = log((E_k + eta F) / (tail + eta F)), F = ||W||_F^2 = trace of the Gram
 //   g(W) = sqrt(F) sqrt(rho), rho = (E_k + eta F) / (E_k + tail + 2 eta F)
@@ -12,14 +11,10 @@
 // app-conv-score, sum per unit (Eq. app-block-score) and normalise with eps = 1e-12
 // (Eq. app-score-normalization).  Lifetimes follow Eq. schedule.
 #include <algorithm>
-#include <atomic>
-#include <cfloat>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <limits>
-#include <mutex>
-#include <thread>
 #include <tuple>
 #include <vector>
 
@@ -27,63 +22,6 @@
 #include "kernels.h"
 
 namespace sgd {
-
-// ---------------------------------------------------------------------------- eigenvalues
-
-// One implicit symmetric QR step on the unreduced block [lo, hi] of the tridiagonal
-// matrix with diagonal a and subdiagonal b (b[i] = T[i+1][i]).  The shift is the
-// eigenvalue of the trailing 2 x 2 block closer to its last diagonal entry.  Rotations
-// R = [[c, s], [-s, c]] act on rows/columns (k, k+1); the first is chosen from the
-// shifted first column, the others chase the bulge T[k+1][k-1] down the band.
-static void qr_step(double* a, double* b, int lo, int hi) {
-    const double dd = 0.5 * (a[hi - 1] - a[hi]);
-    const double bn = b[hi - 1];
-    const double den = dd + std::copysign(std::hypot(dd, bn), dd == 0.0 ? 1.0 : dd);
-    const double mu = a[hi] - (den != 0.0 ? bn * bn / den : 0.0);
-    double x = a[lo] - mu, z = b[lo];
-    for (int k = lo; k < hi; ++k) {
-        const double r = std::hypot(x, z);
-        const double c = r == 0.0 ? 1.0 : x / r;
-        const double s = r == 0.0 ? 0.0 : z / r;
-        if (k > lo) b[k - 1] = r;
-        const double ak = a[k], ak1 = a[k + 1], bk = b[k];
-        a[k] = c * c * ak + 2.0 * c * s * bk + s * s * ak1;
-        a[k + 1] = s * s * ak - 2.0 * c * s * bk + c * c * ak1;
-        b[k] = c * s * (ak1 - ak) + (c * c - s * s) * bk;
-        if (k + 1 < hi) {
-            z = s * b[k + 1];
-            b[k + 1] = c * b[k + 1];
-            x = b[k];
-        }
-    }
-}
-
-// Eigenvalues of the symmetric tridiagonal (a, b); a is overwritten with them (unsorted).
-static bool tridiag_eigenvalues(std::vector<double>& a, std::vector<double>& b) {
-    const int n = (int)a.size();
-    if (n <= 1) return true;
-    double anorm = 0.0;
-    for (int i = 0; i < n; ++i) anorm = std::max(anorm, std::fabs(a[i]) + (i ? std::fabs(b[i - 1]) : 0.0) +
-                                                            (i + 1 < n ? std::fabs(b[i]) : 0.0));
-    const double eps = DBL_EPSILON;
-    const double floor_tol = 1e-3 * eps * anorm;
-    auto negligible = [&](int i) { return std::fabs(b[i]) <= eps * (std::fabs(a[i]) + std::fabs(a[i + 1])) + floor_tol; };
-    int hi = n - 1, iter = 0;
-    while (hi > 0) {
-        if (negligible(hi - 1)) {
-            b[hi - 1] = 0.0;
-            --hi;
-            iter = 0;
-            continue;
-        }
-        int lo = hi - 1;
-        while (lo > 0 && !negligible(lo - 1)) --lo;
-        if (lo > 0) b[lo - 1] = 0.0;
-        if (++iter > 200) return false;
-        qr_step(a.data(), b.data(), lo, hi);
-    }
-    return true;
-}
 
 struct MatStats {
     double e_top = 0, e_tail = 0, frob = 0, scr = 0, g = 0, sigma1_sq = 0;
@@ -94,17 +32,22 @@ static int rank_k(long m, long n) {
     return (int)std::min<long>(d, std::max<long>(1, d / 10));
 }
 
-static MatStats stats_from_eigs(std::vector<double>& lam, double frob, int k, double eta) {
-    for (double& v : lam) v = std::max(v, 0.0);
-    std::sort(lam.begin(), lam.end(), [](double x, double y) { return x > y; });
+// Statistics from the tridiagonal form's diagonal and its k largest eigenvalues (descending): the
+// tail energy is what they leave of its trace (nothing when they are all of the eigenvalues), summed
+// in extended precision, so that it carries the roundings of the eigenvalues and none of the sums.
+static MatStats stats_from_eigs(const double* diag, const double* lam, double frob, int k, int n, double eta) {
     MatStats s;
-    for (size_t i = 0; i < lam.size(); ++i) (i < (size_t)k ? s.e_top : s.e_tail) += lam[i];
+    long double top = 0.0L, trace = 0.0L;
+    for (int i = 0; i < k; ++i) top += std::max(lam[i], 0.0);
+    for (int i = 0; i < n; ++i) trace += diag[i];
+    s.e_top = (double)top;
+    s.e_tail = k < n ? std::max((double)(trace - top), 0.0) : 0.0;
     s.frob = frob;
     const double A = s.e_top + eta * frob, B = s.e_tail + eta * frob;
     s.scr = B > 0 ? std::log(A / B) : std::numeric_limits<double>::infinity();
     const double rho = (A + B) > 0 ? A / (A + B) : 0.0;
     s.g = std::sqrt(frob) * std::sqrt(rho);
-    s.sigma1_sq = lam.empty() ? 0.0 : lam[0];
+    s.sigma1_sq = std::max(lam[0], 0.0);
     return s;
 }
 
@@ -124,100 +67,80 @@ static int validate_matrix(const sgd_matrix* m) {
     return SGD_OK;
 }
 
-// Device doubles one worker needs for matrices whose short side is at most n: the Gram
-// matrix, the diagonal, the off-diagonal, the Householder work array and the Gram's
-// diagonal (for ||W||_F^2), each rounded up to 256 bytes.
-static size_t worker_bytes(long n) {
-    auto a = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    return a((size_t)n * n * 8) + 3 * a((size_t)n * 8) + a((size_t)(5 * n + 8) * 8);
+static size_t pad256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// Device bytes of one matrix of a batch whose short sides are at most n: its job record, its results
+// (four vectors) and its slot (the Gram matrix, then work vectors).
+static size_t slot_bytes(long n) {
+    return pad256((size_t)n * spectral_lda((int)n) * 8 + (size_t)(5 * n + 8) * 8);
 }
+static size_t matrix_bytes(long n) { return pad256(sizeof(SpectralJob)) + pad256((size_t)n * 32) + slot_bytes(n); }
 
-// Score every job with a pool of host workers, each driving its own stream and one slot of
-// the caller's workspace.
-static int run_stats(std::vector<MatJob>& jobs, double eta, char* ws, size_t ws_bytes, hipStream_t user_stream) {
+// Device bytes per worker: at least 4 MiB, so that a batch of small matrices, whose chain of steps
+// costs the same for one matrix as for all of them, takes several per worker.
+static size_t worker_bytes(long n) { return std::max(matrix_bytes(n), (size_t)4 << 20); }
+
+// Score every job on hip_stream, in batches of as many matrices as the workspace holds, largest first
+// (a batch's launches cover its largest matrix's steps).
+static int run_stats(std::vector<MatJob>& jobs, double eta, char* ws, size_t ws_bytes, hipStream_t st) {
     if (jobs.empty()) return SGD_OK;
-    int dev = 0;
-    SGD_HIP_TRY(hipGetDevice(&dev));
-    SGD_HIP_TRY(hipStreamSynchronize(user_stream));
-    long nmax = 0;
-    for (auto& j : jobs) nmax = std::max(nmax, std::min(j.m->rows, j.m->cols));
-    const size_t per = worker_bytes(nmax);
-    if (!ws || ws_bytes < per) return fail(SGD_E_ARG, "schedule workspace smaller than one worker slot");
+    std::vector<size_t> order(jobs.size());
+    for (size_t i = 0; i < order.size(); ++i) order[i] = i;
+    auto side = [&](size_t i) { return std::min(jobs[i].m->rows, jobs[i].m->cols); };
+    std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return side(x) > side(y); });
+    if (!ws || ws_bytes < matrix_bytes(side(order[0]))) return fail(SGD_E_ARG, "schedule workspace smaller than one worker slot");
     if ((uintptr_t)ws % 256) return fail(SGD_E_ARG, "schedule workspace must be 256-byte aligned");
-    unsigned hc = std::thread::hardware_concurrency();
-    int nw = (int)std::min<size_t>(jobs.size(), std::max(1u, std::min(hc ? hc : 1u, 16u)));
-    nw = (int)std::min<size_t>(nw, ws_bytes / per);
-
-    std::atomic<size_t> next{0};
-    std::mutex emu;
-    int first_err = SGD_OK;
-    std::string err_msg;
-    auto record = [&](int code, const std::string& msg) {
-        std::lock_guard<std::mutex> lk(emu);
-        if (first_err == SGD_OK) { first_err = code; err_msg = msg; }
-    };
-    auto worker = [&](int slot) {
-        if (hipSetDevice(dev) != hipSuccess) { record(SGD_E_HIP, "hipSetDevice failed in a worker"); return; }
-        hipStream_t st = nullptr;
-        auto a = [](size_t b) { return (b + 255) & ~(size_t)255; };
-        char* base = ws + (size_t)slot * per;
-        double* G = (double*)base;
-        double* dg = (double*)(base + a((size_t)nmax * nmax * 8));
-        double* od = (double*)((char*)dg + a((size_t)nmax * 8));
-        double* trace = (double*)((char*)od + a((size_t)nmax * 8));
-        double* work = (double*)((char*)trace + a((size_t)nmax * 8));
-        hipError_t e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking);
-        if (e != hipSuccess) {
-            record(SGD_E_HIP, std::string("worker stream: ") + hipGetErrorString(e));
-            return;
+    constexpr size_t kBatchMax = 512;
+    for (size_t done = 0; done < order.size();) {
+        const long nmax = side(order[done]);
+        size_t count = std::min({order.size() - done, ws_bytes / matrix_bytes(nmax), kBatchMax});
+        if (nmax > kSpectralMax)  // batches lie on one side of the fused reduction's limit
+            while (count > 1 && side(order[done + count - 1]) <= kSpectralMax) --count;
+        std::vector<SpectralJob> hj(count);
+        int tiles = 0;
+        for (size_t b = 0; b < count; ++b) {
+            const sgd_matrix* m = jobs[order[done + b]].m;
+            SpectralJob& j = hj[b];
+            j.X = m->ptr;
+            j.rows = m->rows;
+            j.cols = m->cols;
+            j.trans = m->cols > m->rows ? 1 : 0;  // Gram of the short side
+            j.dtype = m->dtype;
+            j.n = (int)std::min(m->rows, m->cols);
+            j.k = rank_k(m->rows, m->cols);
+            j.tile0 = tiles;
+            j.pad = 0;
+            const int nt = (j.n + 63) / 64;
+            tiles += nt * (nt + 1) / 2;
         }
-        std::vector<double> ha, hb, htr;
-        for (;;) {
-            const size_t i = next.fetch_add(1);
-            if (i >= jobs.size()) break;
-            {
-                std::lock_guard<std::mutex> lk(emu);
-                if (first_err != SGD_OK) break;
-            }
-            const sgd_matrix* m = jobs[i].m;
-            const int trans = m->cols > m->rows ? 1 : 0;  // Gram of the short side
-            const int n = (int)std::min(m->rows, m->cols);
-            e = launch_gram(m->dtype, m->ptr, m->rows, m->cols, trans, G, st);
-            if (e == hipSuccess) e = launch_diag_copy(G, n, trace, st);
-            if (e == hipSuccess) e = launch_tridiagonalize(G, n, dg, od, work, st);
-            ha.assign(n, 0.0);
-            hb.assign(n > 1 ? n - 1 : 0, 0.0);
-            htr.assign(n, 0.0);
-            if (e == hipSuccess) e = hipMemcpyAsync(ha.data(), dg, n * sizeof(double), hipMemcpyDeviceToHost, st);
-            if (e == hipSuccess && n > 1)
-                e = hipMemcpyAsync(hb.data(), od, (n - 1) * sizeof(double), hipMemcpyDeviceToHost, st);
-            if (e == hipSuccess) e = hipMemcpyAsync(htr.data(), trace, n * sizeof(double), hipMemcpyDeviceToHost, st);
-            if (e == hipSuccess) e = hipStreamSynchronize(st);
-            if (e != hipSuccess) {
-                record(SGD_E_HIP, std::string("spectral kernels: ") + hipGetErrorString(e));
-                break;
-            }
+        SpectralBatch sb;
+        sb.jobs = (const SpectralJob*)ws;
+        sb.outs = (double*)(ws + pad256(count * sizeof(SpectralJob)));
+        sb.slots = (double*)((char*)sb.outs + pad256(count * (size_t)nmax * 32));
+        sb.slot = (long)(slot_bytes(nmax) / 8);
+        sb.nmax = (int)nmax;
+        sb.count = (int)count;
+        std::vector<double> ho(count * (size_t)nmax * 4);
+        hipError_t e = hipMemcpyAsync(ws, hj.data(), count * sizeof(SpectralJob), hipMemcpyHostToDevice, st);
+        if (e == hipSuccess) e = launch_spectra(sb, hj.data(), st);
+        if (e == hipSuccess) e = hipMemcpyAsync(ho.data(), sb.outs, ho.size() * 8, hipMemcpyDeviceToHost, st);
+        // the host vectors live until here on every path
+        const hipError_t es = hipStreamSynchronize(st);
+        if (e == hipSuccess) e = es;
+        if (e != hipSuccess) return fail(SGD_E_HIP, std::string("spectral kernels: ") + hipGetErrorString(e));
+        for (size_t b = 0; b < count; ++b) {
+            const double* o = ho.data() + b * (size_t)nmax * 4;
+            const int n = hj[b].n, k = hj[b].k;
             double frob = 0.0;
-            for (double v : htr) frob += v;
+            for (int i = 0; i < n; ++i) frob += o[2 * nmax + i];
             bool finite = std::isfinite(frob);
-            for (double v : ha) finite = finite && std::isfinite(v);
-            for (double v : hb) finite = finite && std::isfinite(v);
-            if (!finite) {
-                record(SGD_E_NUMERIC, "non-finite weights in a scored matrix");
-                break;
-            }
-            if (!tridiag_eigenvalues(ha, hb)) {
-                record(SGD_E_NUMERIC, "tridiagonal eigenvalue iteration did not converge");
-                break;
-            }
-            jobs[i].out = stats_from_eigs(ha, frob, rank_k(m->rows, m->cols), eta);
+            for (int i = 0; i < n; ++i) finite = finite && std::isfinite(o[i]) && (i + 1 >= n || std::isfinite(o[nmax + i]));
+            for (int i = 0; i < k; ++i) finite = finite && std::isfinite(o[3 * nmax + i]);
+            if (!finite) return fail(SGD_E_NUMERIC, "non-finite weights in a scored matrix");
+            jobs[order[done + b]].out = stats_from_eigs(o, o + 3 * nmax, frob, k, n, eta);
         }
-        (void)hipStreamDestroy(st);
-    };
-    std::vector<std::thread> th;
-    for (int w = 0; w < nw; ++w) th.emplace_back(worker, w);
-    for (auto& t : th) t.join();
-    if (first_err != SGD_OK) return fail(first_err, err_msg);
+        done += count;
+    }
     return SGD_OK;
 }
 

@@ -67,6 +67,49 @@ def test_matrix_stats(P, shape, dtype):
     assert got[5] == pytest.approx(ref.sigma1_sq, rel=1e-11)
 
 
+def test_schedule_build_mixed_sizes(P):
+    """One batch of matrices of very different sizes: short sides 1, 2 and 3 (no or one reduction
+    step), odd and even ones around a row pass of the reduction (17, 18, 33), both orientations and
+    both storage types; each matrix's statistics as from a batch of its own and as the oracle's."""
+    from oracle.numerics import decode
+    rng = np.random.default_rng(41)
+    shapes = [(1, 9), (2, 2), (7, 2), (3, 3), (3, 40), (17, 17), (18, 50), (90, 33), (130, 129)]
+    mats = [synth.store(synth.planted_matrix(rng, *sh, np.float64)[0], "bf16" if i % 2 else "f32")
+            for i, sh in enumerate(shapes)]
+    units = [[("conv", _dev(m)) for m in mats[:4]], [("conv", _dev(m)) for m in mats[4:]]]
+    got = P.schedule_build(units, [64, 64], 10, budget_pct=50).mat_stats
+    for i, m in enumerate(mats):
+        ref = osp.matrix_stats(decode(m, "bf16" if i % 2 else "f32"), eta=1e-6)
+        F = ref.frob_sq
+        assert np.array_equal(got[i], P.matrix_stats(_dev(m), eta=1e-6)), shapes[i]
+        assert abs(got[i, 0] - ref.energy_top) <= 1e-13 * F and abs(got[i, 1] - ref.energy_tail) <= 1e-13 * F
+        assert got[i, 2] == pytest.approx(F, rel=1e-13) and got[i, 4] == pytest.approx(ref.g, rel=1e-13)
+        assert got[i, 5] == pytest.approx(ref.sigma1_sq, rel=1e-13)
+
+
+@pytest.mark.parametrize("n", [6592, 6720])
+def test_matrix_stats_large(P, n):
+    """The last short sides whose reduction keeps its vectors in LDS and the first that does not:
+    W = diag(s) Q with Q block diagonal, 64 x 64 Hadamard blocks over 8 (orthogonal, exact in bf16),
+    so the singular values are exactly s (powers of two)."""
+    import torch
+    h = torch.ones(1, 1)
+    while h.shape[0] < 64:
+        h = torch.cat([torch.cat([h, h], 1), torch.cat([h, -h], 1)])
+    rng = np.random.default_rng(n)
+    s = 2.0 ** rng.integers(-6, 3, n)
+    w = torch.zeros((n, n), dtype=torch.bfloat16, device="cuda")
+    sd = torch.from_numpy(s).cuda()
+    for i in range(0, n, 64):
+        w[i:i + 64, i:i + 64] = (sd[i:i + 64, None] * (h.double().cuda() / 8)).bfloat16()
+    got = P.matrix_stats(w, eta=1e-6)
+    lam = np.sort(s * s)[::-1]
+    k, F = n // 10, lam.sum()
+    assert got[2] == pytest.approx(F, rel=1e-14)
+    assert abs(got[0] - lam[:k].sum()) <= 1e-13 * F and abs(got[1] - lam[k:].sum()) <= 1e-13 * F
+    assert got[5] == pytest.approx(lam[0], rel=1e-13)
+
+
 @pytest.mark.parametrize("name", MINIS + ["tiny"])
 def test_schedule_bit_exact(P, name):
     cfg, w, x = workload(name)
