@@ -102,10 +102,10 @@ __global__ __launch_bounds__(256) void gram_kernel(SpectralBatch sb) {
 // of its own, took 4-5 us each and were bound by the launches (24 matrices of 256 x 256 to
 // 1024 x 256: 21.3 ms; 4 of 1152 x 1152 and 2 of 4608 x 1152: 62.9 ms, both with the host's QR).
 
-__device__ double block_sum_d(double v, double* red) {
+// sum over the workgroup through red (one double per wave, used once per call)
+__device__ __forceinline__ double block_sum_d(double v, double* red) {
     v = warp_sum(v);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    __syncthreads();
     if (lane == 0) red[w] = v;
     __syncthreads();
     double t = 0.0;
@@ -122,7 +122,7 @@ constexpr int kTriThreads = 256, kTriRows = 16;  // rows per workgroup pass: fou
 template <bool FIRST>
 __global__ __launch_bounds__(kTriThreads) void tri_step_kernel(SpectralBatch sb, int j) {
     extern __shared__ __attribute__((aligned(16))) double sh[];
-    __shared__ double red[kTriThreads / 64];
+    __shared__ double red[2 * (kTriThreads / 64)];
     const int b = blockIdx.y, n = sb.jobs[b].n, tid = threadIdx.x;
     if (n < 3) {
         if (FIRST && blockIdx.x == 0 && tid == 0) {  // already tridiagonal
@@ -145,49 +145,77 @@ __global__ __launch_bounds__(kTriThreads) void tri_step_kernel(SpectralBatch sb,
     const int c0 = (r0 + 1) & ~1, len = ((n + 1) & ~1) - c0, sp = r0 + 1 - c0;
     double *sv = sh, *sw = sh + len, *sx = sh + 2 * len;
     const double* arow = A + (long)r0 * lda + r0;  // row 0 of the block (== column 0)
-    double v0 = 1.0, w0 = 0.0, tau = 0.0;
     const int nx = j + 1;                          // index of the reflector formed here (FIRST: j = -1)
     double* const vn = work + (long)(nx & 1) * sb.nmax;
     double* const pn = work + (long)(2 + (nx & 1)) * sb.nmax;
     double* const taus = work + 4 * (long)sb.nmax;
-    for (int i = tid; i < len; i += kTriThreads) { sv[i] = 0.0; sw[i] = 0.0; sx[i] = 0.0; }
-    __syncthreads();
+    // rows 1 .. m - 1 of the block, four per wave at once (the LDS vectors are read once for four).
+    // The first PRE column chunks of the first pass are loaded here, before the vectors are formed:
+    // the step is a chain of memory round trips and block sums, and the rows depend on none of them.
+    const int lane = tid & 63, wave = tid >> 6;
+    constexpr int PRE = 2;
+    double2 pre[PRE][4];
+    {
+        const int i0 = 1 + blockIdx.x * kTriRows + wave * 4;
+#pragma unroll
+        for (int u = 0; u < PRE; ++u)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int c = lane * 2 + u * 128;
+                pre[u][r] = c < len ? *(const double2*)(A + (long)(r0 + min(i0 + r, m - 1)) * lda + c0 + c)
+                                    : make_double2(0.0, 0.0);
+            }
+    }
+    if (tid == 0) {
+        if (sp) { sv[0] = 0.0; sw[0] = 0.0; sx[0] = 0.0; }
+        if (n & 1) { sv[len - 1] = 0.0; sw[len - 1] = 0.0; sx[len - 1] = 0.0; }
+    }
+    // a thread handles the same entries in every pass over the vectors, so only the sums need barriers
+    double v0 = 0.0, w0 = 0.0, k = 0.0;
+    double alpha = arow[1];
     if (!FIRST) {
         const double* v = work + (long)(j & 1) * sb.nmax;
         const double* p = work + (long)(2 + (j & 1)) * sb.nmax;
-        tau = taus[j & 1];
+        const double tau = taus[j & 1], p0 = p[0], v1 = v[1], p1 = p[1];
         double s = 0.0;
-        for (int i = tid; i < m; i += kTriThreads) {
-            const double vi = v[i], pi = p[i];
+        v0 = 1.0;
+        for (int i = tid; i < m - 1; i += kTriThreads) {
+            const double vi = v[i + 1], pi = p[i + 1];
             s += pi * vi;
-            if (i > 0) { sv[i - 1 + sp] = vi; sw[i - 1 + sp] = pi; }
+            sv[i + sp] = vi;
+            sw[i + sp] = pi;
+            sx[i + sp] = arow[i + 1];
         }
-        const double k = 0.5 * tau * block_sum_d(s, red);
-        v0 = v[0];
-        w0 = p[0] - k * v0;
-        for (int i = tid; i < m - 1; i += kTriThreads) sw[i + sp] -= k * sv[i + sp];
-        __syncthreads();
+        k = 0.5 * tau * (block_sum_d(s, red) + p0);
+        w0 = p0 - k;
+        alpha = alpha - v1 * w0 - (p1 - k * v1);
         if (m == 2) {
             // last step: the trailing 2 x 2 block after its update is the end of T
             if (blockIdx.x == 0 && tid == 0) {
-                diag[j + 1] = arow[0] - 2.0 * v0 * w0;
-                offd[j + 1] = arow[1] - sv[sp] * w0 - sw[sp] * v0;
-                diag[j + 2] = A[(long)(j + 2) * lda + (j + 2)] - 2.0 * sv[sp] * sw[sp];
+                diag[j + 1] = arow[0] - 2.0 * w0;
+                offd[j + 1] = alpha;
+                diag[j + 2] = A[(long)(j + 2) * lda + (j + 2)] - 2.0 * v1 * (p1 - k * v1);
             }
             return;
         }
     }
-    // the updated column 0 below the diagonal, x[i] = A22[1+i][0] - v[1+i] w[0] - w[1+i] v[0], and its
+    // w, the updated column 0 below the diagonal, x[i] = A22[1+i][0] - v[1+i] w[0] - w[1+i] v[0], and its
     // reflector (x[0] is alpha)
     double s = 0.0;
     for (int i = tid; i < m - 1; i += kTriThreads) {
-        double x = arow[1 + i];
-        if (!FIRST) x = x - sv[i + sp] * w0 - sw[i + sp] * v0;
+        double x = FIRST ? arow[1 + i] : sx[i + sp];
+        if (FIRST) {
+            sv[i + sp] = 0.0;
+            sw[i + sp] = 0.0;
+        } else {
+            const double w = sw[i + sp] - k * sv[i + sp];
+            sw[i + sp] = w;
+            x = x - sv[i + sp] * w0 - w;
+        }
         sx[i + sp] = x;
         if (i > 0) s += x * x;
     }
-    const double sigma = block_sum_d(s, red);
-    const double alpha = sx[sp];
+    const double sigma = block_sum_d(s, red + kTriThreads / 64);
     double taun = 0.0, beta = alpha, scale = 0.0;
     if (sigma != 0.0) {
         const double mu = sqrt(alpha * alpha + sigma);
@@ -195,22 +223,20 @@ __global__ __launch_bounds__(kTriThreads) void tri_step_kernel(SpectralBatch sb,
         taun = (beta - alpha) / beta;
         scale = 1.0 / (alpha - beta);
     }
-    __syncthreads();  // alpha is read
     for (int i = tid; i < m - 1; i += kTriThreads) {
         const double y = i == 0 ? 1.0 : sx[i + sp] * scale;
         sx[i + sp] = y;
         if (blockIdx.x == 0) vn[i] = y;
     }
     if (blockIdx.x == 0 && tid == 0) {
-        diag[nx] = FIRST ? A[0] : arow[0] - 2.0 * v0 * w0;
+        diag[nx] = FIRST ? A[0] : arow[0] - 2.0 * w0;
         offd[nx] = beta;
         taus[nx & 1] = taun;
     }
     __syncthreads();
-    // rows 1 .. m - 1 of the block, four per wave at once (the LDS vectors are read once for four)
-    const int lane = tid & 63, wave = tid >> 6;
     for (int base = 1 + blockIdx.x * kTriRows; base < m; base += gridDim.x * kTriRows) {
         const int i0 = base + wave * 4;
+        const bool first = base == 1 + (int)blockIdx.x * kTriRows;
         double vi[4], wi[4], acc[4] = {};
         double* ar[4];
 #pragma unroll
@@ -220,12 +246,8 @@ __global__ __launch_bounds__(kTriThreads) void tri_step_kernel(SpectralBatch sb,
             wi[r] = sw[i - 1 + sp];
             ar[r] = A + (long)(r0 + i) * lda + c0;
         }
-#pragma unroll 2
-        for (int c = lane * 2; c < len; c += 128) {
+        auto chunk = [&](int c, double2 (&a)[4]) {
             const double2 w2 = *(const double2*)(sw + c), v2 = *(const double2*)(sv + c), x2 = *(const double2*)(sx + c);
-            double2 a[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) a[r] = *(const double2*)(ar[r] + c);
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 if (!FIRST) {
@@ -236,6 +258,28 @@ __global__ __launch_bounds__(kTriThreads) void tri_step_kernel(SpectralBatch sb,
                 acc[r] += a[r].x * x2.x;
                 acc[r] += a[r].y * x2.y;
             }
+        };
+        auto load = [&](int c, double2 (&a)[4]) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) a[r] = *(const double2*)(ar[r] + c);
+        };
+        int c = lane * 2;
+        if (first) {
+#pragma unroll
+            for (int u = 0; u < PRE; ++u, c += 128)
+                if (c < len) chunk(c, pre[u]);
+        }
+        for (; c + 128 < len; c += 256) {
+            double2 a[2][4];
+            load(c, a[0]);
+            load(c + 128, a[1]);
+            chunk(c, a[0]);
+            chunk(c + 128, a[1]);
+        }
+        if (c < len) {
+            double2 a[4];
+            load(c, a);
+            chunk(c, a);
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -256,6 +300,7 @@ constexpr int kHouseThreads = 1024;
 __device__ double house(const double* x, int len, double* vout, double* beta_out, double* red) {
     double s = 0.0;
     for (int i = 1 + threadIdx.x; i < len; i += blockDim.x) s += x[i] * x[i];
+    __syncthreads();  // red is free
     const double sigma = block_sum_d(s, red);
     const double alpha = x[0];
     double tau, beta, scale;
