@@ -1,18 +1,10 @@
 // Branch GEMMs of the active units in bf16: C = A . B^T on the CDNA4 matrix cores
 // (v_mfma_f32_32x32x16_bf16, fp32 accumulation) with the unit's epilogue fused.
 //
-// Two kernels share the epilogue: gemm_pp_kernel, 256-row block tiles whose operands go straight
-// into LDS and whose wave groups alternate between loading and MFMAs, and gemm_bf16_kernel, 128-row
-// tiles for products too small to fill the chip with 256-row ones.
-//
-// 128-row kernel.  Eight waves, two per SIMD, 64-deep k tiles (128-byte operand rows, one L2 line
-// each).  Global -> LDS goes through registers: buffer_load_dwordx4 into VGPRs (the buffer
-// descriptor's range check returns zeros for rows past the matrix, so ragged M and N need no
-// clamping), then ds_write_b128 to an XOR-swizzled position so that the 16-byte fragment reads of
-// 16 consecutive rows cover the 64 banks once.  The registers are a third pipeline stage next to
-// the two LDS stages, and the register -> LDS writes and the next loads are spread one part at a
-// time between the MFMAs, so neither the texture unit nor the LDS sees a burst while the MFMA
-// pipes run.
+// Two kernels share the epilogue, both with operands loaded straight into LDS and two wave groups
+// that alternate between reading fragments and MFMAs: gemm_pp_kernel, whose groups share large block
+// tiles, and gemm_pk_kernel, small tiles for products that cannot fill the chip with large ones, whose
+// groups split K.
 //
 // Epilogue.  Straight from the accumulators: the loader orders the weight rows so that what a
 // store or a pair of columns needs sits in one lane (see the epilogue).
@@ -50,29 +42,6 @@ template <int N, class Fn>
 __device__ __forceinline__ void static_for(Fn&& f) {
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
-
-template <int BM_, int BN_, int WGM_, int WGN_, int BK_, int STAGES_, int OCC_ = 2, int RD_ = 1>
-struct TileCfg {
-    static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, BK = BK_, STAGES = STAGES_;
-    static constexpr int OCC = OCC_;                     // waves per SIMD the registers allow
-    static constexpr int RD = RD_;                       // k tiles in flight in registers
-    static constexpr int NW = WGM * WGN;
-    static constexpr int NT = NW * 64;
-    static constexpr int WM = BM / WGM, WN = BN / WGN;   // wave tile
-    static constexpr int TM = WM / 32, TN = WN / 32;     // 32 x 32 MFMA blocks per wave
-    static constexpr int ROWB = BK * 2;                  // bytes per LDS tile row
-    static constexpr int CH = BK / 8;                    // 16-byte chunks per row
-    static constexpr int RPB = 256 / ROWB;               // rows per 256-byte bank line
-    static constexpr int A_BYTES = BM * ROWB, B_BYTES = BN * ROWB;
-    static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-    static constexpr int KSTEPS = BK / 16;
-    // tile row of the first row of wave row wm's MFMA row block i
-    __device__ static __forceinline__ int block_row(int wm, int i) { return wm * WM + i * 32; }
-    static constexpr int LDS_BYTES = STAGE_BYTES * STAGES;
-    static_assert(TM >= 1 && TN >= 1 && WM % 32 == 0 && WN % 32 == 0, "wave tile");
-    static_assert(BK == 64, "128-byte operand rows: one L2 line per row and chunk-swizzled LDS rows");
-    static_assert(LDS_BYTES <= 160 * 1024, "LDS");
-};
 
 // --------------------------------------------------------------------------- epilogue
 //
@@ -174,6 +143,9 @@ __device__ __forceinline__ uint32_t pack_bf16(float x, float y) {
     s[1] = f2bf(y);
     return __builtin_bit_cast(uint32_t, s);
 }
+
+// two bf16 values at p (4-byte aligned)
+__device__ __forceinline__ void put2(bf16* p, const float* v) { *(uint32_t*)p = pack_bf16(v[0], v[1]); }
 
 template <class C>
 __device__ __forceinline__ void epilogue(f32x16 (&acc)[C::TM][C::TN], const GemmArgs& g, const EpiParams& ep, int m0,
@@ -333,12 +305,21 @@ __device__ __forceinline__ void epilogue(f32x16 (&acc)[C::TM][C::TN], const Gemm
                             if (tok0 % 4 == 0 && tok0 + 3 < ep.ntok && row0 + 3 < g.M) {
                                 store_bf16x4(vt + (((long)bs0 * ep.H + vh) * ep.dh + vj) * ep.np + tok0, o);
                             } else {
+                                // two tokens at a time where they stay together (an even sample length)
 #pragma unroll
-                                for (int u = 0; u < 4; ++u) {
+                                for (int u = 0; u < 4; u += 2) {
                                     const int row = row0 + u;
                                     if (row >= g.M) break;
                                     const int bs = sample_of(row), tok = row - bs * ep.ntok;
-                                    vt[(((long)bs * ep.H + vh) * ep.dh + vj) * ep.np + tok] = f2bf(o[u]);
+                                    bf16* const dst = vt + (((long)bs * ep.H + vh) * ep.dh + vj) * ep.np + tok;
+                                    if (tok % 2 == 0 && tok + 1 < ep.ntok && row + 1 < g.M) {
+                                        put2(dst, o + u);
+                                        continue;
+                                    }
+                                    dst[0] = f2bf(o[u]);
+                                    if (row + 1 >= g.M) break;
+                                    const int bs1 = sample_of(row + 1), tok1 = row + 1 - bs1 * ep.ntok;
+                                    vt[(((long)bs1 * ep.H + vh) * ep.dh + vj) * ep.np + tok1] = f2bf(o[u + 1]);
                                 }
                             }
                         }
@@ -514,212 +495,17 @@ __device__ __forceinline__ void epilogue(f32x16 (&acc)[C::TM][C::TN], const Gemm
     }
 }
 
-// --------------------------------------------------------------------------- kernel
+// --------------------------------------------------------------------------- large tiles
 //
-// Pipeline with two LDS stages and a ring of RD register slots: in the period between the
-// barriers before the last k-steps of tiles kt - 1 and kt, the MFMAs consume tile kt (one
-// stage), tile kt + 1 moves from its register slot into the other stage, and tile
-// kt + 1 + RD is loaded into the freed slot, so a load has RD periods to arrive.  Small
-// tiles have short periods and need RD > 1 to cover the latency of weights streamed from
-// HBM.  The register -> LDS writes and the loads are interleaved one part at a time with
-// the period's MFMAs (part p after MFMA slot p * SLOTS / PARTS), so neither the texture
-// unit nor the LDS sees a burst and both SIMD waves keep issuing MFMAs.
-
-template <class C, bool CONV>
-__global__ __launch_bounds__(C::NT, C::OCC) void gemm_bf16_kernel(GemmArgs g, EpiParams ep) {
-    static_assert(C::STAGES == 2, "two LDS stages plus the register stage");
-    __shared__ __attribute__((aligned(1024))) char lds[C::LDS_BYTES];
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nt_m = (g.M - g.m_begin + C::BM - 1) / C::BM;
-    const int nt_n = (g.N + C::BN - 1) / C::BN;
-    int tm, tn;
-    tile_at(tile_position((int)blockIdx.x, nt_m * nt_n), nt_m, nt_n, g.band, tm, tn);
-    const int m0 = g.m_begin + tm * C::BM;
-    const int F = g.N / 2;
-
-    const __amdgpu_buffer_rsrc_t ra0 = buf_rsrc(g.A0, (unsigned)((long)g.M * g.lda0 * 2));
-    const __amdgpu_buffer_rsrc_t ra1 = g.A1 ? buf_rsrc(g.A1, (unsigned)((long)g.M * g.lda1 * 2)) : ra0;
-    const __amdgpu_buffer_rsrc_t rb = buf_rsrc(g.B, (unsigned)((long)g.N * g.ldb * 2));
-
-    // thread -> (row, chunk) of a stage: chunk tid % CH of rows tid / CH + p * RPP; parts
-    // 0 .. AP-1 are A rows, AP .. AP+BP-1 are B rows.  LDS holds the A stages, then the B
-    // stages.  The swizzle key (r / RPB) % CH of a row does not change when r moves by a
-    // multiple of CH * RPB rows, so a thread's write positions (rows vr + p RPP) and fragment
-    // positions (rows w0 + i 32 + lrow) are one base register plus compile-time offsets.
-    constexpr int RPP = C::NT / C::CH;
-    constexpr int AP = C::BM / RPP, BP = C::BN / RPP, PARTS = AP + BP;
-    static_assert(C::BM % RPP == 0 && C::BN % RPP == 0, "pass split");
-    static_assert(RPP % (C::CH * C::RPB) == 0 && 32 % (C::CH * C::RPB) == 0, "row-invariant swizzle key");
-    constexpr int B_LDS = C::STAGES * C::A_BYTES;  // first B stage
-    const int vc = tid % C::CH, vr = tid / C::CH;
-    unsigned goff[PARTS];  // A rows of both A sources share the row pitch
-#pragma unroll
-    for (int p = 0; p < AP; ++p) goff[p] = (unsigned)((long)(m0 + vr + p * RPP) * g.lda0 * 2 + vc * 16);
-    // implicit-GEMM convolution: grid position (y, x) of each A row (y << 16 | x)
-    int gpos[CONV ? AP : 1];
-    if constexpr (CONV) {
-        const int side = g.conv_side, area = side * side;
-#pragma unroll
-        for (int p = 0; p < AP; ++p) {
-            const int pix = (m0 + vr + p * RPP) % area;
-            const int y = pix / side;
-            gpos[p] = (y << 16) | (pix - y * side);
-        }
-    }
-#pragma unroll
-    for (int p = 0; p < BP; ++p) {
-        goff[AP + p] = (unsigned)(weight_row<C>(ep, F, tn, vr + p * RPP) * g.ldb * 2 + vc * 16);
-    }
-    char* const lw = lds + vr * C::ROWB + ((vc ^ ((vr / C::RPB) % C::CH)) << 4);
-    // register slot s holds the k tiles t with t % RD == s (s is a compile-time constant at
-    // every call).  Tiles at or past K load zeros: their offset lies past every operand
-    // buffer (sizes stay below OOB), so the descriptor's range check fails.  The main loop
-    // therefore runs whole trips without a branch, the padding tiles add zero products, and
-    // the compiler sees the same outstanding loads on every trip.
-    const int KT = g.K / C::BK;
-    constexpr unsigned OOB = 0xFFFFFF00u;
-    u32x4 vreg[C::RD][PARTS];
-    auto gload = [&](int kt, int s, int p) {
-        const bool in = kt < KT;
-        const int k0 = kt * C::BK;
-        if (CONV && p < AP) {
-            // the k tile lies inside one tap (conv_c % 64 == 0): shift the row by the tap's
-            // grid offset, or load zeros (an out-of-range offset) where it leaves the grid
-            const int tap = k0 / g.conv_c;
-            const int c0 = k0 - tap * g.conv_c;
-            const int ky = tap / 3, dy = ky - 1, dx = tap - ky * 3 - 1;
-            const int yy = (gpos[p] >> 16) + dy, xx = (gpos[p] & 0xFFFF) + dx;
-            const bool ok = in && (unsigned)yy < (unsigned)g.conv_side && (unsigned)xx < (unsigned)g.conv_side;
-            const int shift = (dy * g.conv_side + dx) * g.lda0 * 2;
-            vreg[s][p] = __builtin_amdgcn_raw_buffer_load_b128(ra0, ok ? (unsigned)((int)goff[p] + shift) : OOB,
-                                                               ok ? c0 * 2 : 0, 0);
-        } else if (p < AP) {
-            const bool second = g.A1 && k0 >= g.K0;
-            vreg[s][p] = __builtin_amdgcn_raw_buffer_load_b128(second ? ra1 : ra0, in ? goff[p] : OOB,
-                                                               in ? (second ? (k0 - g.K0) * 2 : k0 * 2) : 0, 0);
-        } else {
-            vreg[s][p] = __builtin_amdgcn_raw_buffer_load_b128(rb, in ? goff[p] : OOB, in ? k0 * 2 : 0, 0);
-        }
-    };
-    // stage and part are compile-time constants at every call
-    auto lwrite = [&](int stage, int s, int p) {
-        if (p < AP) *(u32x4*)(lw + stage * C::A_BYTES + p * RPP * C::ROWB) = vreg[s][p];
-        else *(u32x4*)(lw + B_LDS + stage * C::B_BYTES + (p - AP) * RPP * C::ROWB) = vreg[s][p];
-    };
-
-    const int wm = wave / C::WGN, wn = wave % C::WGN;
-    const int wm0 = wm * C::WM, wn0 = wn * C::WN;
-    const int lrow = lane & 31, lhalf = lane >> 5;
-
-    f32x16 acc[C::TM][C::TN];
-#pragma unroll
-    for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-        for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-    bf16x8 af[2][C::TM], bfr[2][C::TN];
-    const int fkey = (lrow / C::RPB) % C::CH;
-    const char* const fa = lds + (wm0 + lrow) * C::ROWB;
-    const char* const fb = lds + B_LDS + (wn0 + lrow) * C::ROWB;
-    auto frags = [&](int stage, int q, int buf) {
-        const int sw = ((q * 2 + lhalf) ^ fkey) << 4;
-#pragma unroll
-        for (int i = 0; i < C::TM; ++i)
-            af[buf][i] = *(const bf16x8*)(fa + sw + stage * C::A_BYTES + i * 32 * C::ROWB);
-#pragma unroll
-        for (int j = 0; j < C::TN; ++j)
-            bfr[buf][j] = *(const bf16x8*)(fb + sw + stage * C::B_BYTES + j * 32 * C::ROWB);
-    };
-    constexpr int MPK = C::TM * C::TN, SLOTS = C::KSTEPS * MPK;
-    static_assert(PARTS <= SLOTS, "part spreading");
-    // MFMAs of one k-step; `part` is the k-step's position in its period.  The period moves
-    // a tile from register slot S into stage ws and loads tile lt into slot S.  The compiler
-    // inserts the vmcnt waits from the register dependences: vmcnt(RD * PARTS - 1) before
-    // every write.
-    auto mfmas = [&](int buf, int part, int ws, int lt, auto rs) {
-        constexpr int S = decltype(rs)::value;
-#pragma unroll
-        for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-            for (int j = 0; j < C::TN; ++j) {
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[buf][i], bfr[buf][j], acc[i][j], 0, 0, 0);
-                const int slot = part * MPK + i * C::TN + j;
-                const int p = (slot * PARTS + SLOTS - 1) / SLOTS;
-                if (p < PARTS && (p * SLOTS) / PARTS == slot) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    lwrite(ws, S, p);
-                    gload(lt, S, p);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-    };
-
-    // prologue: tile 0 into stage 0, tiles 1 .. RD into the register slots (tile RD shares
-    // slot 0 with tile 0).  The first period has no "last k-step of tile -1", so the parts of
-    // its first slot group (write tile 1, load tile 1 + RD) are done here.
-#pragma unroll
-    for (int p = 0; p < PARTS; ++p) gload(0, 0, p);
-    static_for<C::RD - 1>([&](auto jc) {
-        constexpr int TT = decltype(jc)::value + 1;
-#pragma unroll
-        for (int p = 0; p < PARTS; ++p) gload(TT, TT, p);
-    });
-#pragma unroll
-    for (int p = 0; p < PARTS; ++p) {
-        lwrite(0, 0, p);
-        gload(C::RD, 0, p);
-    }
-#pragma unroll
-    for (int p = 0; p < PARTS; ++p) {
-        if ((p * SLOTS) / PARTS < MPK) {
-            lwrite(1, 1 % C::RD, p);
-            gload(1 + C::RD, 1 % C::RD, p);
-        }
-    }
-    __syncthreads();
-    frags(0, 0, 0);
-    // one k tile; jc is its position in the trip (tile kt sits in register slot J = kt % RD
-    // and LDS stage st = kt % 2).  The period of tile kt (from the barrier before tile kt-1's
-    // last k-step) moves tile kt + 1 into stage st ^ 1 and loads tile kt + 1 + RD, and the
-    // period of tile kt + 1 starts with the last k-step
-    auto iter = [&](int kt, auto jc) {
-        constexpr int J = decltype(jc)::value % C::RD, st = decltype(jc)::value % 2;
-#pragma unroll
-        for (int q = 0; q < C::KSTEPS; ++q) {
-            const int cur = q & 1, nxt = cur ^ 1;
-            __builtin_amdgcn_sched_barrier(0);
-            if (q + 1 < C::KSTEPS) {
-                frags(st, q + 1, nxt);
-            } else {
-                __syncthreads();  // tile kt + 1 is in stage st ^ 1; stage st is free
-                frags(st ^ 1, 0, nxt);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            if (q + 1 < C::KSTEPS) mfmas(cur, q + 1, st ^ 1, kt + 1 + C::RD, IntC<(J + 1) % C::RD>{});
-            else mfmas(cur, 0, st, kt + 2 + C::RD, IntC<(J + 2) % C::RD>{});
-        }
-    };
-    static_assert(C::KSTEPS % 2 == 0, "fragment ring");
-    constexpr int TRIP = C::RD % 2 ? 2 * C::RD : C::RD;  // whole register rings and LDS stage pairs
-    for (int kt = 0; kt < KT; kt += TRIP) static_for<TRIP>([&](auto jc) { iter(kt + decltype(jc)::value, jc); });
-    epilogue<C>(acc, g, ep, m0, tn, wm, wn, 0);
-}
-
-// --------------------------------------------------------------------------- 256-row kernel
-//
-// 256 x BN block tiles, eight waves, 64-deep k tiles.  Operands go from global memory straight
+// 256 x BN and 128 x 256 block tiles, eight waves, 64-deep k tiles.  Operands go from global memory straight
 // into LDS (buffer_load ... lds, 16 bytes a lane: no staging registers, no ds_write issue); the
 // XOR swizzle of a row's chunks is applied to the lanes' global addresses, since a wave's LDS
 // destination is contiguous.  The waves form two groups (one wave of each per SIMD) that run the
 // same phases half a phase apart: while one group issues its MFMAs the other reads its fragments
 // and issues loads, so each SIMD always has one wave in the matrix cores.
 //
-// A k tile is two phases.  Phase 0 reads the fragments of A rows [0, 128) and of all of B, phase
-// 1 those of A rows [128, 256); a phase's LDS regions are free once both groups have read them, so
+// A k tile is two phases.  Phase 0 reads the fragments of A's first half of rows and of all of B,
+// phase 1 those of the second half; a phase's LDS regions are free once both groups have read them, so
 // they are refilled two k tiles ahead, one to two tiles before they are read (128 KB of LDS at
 // BN = 256 keep ~1.5 tiles in flight).  Each wave waits for its own loads by count (vmcnt), one
 // phase before the data is read, and the barrier in between makes that true of every wave.
@@ -734,17 +520,18 @@ __global__ __launch_bounds__(C::NT, C::OCC) void gemm_bf16_kernel(GemmArgs g, Ep
 // in a whole step the clock falls with the power drawn and half of that remains.  Two workgroups of 128 x 256 per CU instead (epilogues overlapped)
 // ran at 1030 on 8192^3: they move 1.5x the operand bytes.
 
-template <int BN_, int WGM_, int WGN_>
+template <int BM_, int BN_, int WGM_, int WGN_>
 struct PPCfg {
-    static constexpr int BM = 256, BN = BN_, WGM = WGM_, WGN = WGN_, NT = 512, NW = 8;
-    static constexpr int RW = 128 / WGM;                 // a wave's rows of each 128-row half
+    static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, NT = 512, NW = 8;
+    static constexpr int BH = BM / 2, HP = BH / 64;      // rows and load parts (64 rows) of each half
+    static constexpr int RW = BH / WGM;                  // a wave's rows of each half
     static constexpr int CB = RW / 32, TM = 2 * CB;      // MFMA row blocks per half, per wave
     static constexpr int WN = BN / WGN, TN = WN / 32;
     static constexpr int BP = BN / 64, BL = BP / 2;      // B parts (64 rows) per tile; those loaded in phase 1
-    static constexpr int A_HALF = 16384, A_STAGE = 32768, B_STAGE = BN * 128, B_LDS = 2 * A_STAGE;
+    static constexpr int A_HALF = BH * 128, A_STAGE = BM * 128, B_STAGE = BN * 128, B_LDS = 2 * A_STAGE;
     static constexpr int LDS_BYTES = B_LDS + 2 * B_STAGE;
-    __device__ static __forceinline__ int block_row(int wm, int i) { return (i / CB) * 128 + wm * RW + (i % CB) * 32; }
-    static_assert(WGM * WGN == NW && RW % 32 == 0 && WN % 32 == 0 && BN % 64 == 0, "wave tile");
+    __device__ static __forceinline__ int block_row(int wm, int i) { return (i / CB) * BH + wm * RW + (i % CB) * 32; }
+    static_assert(WGM * WGN == NW && RW % 32 == 0 && WN % 32 == 0 && BN % 64 == 0 && BH % 64 == 0, "wave tile");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
 };
 
@@ -793,13 +580,13 @@ __global__ __launch_bounds__(C::NT, 2) void gemm_pp_kernel(GemmArgs g, EpiParams
     constexpr unsigned OOB = 0xFFFFFF00u;
 
     // Load part p of an operand tile: rows 64 p + 8 wave + lane / 8, the 16-byte chunk of the row
-    // that belongs at LDS position lane % 8.  A parts 0, 1 are the first half's rows.
+    // that belongs at LDS position lane % 8.  The first HP A parts are the first half's rows.
     const int prow = wave * 8 + (lane >> 3);
     const int pch = ((lane & 7) ^ ((prow >> 1) & 7)) * 16;  // swizzle key of the row: 64-row parts keep it
-    unsigned aoff[4], boff[C::BP];  // both A sources share the row pitch
-    int gpos[CONV ? 4 : 1];         // convolution: grid position (y << 16 | x) of the A row
+    unsigned aoff[2 * C::HP], boff[C::BP];  // both A sources share the row pitch
+    int gpos[CONV ? 2 * C::HP : 1];         // convolution: grid position (y << 16 | x) of the A row
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
+    for (int p = 0; p < 2 * C::HP; ++p) {
         const int row = m0 + p * 64 + prow;
         aoff[p] = (unsigned)((long)row * g.lda0 * 2 + pch);
         if constexpr (CONV) {
@@ -826,17 +613,17 @@ __global__ __launch_bounds__(C::NT, 2) void gemm_pp_kernel(GemmArgs g, EpiParams
             const int shift = (dy * g.conv_side + dx) * (int)g.lda0 * 2;
             const u32x4 r = buf_desc(g.A0, bytesA);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int yy = (gpos[h * 2 + i] >> 16) + dy, xx = (gpos[h * 2 + i] & 0xFFFF) + dx;
+            for (int i = 0; i < C::HP; ++i) {
+                const int yy = (gpos[h * C::HP + i] >> 16) + dy, xx = (gpos[h * C::HP + i] & 0xFFFF) + dx;
                 const bool ok = in && (unsigned)yy < (unsigned)g.conv_side && (unsigned)xx < (unsigned)g.conv_side;
-                dma16(l + i * 8192, ok ? (unsigned)((int)aoff[h * 2 + i] + shift) : OOB, r, in ? c0 * 2 : 0);
+                dma16(l + i * 8192, ok ? (unsigned)((int)aoff[h * C::HP + i] + shift) : OOB, r, in ? c0 * 2 : 0);
             }
         } else {
             const bool second = g.A1 && k0 >= g.K0;
             const u32x4 r = buf_desc(second ? g.A1 : g.A0, in ? bytesA : 0);
             const unsigned so = in ? (second ? (k0 - g.K0) * 2 : (kbase + k0) * 2) : 0;
 #pragma unroll
-            for (int i = 0; i < 2; ++i) dma16(l + i * 8192, aoff[h * 2 + i], r, so);
+            for (int i = 0; i < C::HP; ++i) dma16(l + i * 8192, aoff[h * C::HP + i], r, so);
         }
     };
     auto load_b = [&](int t, int stage, auto from, auto to) {
@@ -895,18 +682,18 @@ __global__ __launch_bounds__(C::NT, 2) void gemm_pp_kernel(GemmArgs g, EpiParams
         __builtin_amdgcn_sched_barrier(0);
     };
     constexpr IntC<0> B0{};
-    constexpr IntC<C::BL> BM_{};
+    constexpr IntC<C::BL> BLO{};
     constexpr IntC<C::BP> B1{};
     // load order per tile: A half 0 and the first BL B parts (phase 1 of tile t - 2), the other B
     // parts and A half 1 (phase 0 of tile t - 1).  Before phase 1 of tile t is read, at most the
-    // loads issued after its A half 1 may be outstanding: phase 1 of t - 1 (2 + BL) and phase 0
-    // of t (BP - BL + 2); before phase 0 of tile t: its A half 1 (2) and phase 1 of t - 1 (2 + BL).
-    constexpr int W0 = C::BP + 4, W1 = C::BL + 4;
+    // loads issued after its A half 1 may be outstanding: phase 1 of t - 1 (HP + BL) and phase 0
+    // of t (BP - BL + HP); before phase 0 of tile t: its A half 1 (HP) and phase 1 of t - 1 (HP + BL).
+    constexpr int W0 = C::BP + 2 * C::HP, W1 = C::BL + 2 * C::HP;
     load_a(0, 0, 0);
     load_b(0, 0, B0, B1);
     load_a(0, 0, 1);
     load_a(1, 1, 0);
-    load_b(1, 1, B0, BM_);
+    load_b(1, 1, B0, BLO);
     vm_wait<W1>();
     raw_barrier();
     const bool late = wave >= 4;  // the second group runs half a phase behind
@@ -916,7 +703,7 @@ __global__ __launch_bounds__(C::NT, 2) void gemm_pp_kernel(GemmArgs g, EpiParams
         __builtin_amdgcn_sched_barrier(0);
         read_b(s);
         read_a(s, 0);
-        load_b(t + 1, s ^ 1, BM_, B1);
+        load_b(t + 1, s ^ 1, BLO, B1);
         load_a(t + 1, s ^ 1, 1);
         vm_wait<W0>();
         turn();
@@ -926,7 +713,7 @@ __global__ __launch_bounds__(C::NT, 2) void gemm_pp_kernel(GemmArgs g, EpiParams
         __builtin_amdgcn_sched_barrier(0);
         read_a(s, 1);
         load_a(t + 2, s, 0);
-        load_b(t + 2, s, B0, BM_);
+        load_b(t + 2, s, B0, BLO);
         vm_wait<W1>();
         turn();
         mfmas(1);
@@ -950,68 +737,300 @@ __global__ __launch_bounds__(C::NT, 2) void gemm_pp_kernel(GemmArgs g, EpiParams
                 split);
 }
 
+// --------------------------------------------------------------------------- K-group kernel
+//
+// Small tiles (64 x 64 to 128 x 128) for products with too few tiles to fill the chip: what such a
+// product takes is its chain of k tiles, so the two wave groups split K instead of the tile.  Group
+// g takes k tiles g, g + 2, ..., each with a full set of accumulators (four waves, 2 x 2), and the
+// groups run half a step apart as above: while one issues a tile's MFMAs the other reads its
+// fragments.  The MFMA slot also issues the loads that refill the stage just read, one between two
+// MFMAs.  At the end the groups exchange halves of their sums through LDS and each finishes its own
+// half of the rows (64-row tiles: group 0 finishes all).
+//
+// A step's length is the LDS's: 128 x 128 tiles take 0.38 us per 64-deep k tile on their own (64 KB
+// of fragment reads, 32 KB of loads landing at 64 bytes a cycle), 64 x 64 0.18.  The 128 x 128
+// kernel with register-staged loads that it replaced took 0.37-0.46.  Residual products, before ->
+// after (weights cold): 200 x 4096 x 12288 100 -> 46 us, 512 x 1152 x 4608 34 -> 19, 625 x 1280 x 5120
+// 40 -> 21; 3 x 3 convolution on 625 positions of 1280 channels 100 -> 38.
+
+template <int BM_, int BN_, int S_>
+struct PKCfg {
+    static constexpr int BM = BM_, BN = BN_, S = S_, NT = 512;
+    static constexpr int TMW = BM / 64, TN = BN / 64, WN = BN / 2;  // a wave's MFMA blocks, columns
+    static constexpr int TM = 1;                                    // row blocks per wave in the epilogue
+    static constexpr int AP = BM / 32, BP = BN / 32, P = AP + BP;   // loads per wave and k tile
+    static constexpr int A_BYTES = BM * 128, STAGE = (BM + BN) * 128;
+    static constexpr int LDS_BYTES = 2 * S * STAGE;
+    // two-block waves: group g finishes row block g of its wave row (row index wm * 2 + g)
+    __device__ static __forceinline__ int block_row(int w, int) { return w * 32; }
+    static_assert((TMW == 1 || TMW == 2) && P <= 4 * TMW * TN && (S - 1) * P < 64, "k-group tile");
+    static_assert(LDS_BYTES <= 160 * 1024 && LDS_BYTES >= BM * BN * 4, "LDS: stages, then the exchange");
+};
+
+template <class C, bool CONV, bool SPLIT>
+__global__ __launch_bounds__(C::NT, 2) void gemm_pk_kernel(GemmArgs g, EpiParams ep) {
+    __shared__ __attribute__((aligned(1024))) char lds[C::LDS_BYTES];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), grp = wave >> 2, gw = wave & 3;
+    const int nt_m = (g.M - g.m_begin + C::BM - 1) / C::BM;
+    const int nt_n = (g.N + C::BN - 1) / C::BN;
+    const int split = SPLIT ? (int)blockIdx.x / (nt_m * nt_n) : 0;
+    int tm, tn;
+    tile_at(tile_position((int)blockIdx.x - split * nt_m * nt_n, nt_m * nt_n), nt_m, nt_n, g.band, tm, tn);
+    const int m0 = g.m_begin + tm * C::BM;
+    const int KT = (SPLIT ? g.K / g.ksplit : g.K) / 64;
+    const int kbase = SPLIT ? split * (g.K / g.ksplit) : 0;
+    const unsigned bytesA = (unsigned)((long)g.M * g.lda0 * 2), bytesB = (unsigned)((long)g.N * g.ldb * 2);
+    constexpr unsigned OOB = 0xFFFFFF00u;
+
+    // load part p: rows 32 p + 8 gw + lane / 8 of an operand tile, swizzled chunk as in the large-tile kernel
+    const int prow = gw * 8 + (lane >> 3);
+    const int pch = ((lane & 7) ^ ((prow >> 1) & 7)) * 16;
+    unsigned off[C::P];
+    int gpos[CONV ? C::AP : 1];
+#pragma unroll
+    for (int p = 0; p < C::AP; ++p) {
+        const int row = m0 + p * 32 + prow;
+        off[p] = (unsigned)((long)row * g.lda0 * 2 + pch);
+        if constexpr (CONV) {
+            const int side = g.conv_side, pix = row % (side * side), y = pix / side;
+            gpos[p] = (y << 16) | (pix - y * side);
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < C::BP; ++p)
+        off[C::AP + p] = (unsigned)(weight_row<C>(ep, g.N / 2, tn, p * 32 + prow) * g.ldb * 2 + pch);
+    const unsigned lw = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds + grp * (C::S * C::STAGE) + gw * 1024;
+    // the group's i-th k tile into stage i % S; tiles at or past K load zeros
+    struct Src { u32x4 ra, rb; unsigned sa, sb; int dy, dx, shift; bool in; };
+    auto source = [&](int i) {
+        const int t = 2 * i + grp, k0 = t * 64;
+        Src c;
+        c.in = t < KT;
+        c.sb = c.in ? (kbase + k0) * 2 : 0;
+        c.rb = buf_desc(g.B, c.in ? bytesB : 0);
+        c.dy = c.dx = c.shift = 0;
+        if constexpr (CONV) {
+            const int tap = k0 / g.conv_c, ky = tap / 3;
+            c.dy = ky - 1;
+            c.dx = tap - ky * 3 - 1;
+            c.shift = (c.dy * g.conv_side + c.dx) * (int)g.lda0 * 2;
+            c.ra = buf_desc(g.A0, c.in ? bytesA : 0);
+            c.sa = c.in ? (k0 - tap * g.conv_c) * 2 : 0;
+        } else {
+            const bool second = g.A1 && k0 >= g.K0;
+            c.ra = buf_desc(second ? g.A1 : g.A0, c.in ? bytesA : 0);
+            c.sa = c.in ? (second ? (k0 - g.K0) * 2 : (kbase + k0) * 2) : 0;
+        }
+        return c;
+    };
+    auto load = [&](const Src& c, unsigned l, int p) {
+        if (p < C::AP) {
+            unsigned o = off[p];
+            if constexpr (CONV) {
+                const int yy = (gpos[p] >> 16) + c.dy, xx = (gpos[p] & 0xFFFF) + c.dx;
+                const bool ok = (unsigned)yy < (unsigned)g.conv_side && (unsigned)xx < (unsigned)g.conv_side;
+                o = ok ? (unsigned)((int)o + c.shift) : OOB;
+            }
+            dma16(l + p * 4096, o, c.ra, c.sa);
+        } else {
+            dma16(l + C::A_BYTES + (p - C::AP) * 4096, off[p], c.rb, c.sb);
+        }
+    };
+
+    const int wm = gw >> 1, wn = gw & 1;
+    const int lrow = lane & 31, lhalf = lane >> 5;
+    const char *fa[4], *fb[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int sw = ((q * 2 + lhalf) ^ ((lrow >> 1) & 7)) << 4;
+        fa[q] = lds + grp * (C::S * C::STAGE) + (wm * (C::BM / 2) + lrow) * 128 + sw;
+        fb[q] = lds + grp * (C::S * C::STAGE) + C::A_BYTES + (wn * C::WN + lrow) * 128 + sw;
+    }
+    f32x16 acc[C::TMW][C::TN];
+#pragma unroll
+    for (int i = 0; i < C::TMW; ++i)
+#pragma unroll
+        for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+#pragma unroll
+    for (int s = 0; s < C::S; ++s) {
+        const Src c = source(s);
+#pragma unroll
+        for (int p = 0; p < C::P; ++p) load(c, lw + s * C::STAGE, p);
+    }
+    constexpr int W = (C::S - 1) * C::P;  // the next tile has landed; those after it may be in flight
+    vm_wait<W>();
+    raw_barrier();
+    if (grp) raw_barrier();
+    const int steps = (KT + 1) / 2;  // the same for both groups: barriers match
+    int stage = 0;
+    for (int i = 0; i < steps; ++i) {
+        const int so = stage * C::STAGE;
+        bf16x8 af[C::TMW][4], bfr[C::TN][4];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+#pragma unroll
+            for (int x = 0; x < C::TMW; ++x) af[x][q] = *(const bf16x8*)(fa[q] + so + x * 4096);
+#pragma unroll
+            for (int x = 0; x < C::TN; ++x) bfr[x][q] = *(const bf16x8*)(fb[q] + so + x * 4096);
+        }
+        const Src c = source(i + C::S);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        raw_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int x = 0; x < C::TMW; ++x)
+#pragma unroll
+                for (int y = 0; y < C::TN; ++y) {
+                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[x][q], bfr[y][q], acc[x][y], 0, 0, 0);
+                    const int slot = (q * C::TMW + x) * C::TN + y;
+                    if (slot < C::P) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        load(c, lw + so, slot);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+        vm_wait<W>();
+        __builtin_amdgcn_sched_barrier(0);
+        raw_barrier();
+        stage = stage + 1 == C::S ? 0 : stage + 1;
+    }
+    if (!grp) raw_barrier();
+    vm_wait<0>();  // the loads past K have written their zeros before LDS is used for the exchange
+    raw_barrier();
+    // exchange: register group of four of block (x, y), register quad q, of wave gw: 1 KB a wave
+    f32x4* const ex = (f32x4*)lds;
+    auto slot_of = [&](int y, int q, int half) { return (((half * 4 + gw) * C::TN + y) * 4 + q) * 64 + lane; };
+    f32x16 sum[1][C::TN];
+    if constexpr (C::TMW == 2) {
+#pragma unroll
+        for (int y = 0; y < C::TN; ++y)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                f32x4 o;  // the other group's row block
+#pragma unroll
+                for (int u = 0; u < 4; ++u) o[u] = grp ? acc[0][y][q * 4 + u] : acc[1][y][q * 4 + u];
+                ex[slot_of(y, q, grp)] = o;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int y = 0; y < C::TN; ++y)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 o = ex[slot_of(y, q, grp ^ 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) sum[0][y][q * 4 + u] = (grp ? acc[1][y][q * 4 + u] : acc[0][y][q * 4 + u]) + o[u];
+            }
+    } else {
+        if (grp) {
+#pragma unroll
+            for (int y = 0; y < C::TN; ++y)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    f32x4 o;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) o[u] = acc[0][y][q * 4 + u];
+                    ex[slot_of(y, q, 0)] = o;
+                }
+        }
+        __syncthreads();
+        if (grp) return;
+#pragma unroll
+        for (int y = 0; y < C::TN; ++y)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 o = ex[slot_of(y, q, 0)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) sum[0][y][q * 4 + u] = acc[0][y][q * 4 + u] + o[u];
+            }
+    }
+    const char __attribute__((address_space(4)))* args =
+        (const char __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    constexpr int EP_AT = (sizeof(GemmArgs) + alignof(EpiParams) - 1) / alignof(EpiParams) * alignof(EpiParams);
+    epilogue<C>(sum, *(const GemmArgs*)(const char*)args, *(const EpiParams*)(const char*)(args + EP_AT), m0, tn,
+                wm * C::TMW + (C::TMW == 2 ? grp : 0), wn, split);
+}
+
 // --------------------------------------------------------------------------- dispatch
 
 namespace {
-// block tiles (BM, BN), eight waves, 64-deep k tiles.  The 128-row tiles have two LDS stages plus
-// two register slots: with weights streamed from HBM, one period of a 128 x 128 tile is too short
-// for a load to arrive (LLaDA O and W2: -17 % time with two slots instead of one).
-using T256x256 = PPCfg<256, 2, 4>;                      // 128 x 64 wave tiles
-using T256x192 = PPCfg<192, 4, 2>;                      // 64 x 96
-using T256x128 = PPCfg<128, 4, 2>;                      // 64 x 64
-using T128x256 = TileCfg<128, 256, 2, 4, 64, 2, 2, 2>;  // 64 x 64
-using T128x128 = TileCfg<128, 128, 2, 4, 64, 2, 2, 2>;  // 64 x 32
+using T256x256 = PPCfg<256, 256, 2, 4>;  // 128 x 64 wave tiles
+using T256x192 = PPCfg<256, 192, 4, 2>;  // 64 x 96
+using T256x128 = PPCfg<256, 128, 4, 2>;  // 64 x 64
+using T128x256 = PPCfg<128, 256, 2, 4>;  // 64 x 64
+using T128x128 = PKCfg<128, 128, 2>;
+using T128x64 = PKCfg<128, 64, 3>;
+using T64x64 = PKCfg<64, 64, 4>;
 
-struct Shape { int bm, bn; double rate; };
-// tile id -> block shape and its per-CU throughput relative to 256 x 256 (measured on the
-// branch GEMM shapes: smaller tiles move more operand bytes per FLOP through L2 and LDS)
+// tile id -> block shape and what a tile takes: us per 64-deep k tile with the chip nearly empty and
+// with every CU busy, and us for its start and epilogue.  Fitted to 62 products (64 to 8256 rows, 640
+// to 24576 columns, K 640 to 12288, weights cold) timed with every tile; the choice made from
+// them is within 0.2 % of the fastest tile on average and 7 % at worst.  An empty chip is bound by
+// the LDS (fragment reads at ~200 bytes and direct loads at 64 bytes a cycle), a full one by power
+// and the memory side.
+struct Shape { int bm, bn; double t0, t1, fix; };
 Shape tile_shape(int tile) {
     switch (tile) {
-        case 1: return {256, 256, 1.0};
-        case 2: return {256, 128, 0.78};
-        case 3: return {128, 256, 0.80};
-        case 4: return {128, 128, 0.51};
-        case 5: return {256, 192, 0.82};
-        default: return {0, 0, 0.0};
+        case 1: return {256, 256, 0.86, 1.51, 7.7};
+        case 2: return {256, 128, 0.62, 1.03, 2.3};
+        case 3: return {128, 256, 0.66, 1.05, 2.4};
+        case 4: return {128, 128, 0.28, 0.58, 2.2};
+        case 5: return {256, 192, 0.77, 1.31, 5.1};
+        case 6: return {128, 64, 0.17, 0.36, 2.3};
+        case 7: return {64, 64, 0.11, 0.23, 2.3};
+        default: return {0, 0, 0.0, 0.0, 0.0};
     }
 }
+// a second launch for the tail rows
+constexpr double kTailLaunch = 4.0;
 }  // namespace
 
-// Cost of one launch of `tile` over `rows` rows in units of a 256 x 256 tile at full rate: one
-// workgroup per CU, so n tiles take ceil(n / 256) rounds of tile area / per-CU rate.
-// Infinite when the epilogue cannot use the tile.
-static bool conv_tile(int tile) { return tile == 2 || tile == 4 || tile == 5; }
+static bool conv_tile(int tile) { return tile == 2 || (tile >= 4 && tile <= 7); }
 
+// Time (us) of one launch of `tile` over `rows` rows: one workgroup per CU, so n tiles take n / 256
+// full rounds and a last one whose k tiles are faster the emptier it is.  Infinite when the epilogue
+// cannot use the tile.
 static double tile_cost(int tile, long rows, const GemmArgs& g, const EpiParams& e) {
     const Shape s = tile_shape(tile);
     if (!s.bm) return 1e300;
     if (g.conv_side > 0 && !conv_tile(tile)) return 1e300;
     if (e.kind == EP_GATED && g.N % s.bn) return 1e300;
     const long tiles = ((rows + s.bm - 1) / s.bm) * ((g.N + s.bn - 1) / s.bn);
-    return (double)((tiles + 255) / 256) * s.bm * s.bn / s.rate / (256.0 * 256.0);
+    const long full = tiles / 256, rem = tiles % 256;
+    const double kt = g.K / 64.0;
+    double t = full * (kt * s.t1 + s.fix);
+    if (rem) t += kt * (s.t0 + (s.t1 - s.t0) * (double)rem / 256.0) + s.fix;
+    return t;
 }
 
-// Automatic choice: the tile with the least cost (e.g. at 1024 rows the 4096-column GEMMs run
-// 128 x 128 tiles, one full round, rather than 64 large tiles).  When the rows leave a short
-// tail past the last whole 256-row tile (U-ViT: 32 x 258 = 8256 = 32 x 256 + 64 rows), the
-// tail can go to a second launch of 128-row tiles, so the main launch fills whole rounds
-// instead of starting a third round for 64 rows; the split is taken when it is cheaper with
-// the second launch charged a tenth of a round for its start-up.
+// Automatic choice: the tile with the least cost (200 x 4096 x 12288: 64 x 64 tiles, 256 of them, 45 us
+// against 99 with 64 of 128 x 128; 1024 x 4096 x 4096: one round of 128 x 128).  When the rows leave a
+// short tail past the last whole 256-row tile (U-ViT: 32 x 258 = 8256 = 32 x 256 + 64 rows), the tail
+// can go to a second launch of small tiles, so the main launch fills whole rounds instead of starting
+// a third one for 64 rows (8256 x 4096 x 1024: 90 us against 100).
 GemmPlan gemm_bf16_plan(const GemmArgs& g, const EpiParams& e) {
     GemmPlan best{1, g.M, 0};
     double best_t = 1e300;
     for (int tile = 1; tile <= kGemmTiles; ++tile) {
         const double t = tile_cost(tile, g.M, g, e);
-        if (t < best_t * 0.999) { best_t = t; best = GemmPlan{tile, g.M, 0}; }
+        if (t < best_t) { best_t = t; best = GemmPlan{tile, g.M, 0}; }
     }
     const int tail = g.M % 256;
-    if (g.M > 2048 && tail > 0 && tail <= 128 && g.conv_side == 0) {
+    if (g.M > 512 && tail > 0 && tail <= 128 && g.conv_side == 0) {
         for (int tile = 1; tile <= kGemmTiles; ++tile) {
             if (tile_shape(tile).bm != 256) continue;
             const double tm = tile_cost(tile, g.M - tail, g, e);
             for (int tt = 1; tt <= kGemmTiles; ++tt) {
-                if (tile_shape(tt).bm != 128) continue;
-                const double t = tm + tile_cost(tt, tail, g, e) + 0.1;
+                if (tile_shape(tt).bm > 128) continue;
+                const double t = tm + tile_cost(tt, tail, g, e) + kTailLaunch;
                 if (t < best_t * 0.97) { best_t = t; best = GemmPlan{tile, g.M - tail, tt}; }
             }
         }
@@ -1081,16 +1100,17 @@ bool gemm_bf16_shape_ok(const GemmArgs& g, const EpiParams& e, int tile) {
     return true;
 }
 
+template <class C> struct is_pk : std::false_type {};
+template <int BM, int BN, int S> struct is_pk<PKCfg<BM, BN, S>> : std::true_type {};
+
 template <class C, bool CONV = false, bool SPLIT = false>
 static hipError_t run_tile(const GemmArgs& g, const EpiParams& e, hipStream_t st) {
     const int nt_m = (g.M - g.m_begin + C::BM - 1) / C::BM, nt_n = (g.N + C::BN - 1) / C::BN;
     GemmArgs ga = g;
     ga.band = tile_band(nt_m, nt_n, C::BM, C::BN);
-    if constexpr (C::BM == 256)
-        hipLaunchKernelGGL((gemm_pp_kernel<C, CONV, SPLIT>), dim3(nt_m * nt_n * (SPLIT ? g.ksplit : 1)), dim3(C::NT), 0,
-                           st, ga, e);
-    else
-        hipLaunchKernelGGL((gemm_bf16_kernel<C, CONV>), dim3(nt_m * nt_n), dim3(C::NT), 0, st, ga, e);
+    const dim3 grid(nt_m * nt_n * (SPLIT ? g.ksplit : 1));
+    if constexpr (is_pk<C>::value) hipLaunchKernelGGL((gemm_pk_kernel<C, CONV, SPLIT>), grid, dim3(C::NT), 0, st, ga, e);
+    else hipLaunchKernelGGL((gemm_pp_kernel<C, CONV, SPLIT>), grid, dim3(C::NT), 0, st, ga, e);
     return hipGetLastError();
 }
 
@@ -1100,6 +1120,8 @@ static hipError_t launch_tile(const GemmArgs& g, const EpiParams& e, hipStream_t
             case 2: return run_tile<T256x128, true>(g, e, st);
             case 4: return run_tile<T128x128, true>(g, e, st);
             case 5: return run_tile<T256x192, true>(g, e, st);
+            case 6: return run_tile<T128x64, true>(g, e, st);
+            case 7: return run_tile<T64x64, true>(g, e, st);
             default: return hipErrorInvalidValue;
         }
     }
@@ -1113,6 +1135,8 @@ static hipError_t launch_tile(const GemmArgs& g, const EpiParams& e, hipStream_t
         case 3: return run_tile<T128x256>(g, e, st);
         case 4: return run_tile<T128x128>(g, e, st);
         case 5: return run_tile<T256x192>(g, e, st);
+        case 6: return run_tile<T128x64>(g, e, st);
+        case 7: return run_tile<T64x64>(g, e, st);
         default: return hipErrorInvalidValue;
     }
 }

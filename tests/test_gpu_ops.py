@@ -463,3 +463,27 @@ def test_heads_short_dims(P, tile, H, dh):
         r = om.heads(z[:, i * d:(i + 1) * d].reshape(B, N, d), H)
         assert np.isfinite(g).all()
         assert np.max(np.abs(g - r)) <= 2 ** -7 * np.max(np.abs(r))
+
+
+@pytest.mark.parametrize("M,N,K", [(300, 4608, 192), (1, 2304, 64), (129, 2560, 128), (65, 64, 64), (64, 4096, 576)])
+def test_small_products_bf16(P, M, N, K):
+    """Products the automatic choice gives to 128 x 64 and 64 x 64 tiles, whose two wave groups take
+    alternate k tiles: one, two, three and nine of them (an odd count leaves the second group a tile
+    of zeros), one row, one row past a tile, a single tile; plain, gated and residual epilogues."""
+    rng = np.random.default_rng(M + N + K)
+    A = synth.store(rng.standard_normal((M, K)), "bf16")
+    W = synth.store(rng.standard_normal((N, K)) / np.sqrt(K), "bf16")
+    b = synth.representable(0.1 * rng.standard_normal(N), "bf16")
+    z = decode(A, "bf16") @ decode(W, "bf16").T + b
+    out = empty((M, N), "bf16")
+    P.op_linear(dev(A), dev(W), out, bias=dev(b))
+    assert np.max(np.abs(host(out) - round_bf16(z))) <= 2 ** -7 * np.max(np.abs(z))
+    if N % 128 == 0:
+        F = N // 2
+        out = empty((M, F), "bf16")
+        P.op_linear(dev(A), dev(W), out, bias=dev(b), act=3, gated=True)
+        assert relmax(host(out), om.silu(z[:, :F]) * z[:, F:]) <= 1e-2
+    h0 = rng.standard_normal((M, N)).astype(np.float32)
+    th, td = dev(h0), dev(np.zeros_like(h0))
+    P.op_residual(dev(A), dev(W), th, bias=dev(b), delta=td, delta_mode=1)
+    assert relmax(host(td), z) <= 1e-5 and relmax(host(th), h0 + z) <= 1e-5
