@@ -520,16 +520,16 @@ __device__ __forceinline__ void epilogue(f32x16 (&acc)[C::TM][C::TN], const Gemm
 // in a whole step the clock falls with the power drawn and half of that remains.  Two workgroups of 128 x 256 per CU instead (epilogues overlapped)
 // ran at 1030 on 8192^3: they move 1.5x the operand bytes.
 
-template <int BM_, int BN_, int WGM_, int WGN_>
+template <int BM_, int BN_, int WGM_, int WGN_, int ST_ = 2>
 struct PPCfg {
-    static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, NT = 512, NW = 8;
+    static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, ST = ST_, NT = 512, NW = 8;
     static constexpr int BH = BM / 2, HP = BH / 64;      // rows and load parts (64 rows) of each half
     static constexpr int RW = BH / WGM;                  // a wave's rows of each half
     static constexpr int CB = RW / 32, TM = 2 * CB;      // MFMA row blocks per half, per wave
     static constexpr int WN = BN / WGN, TN = WN / 32;
     static constexpr int BP = BN / 64, BL = BP / 2;      // B parts (64 rows) per tile; those loaded in phase 1
-    static constexpr int A_HALF = BH * 128, A_STAGE = BM * 128, B_STAGE = BN * 128, B_LDS = 2 * A_STAGE;
-    static constexpr int LDS_BYTES = B_LDS + 2 * B_STAGE;
+    static constexpr int A_HALF = BH * 128, A_STAGE = BM * 128, B_STAGE = BN * 128, B_LDS = ST * A_STAGE;
+    static constexpr int LDS_BYTES = B_LDS + ST * B_STAGE;
     __device__ static __forceinline__ int block_row(int wm, int i) { return (i / CB) * BH + wm * RW + (i % CB) * 32; }
     static_assert(WGM * WGN == NW && RW % 32 == 0 && WN % 32 == 0 && BN % 64 == 0 && BH % 64 == 0, "wave tile");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS");
@@ -599,7 +599,7 @@ __global__ __launch_bounds__(C::NT, 2) void gemm_pp_kernel(GemmArgs g, EpiParams
         boff[p] = (unsigned)(weight_row<C>(ep, F, tn, p * 64 + prow) * g.ldb * 2 + pch);
     }
     const unsigned lw = (unsigned)(uintptr_t)(__attribute__((address_space(3))) char*)lds + wave * 1024;
-    // k tile t's half h of A into stage t % 2 (stage and part numbers are compile-time constants
+    // k tile t's half h of A into stage t % ST (stage and part numbers are compile-time constants
     // at every call); tiles at or past K load nothing but still count
     auto load_a = [&](int t, int stage, int h) {
         const bool in = t < KT;
@@ -684,27 +684,32 @@ __global__ __launch_bounds__(C::NT, 2) void gemm_pp_kernel(GemmArgs g, EpiParams
     constexpr IntC<0> B0{};
     constexpr IntC<C::BL> BLO{};
     constexpr IntC<C::BP> B1{};
-    // load order per tile: A half 0 and the first BL B parts (phase 1 of tile t - 2), the other B
-    // parts and A half 1 (phase 0 of tile t - 1).  Before phase 1 of tile t is read, at most the
-    // loads issued after its A half 1 may be outstanding: phase 1 of t - 1 (HP + BL) and phase 0
-    // of t (BP - BL + HP); before phase 0 of tile t: its A half 1 (HP) and phase 1 of t - 1 (HP + BL).
-    constexpr int W0 = C::BP + 2 * C::HP, W1 = C::BL + 2 * C::HP;
-    load_a(0, 0, 0);
-    load_b(0, 0, B0, B1);
-    load_a(0, 0, 1);
-    load_a(1, 1, 0);
-    load_b(1, 1, B0, BLO);
+    // load order per tile: A half 0 and the first BL B parts (phase 1 of tile t - ST), the other B
+    // parts and A half 1 (phase 0 of tile t - ST + 1).  Before phase 1 of tile t is read, at most the
+    // loads issued after its A half 1 may be outstanding: ST - 1 tiles' worth; before phase 0 of
+    // tile t, those after its B parts: its A half 1, ST - 1 phases 1 and ST - 2 phases 0.
+    constexpr int L1 = C::HP + C::BL, L0 = C::BP - C::BL + C::HP;  // loads of phases 1 and 0
+    constexpr int W0 = (C::ST - 1) * (L0 + L1), W1 = C::HP + (C::ST - 1) * L1 + (C::ST - 2) * L0;
+    static_assert(W0 < 64, "vmcnt");
+    static_for<C::ST - 1>([&](auto sc) {
+        constexpr int s = decltype(sc)::value;
+        load_a(s, s, 0);
+        load_b(s, s, B0, B1);
+        load_a(s, s, 1);
+    });
+    load_a(C::ST - 1, C::ST - 1, 0);
+    load_b(C::ST - 1, C::ST - 1, B0, BLO);
     vm_wait<W1>();
     raw_barrier();
     const bool late = wave >= 4;  // the second group runs half a phase behind
     if (late) raw_barrier();
     auto tile = [&](int t, auto sc) {
-        constexpr int s = decltype(sc)::value;
+        constexpr int s = decltype(sc)::value, prev = (s + C::ST - 1) % C::ST;
         __builtin_amdgcn_sched_barrier(0);
         read_b(s);
         read_a(s, 0);
-        load_b(t + 1, s ^ 1, BLO, B1);
-        load_a(t + 1, s ^ 1, 1);
+        load_b(t + C::ST - 1, prev, BLO, B1);
+        load_a(t + C::ST - 1, prev, 1);
         vm_wait<W0>();
         turn();
         mfmas(0);
@@ -712,8 +717,8 @@ __global__ __launch_bounds__(C::NT, 2) void gemm_pp_kernel(GemmArgs g, EpiParams
         raw_barrier();
         __builtin_amdgcn_sched_barrier(0);
         read_a(s, 1);
-        load_a(t + 2, s, 0);
-        load_b(t + 2, s, B0, BLO);
+        load_a(t + C::ST, s, 0);
+        load_b(t + C::ST, s, B0, BLO);
         vm_wait<W1>();
         turn();
         mfmas(1);
@@ -721,10 +726,10 @@ __global__ __launch_bounds__(C::NT, 2) void gemm_pp_kernel(GemmArgs g, EpiParams
         raw_barrier();
         __builtin_amdgcn_sched_barrier(0);
     };
-    for (int t = 0; t < KT; t += 2) {
-        tile(t, IntC<0>{});
-        if (t + 1 < KT) tile(t + 1, IntC<1>{});
-    }
+    for (int t = 0; t < KT; t += C::ST)
+        static_for<C::ST>([&](auto sc) {
+            if (t + decltype(sc)::value < KT) tile(t + decltype(sc)::value, sc);
+        });
     if (!late) raw_barrier();
     vm_wait<0>();
     // the epilogue's arguments are read again here, through an address the compiler cannot see
@@ -964,8 +969,8 @@ __global__ __launch_bounds__(C::NT, 2) void gemm_pk_kernel(GemmArgs g, EpiParams
 namespace {
 using T256x256 = PPCfg<256, 256, 2, 4>;  // 128 x 64 wave tiles
 using T256x192 = PPCfg<256, 192, 4, 2>;  // 64 x 96
-using T256x128 = PPCfg<256, 128, 4, 2>;  // 64 x 64
-using T128x256 = PPCfg<128, 256, 2, 4>;  // 64 x 64
+using T256x128 = PPCfg<256, 128, 4, 2, 3>;  // 64 x 64
+using T128x256 = PPCfg<128, 256, 2, 4, 3>;  // 64 x 64
 using T128x128 = PKCfg<128, 128, 2>;
 using T128x64 = PKCfg<128, 64, 3>;
 using T64x64 = PKCfg<64, 64, 4>;
@@ -979,13 +984,13 @@ using T64x64 = PKCfg<64, 64, 4>;
 struct Shape { int bm, bn; double t0, t1, fix; };
 Shape tile_shape(int tile) {
     switch (tile) {
-        case 1: return {256, 256, 0.86, 1.51, 7.7};
-        case 2: return {256, 128, 0.62, 1.03, 2.3};
-        case 3: return {128, 256, 0.66, 1.05, 2.4};
-        case 4: return {128, 128, 0.28, 0.58, 2.2};
-        case 5: return {256, 192, 0.77, 1.31, 5.1};
-        case 6: return {128, 64, 0.17, 0.36, 2.3};
-        case 7: return {64, 64, 0.11, 0.23, 2.3};
+        case 1: return {256, 256, 0.87, 1.5, 7.5};
+        case 2: return {256, 128, 0.56, 0.89, 2.7};
+        case 3: return {128, 256, 0.65, 0.97, 1.9};
+        case 4: return {128, 128, 0.29, 0.59, 2.1};
+        case 5: return {256, 192, 0.78, 1.3, 4.9};
+        case 6: return {128, 64, 0.18, 0.38, 1.7};
+        case 7: return {64, 64, 0.10, 0.245, 2.4};
         default: return {0, 0, 0.0, 0.0, 0.0};
     }
 }
@@ -998,14 +1003,14 @@ static bool conv_tile(int tile) { return tile == 2 || (tile >= 4 && tile <= 7); 
 // Time (us) of one launch of `tile` over `rows` rows: one workgroup per CU, so n tiles take n / 256
 // full rounds and a last one whose k tiles are faster the emptier it is.  Infinite when the epilogue
 // cannot use the tile.
-static double tile_cost(int tile, long rows, const GemmArgs& g, const EpiParams& e) {
+static double tile_cost(int tile, long rows, const GemmArgs& g, const EpiParams& e, int ks = 1) {
     const Shape s = tile_shape(tile);
     if (!s.bm) return 1e300;
     if (g.conv_side > 0 && !conv_tile(tile)) return 1e300;
     if (e.kind == EP_GATED && g.N % s.bn) return 1e300;
-    const long tiles = ((rows + s.bm - 1) / s.bm) * ((g.N + s.bn - 1) / s.bn);
+    const long tiles = ((rows + s.bm - 1) / s.bm) * ((g.N + s.bn - 1) / s.bn) * ks;
     const long full = tiles / 256, rem = tiles % 256;
-    const double kt = g.K / 64.0;
+    const double kt = g.K / (64.0 * ks);
     double t = full * (kt * s.t1 + s.fix);
     if (rem) t += kt * (s.t0 + (s.t1 - s.t0) * (double)rem / 256.0) + s.fix;
     return t;
@@ -1040,25 +1045,41 @@ GemmPlan gemm_bf16_plan(const GemmArgs& g, const EpiParams& e) {
 
 int gemm_bf16_auto_tile(const GemmArgs& g, const EpiParams& e) { return gemm_bf16_plan(g, e).tile; }
 
-// Two K ranges where one round of 128 x 128 tiles is the best unsplit plan of a long-K product
-// and 256 x 128 tiles over half of K still fill at most one round: the larger tiles move ~1.5x
-// fewer operand bytes per FLOP through the load path that bounds the small ones (LLaDA's MLP
-// output GEMM, 1024 x 4096 x 12288: 128 tiles x 2 ranges).  The caller adds the two fp32
-// partial products (EP_PARTIAL) to the stream itself.
+// Tiles of a product in K ranges (EP_PARTIAL)
+static bool split_tile(int tile) { return tile == 2 || tile == 4 || tile == 6 || tile == 7; }
+static int partial_tile(const GemmArgs& g, const EpiParams& e) {
+    int best = 2;
+    double best_t = 1e300;
+    for (int tile = 1; tile <= kGemmTiles; ++tile) {
+        if (!split_tile(tile)) continue;
+        const double t = tile_cost(tile, g.M, g, e, g.ksplit);
+        if (t < best_t) { best_t = t; best = tile; }
+    }
+    return best;
+}
+
+// Two K ranges where they shorten a residual product by more than their fp32 partials cost: the
+// pre-norm that adds them to the stream itself reads and writes 12 bytes a value more than the
+// residual epilogue moves (at ~4 TB/s) and is charged 1 us.  Large products gain from larger tiles that
+// still fill the chip (LLaDA's 1024 x 4096 x 12288: 256 x 128 tiles over half of K, 100 us against
+// 120), small ones from a chain of k tiles half as long (200 x 256 x 8192).
 int gemm_bf16_ksplit(const GemmArgs& g) {
+    if (g.A1 || g.conv_side > 0 || g.K % 128) return 1;
     EpiParams e;
     e.kind = EP_RESID;
     e.d = g.N;
     const GemmPlan p = gemm_bf16_plan(g, e);
-    if (p.tile != 4 || p.tail_tile || g.A1 || g.conv_side > 0 || g.K < 8192 || g.K % 128) return 1;
-    const long tiles = (long)((g.M + 255) / 256) * ((g.N + 127) / 128);
-    return 2 * tiles <= 256 ? 2 : 1;
+    if (p.tail_tile) return 1;
+    GemmArgs gs = g;
+    gs.ksplit = 2;
+    const double extra = 12.0 * g.M * g.N / 4e6 + 1.0;
+    return tile_cost(partial_tile(gs, e), g.M, gs, e, 2) + extra < 0.95 * tile_cost(p.tile, g.M, g, e) ? 2 : 1;
 }
 
 static bool aligned(const void* p, unsigned a) { return ((uintptr_t)p % a) == 0; }
 
 bool gemm_bf16_shape_ok(const GemmArgs& g, const EpiParams& e, int tile) {
-    if (tile == 0 && e.kind == EP_PARTIAL) tile = 2;
+    if (tile == 0 && e.kind == EP_PARTIAL) tile = partial_tile(g, e);
     if (tile == 0) {
         const GemmPlan p = gemm_bf16_plan(g, e);
         if (p.tail_tile && !gemm_bf16_shape_ok(g, e, p.tail_tile)) return false;
@@ -1086,7 +1107,7 @@ bool gemm_bf16_shape_ok(const GemmArgs& g, const EpiParams& e, int tile) {
     if (e.kind == EP_GATED && (g.N % s.bn || e.ldo % 4)) return false;
     if (e.kind == EP_ACT && e.ldo % 4) return false;
     if ((e.kind == EP_RESID || e.kind == EP_SKIP || e.kind == EP_PARTIAL) && (g.N != e.d)) return false;
-    if (g.ksplit < 1 || (g.ksplit > 1) != (e.kind == EP_PARTIAL) || (g.ksplit > 1 && tile != 2)) return false;
+    if (g.ksplit < 1 || (g.ksplit > 1) != (e.kind == EP_PARTIAL) || (g.ksplit > 1 && !split_tile(tile))) return false;
     if (e.kind == EP_PARTIAL && (g.A1 || g.conv_side > 0 || g.K % (64 * g.ksplit) || e.gate || e.hcopy ||
                                  e.delta_mode || (long)e.part_stride < (long)g.M * g.N || e.part_stride % 4))
         return false;
@@ -1125,9 +1146,14 @@ static hipError_t launch_tile(const GemmArgs& g, const EpiParams& e, hipStream_t
             default: return hipErrorInvalidValue;
         }
     }
-    if (g.ksplit > 1) {  // K ranges (EP_PARTIAL): the 256 x 128 tiles only
-        if (tile != 2) return hipErrorInvalidValue;
-        return run_tile<T256x128, false, true>(g, e, st);
+    if (g.ksplit > 1) {  // K ranges (EP_PARTIAL)
+        switch (tile) {
+            case 2: return run_tile<T256x128, false, true>(g, e, st);
+            case 4: return run_tile<T128x128, false, true>(g, e, st);
+            case 6: return run_tile<T128x64, false, true>(g, e, st);
+            case 7: return run_tile<T64x64, false, true>(g, e, st);
+            default: return hipErrorInvalidValue;
+        }
     }
     switch (tile) {
         case 1: return run_tile<T256x256>(g, e, st);
@@ -1144,7 +1170,7 @@ static hipError_t launch_tile(const GemmArgs& g, const EpiParams& e, hipStream_t
 // rows [0, m_split) with the plan's tile, then the tail rows [m_split, M) with the tail tile;
 // both launches index rows globally (the epilogue's sample / token split needs it)
 hipError_t launch_gemm_bf16(const GemmArgs& g, const EpiParams& e, hipStream_t st, int tile) {
-    if (e.kind == EP_PARTIAL && tile == 0) tile = 2;  // the split product's 256 x 128 tiles
+    if (e.kind == EP_PARTIAL && tile == 0) tile = partial_tile(g, e);
     if (tile != 0) return launch_tile(g, e, st, tile);
     const GemmPlan p = gemm_bf16_plan(g, e);
     if (!p.tail_tile) return launch_tile(g, e, st, p.tile);

@@ -65,9 +65,8 @@ int gemm_bf16_auto_tile(const GemmArgs& g, const EpiParams& e);
 // automatic tiling: rows [0, m_split) with `tile`, rows [m_split, M) (if any) with tail_tile
 struct GemmPlan { int tile, m_split, tail_tile; };
 GemmPlan gemm_bf16_plan(const GemmArgs& g, const EpiParams& e);
-// K ranges worth splitting the [M x N] product of `g` into (1: none), when one round of
-// 128 x 128 tiles is the best unsplit plan and the K ranges of larger tiles still fit one
-// round; the split product runs 256 x 128 tiles (EP_PARTIAL)
+// K ranges worth splitting the residual product `g` into (1: none), when the partial products
+// (EP_PARTIAL) and their sum in the next pre-norm take less than the unsplit product
 int gemm_bf16_ksplit(const GemmArgs& g);
 
 // ---------------------------------------------------------------- attention
