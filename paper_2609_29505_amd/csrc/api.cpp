@@ -364,8 +364,14 @@ int run_step(sgd_model* m, void* state, int step, const StepPlan& plan, const sg
     const int mlp_act = d.arch == SGD_ARCH_LLADA ? ACT_SILU : dit ? ACT_GELU_TANH : ACT_GELU_ERF;
     const DriftRec* dr = plan.drift;
 
-    // ---- stream set-up and per-step conditioning
-    S.run(SGD_K_STATE, [&] { return launch_stream_init((const float*)state, h, d.B, N, dd, uvit ? 1 : 0, t, S.st); });
+    // ---- stream set-up and per-step conditioning.  hs: where the stream is until the first kernel
+    // that writes it: the state itself, so that no pass copies it (U-ViT's stream starts with its time
+    // token written over the state's)
+    const float* hs = (const float*)state;
+    if (uvit) {
+        S.run(SGD_K_STATE, [&] { return launch_stream_init((const float*)state, h, d.B, N, dd, 1, t, S.st); });
+        hs = h;
+    }
     if (dit || unet)
         S.run(SGD_K_COND, [&] { return launch_cond_silu((const float*)d.class_emb, siluc, d.B, dd, t, S.st); });
 
@@ -414,22 +420,32 @@ int run_step(sgd_model* m, void* state, int step, const StepPlan& plan, const sg
     std::vector<const float*> fold;
     bool fold_parts = false;  // fold holds a split MLP output GEMM's partial products
     auto norm = [&](const float* w, const float* b, const float* shift, const float* scale) {
-        NormArgs a{h, xb, (int)M, dd, norm_kind, norm_eps, w, b, shift, scale, 6L * dd, N};
+        NormArgs a{hs, xb, (int)M, dd, norm_kind, norm_eps, w, b, shift, scale, 6L * dd, N};
+        a.xo = h;
         a.nfold = (int)fold.size();
         for (int i = 0; i < a.nfold; ++i) a.fold[i] = fold[i];
         const int kclass = fold.empty() ? SGD_K_NORM : fold_parts ? SGD_K_NORM_PARTS : SGD_K_FOLD;
         const bool parts = fold_parts;
+        if (!fold.empty()) hs = h;
         fold.clear();
         fold_parts = false;
         S.run(kclass, [&] { return launch_norm(dt, a, S.st, parts); });
     };
+    bool stepped = false;  // the last unit's residual projection has updated the state
     auto resid = [&](int kclass, const void* A, long lda, int K, const void* W, const void* bias, const float* gate,
-                     float* dlt, int dmode, void* hcopy) {
+                     float* dlt, int dmode, void* hcopy, bool last = false) {
         GemmArgs g;
         g.A0 = A; g.lda0 = lda; g.B = W; g.ldb = K; g.M = (int)M; g.N = dd; g.K = K;
         EpiParams e;
         e.kind = EP_RESID; e.bias = (const float*)bias; e.h = h; e.d = dd; e.delta = dlt; e.delta_mode = dmode;
         e.gate = gate; e.gate_ld = 6L * dd; e.ntok = N; e.hcopy = hcopy;
+        e.hin = hs;
+        if (last && plan.sampler) {
+            e.z = (float*)state; e.alpha = args->alpha; e.beta = args->beta;
+            e.r0 = d.update_row_begin; e.r1 = d.update_row_end;
+            stepped = true;
+        }
+        hs = h;
         S.run(kclass, [&] { return launch_gemm(dt, g, e, S.st); });
     };
     auto attention = [&](const void* q, const void* k, const void* vt, int nk, int npk, int kclass) {
@@ -440,7 +456,7 @@ int run_step(sgd_model* m, void* state, int step, const StepPlan& plan, const sg
     auto record_drift = [&](int l) {
         if (!dr) return;
         S.run(SGD_K_DRIFT, [&] {
-            return launch_sumsq(h, dr->prev + (size_t)l * (align256(Md * 4) / 4), dr->prev + (size_t)l * (align256(Md * 4) / 4),
+            return launch_sumsq(hs, dr->prev + (size_t)l * (align256(Md * 4) / 4), dr->prev + (size_t)l * (align256(Md * 4) / 4),
                                 d.B, N, dd, 0, N, dr->have_prev ? 1 : 0, dr->partial + (size_t)l * kSumBlocks * 2, S.st);
         });
     };
@@ -487,7 +503,7 @@ int run_step(sgd_model* m, void* state, int step, const StepPlan& plan, const sg
             // maximal run of frozen units that crosses no skip linear (single units while drift
             // is recorded: each unit's input is measured before its update)
             FrozenRun fr{};
-            fr.h = h; fr.n = (long)Md; fr.r = 0; fr.snap_bf16 = dt;
+            fr.h = h; fr.src = hs; fr.n = (long)Md; fr.r = 0; fr.snap_bf16 = dt;
             const int cap = dr ? 1 : kMaxRun;
             if (dr && !out_start(u)) record_drift(u);
             bool snaps = false;
@@ -507,6 +523,7 @@ int run_step(sgd_model* m, void* state, int step, const StepPlan& plan, const sg
                 fold.assign(fr.delta, fr.delta + fr.r);
                 continue;
             }
+            hs = h;
             S.run(SGD_K_FROZEN, [&] { return launch_frozen_run(fr, S.st); });
             continue;
         }
@@ -522,7 +539,7 @@ int run_step(sgd_model* m, void* state, int step, const StepPlan& plan, const sg
             // ResNet block: GroupNorm + SiLU, 3x3 convolution (+ bias + the block's time
             // projection, computed with the step's modulations) into the hidden buffer,
             // GroupNorm + SiLU, 3x3 convolution added to the stream
-            GroupNormArgs gn{h, xb, d.B, N, dd, d.groups, 1e-5f, (const float*)w.gn1_w, (const float*)w.gn1_b};
+            GroupNormArgs gn{hs, xb, d.B, N, dd, d.groups, 1e-5f, (const float*)w.gn1_w, (const float*)w.gn1_b};
             S.run(SGD_K_GNORM, [&] { return launch_group_norm_silu(0, gn, S.ws + m->w_gn, S.st); });
             GemmArgs g;
             g.A0 = xb; g.lda0 = dd; g.B = w.w_conv1; g.ldb = 9L * dd; g.M = (int)M; g.N = dd; g.K = 9 * dd;
@@ -537,7 +554,8 @@ int run_step(sgd_model* m, void* state, int step, const StepPlan& plan, const sg
             g2.B = w.w_conv2;
             EpiParams e2;
             e2.kind = EP_RESID; e2.bias = (const float*)w.b_conv2; e2.h = h; e2.d = dd; e2.delta = dl;
-            e2.delta_mode = dmode(); e2.ntok = N;
+            e2.delta_mode = dmode(); e2.ntok = N; e2.hin = hs;
+            hs = h;
             S.run(SGD_K_GEMM_CONV, [&] { return launch_gemm(dt, g2, e2, S.st); });
         }
         if (br < 0 || br == BR_ATTN) {
@@ -593,15 +611,15 @@ int run_step(sgd_model* m, void* state, int step, const StepPlan& plan, const sg
                 for (int s2 = 0; s2 < m->w2_ksplit; ++s2) fold.push_back((const float*)(S.ws + m->w_q + s2 * m->part_bytes));
                 fold_parts = true;
             } else {
-                resid(SGD_K_GEMM_W2, hid, F, F, w.w2, w.b2, gate2, dl, dm2, copy2);
+                resid(SGD_K_GEMM_W2, hid, F, F, w.w2, w.b2, gate2, dl, dm2, copy2, u + 1 == nu);
             }
         }
         ++u;
     }
     if (dr && dr->have_prev) S.run(SGD_K_DRIFT, [&] { return launch_sumsq_finish(dr->partial, nu, dr->sums, S.st); });
-    if (plan.sampler)
+    if (plan.sampler && !stepped)
         S.run(SGD_K_STATE, [&] {
-            return launch_state_update((float*)state, h, d.B, N, dd, d.update_row_begin, d.update_row_end, args->alpha,
+            return launch_state_update((float*)state, hs, d.B, N, dd, d.update_row_begin, d.update_row_end, args->alpha,
                                        args->beta, S.st);
         });
     if (S.err != hipSuccess) return hip_fail(S.err, "enqueue");
@@ -937,6 +955,7 @@ extern "C" int sgd_op_norm_fold(int32_t dtype, int32_t kind, float* x, void* y, 
         mod_ld % 4 || (uintptr_t)y % (dtype == SGD_BF16 ? 8 : 16))
         return fail(SGD_E_ARG, "norm operands must be 16-byte aligned (bf16 output: 8)");
     NormArgs a{x, y, M, d, kind, eps, w, b, shift, scale, mod_ld, ntok};
+    a.xo = x;
     a.nfold = r;
     for (int i = 0; i < r; ++i) {
         if (!deltas[i] || (uintptr_t)deltas[i] % 16) return fail(SGD_E_ARG, "NULL or misaligned delta");
@@ -949,7 +968,7 @@ extern "C" int sgd_op_norm_fold(int32_t dtype, int32_t kind, float* x, void* y, 
 extern "C" int sgd_op_frozen_run(float* h, const float* const* deltas, int32_t r, int64_t n, void* hip_stream) {
     if (!h || !deltas || r < 1 || r > kMaxRun || n < 4 || n % 4) return fail(SGD_E_ARG, "bad frozen-run arguments");
     FrozenRun f{};
-    f.h = h; f.n = n; f.r = r; f.snap_bf16 = 1;
+    f.h = h; f.src = h; f.n = n; f.r = r; f.snap_bf16 = 1;
     for (int i = 0; i < r; ++i) {
         if (!deltas[i]) return fail(SGD_E_ARG, "NULL delta");
         f.delta[i] = deltas[i];

@@ -24,7 +24,7 @@ __device__ __forceinline__ void frozen_snap(const FrozenRun& f, int u, long i, c
 __global__ __launch_bounds__(256) void frozen_run_kernel(FrozenRun f) {
     const long n4 = f.n / 4;
     for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n4; i += (long)gridDim.x * 256) {
-        float4 v = ((const float4*)f.h)[i];
+        float4 v = ((const float4*)f.src)[i];
         int u = 0;
         for (; u + 4 <= f.r; u += 4) {
             float4 d[4];

@@ -51,8 +51,12 @@ struct Epi {
                 if (p.bias) v += p.bias[n];
                 if (p.gate) v *= p.gate[(long)(row / p.ntok) * p.gate_ld + n];
                 const long idx = (long)row * p.d + n;
-                const float hn = p.h[idx] + v;
-                p.h[idx] = hn;
+                const float hn = (p.hin ? p.hin : p.h)[idx] + v;
+                if (!p.z) p.h[idx] = hn;
+                else {
+                    const int tok = row % p.ntok;
+                    if (tok >= p.r0 && tok < p.r1) p.z[idx] = p.alpha * p.z[idx] - p.beta * hn;
+                }
                 if (p.delta_mode == 1) p.delta[idx] = v;
                 else if (p.delta_mode == 2) p.delta[idx] = p.delta[idx] + v;
                 if (p.hcopy) ElemIO<OutT>::store((OutT*)p.hcopy + idx, hn);

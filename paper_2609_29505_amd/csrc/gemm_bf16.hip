@@ -412,7 +412,8 @@ __device__ __forceinline__ void epilogue(f32x16 (&acc)[C::TM][C::TN], const Gemm
                 }
         });
     } else {
-        // EP_RESID: v = (acc + bias) [* gate]; h += v; delta = v | delta += v; hcopy = bf16(h)
+        // EP_RESID: v = (acc + bias) [* gate]; h = hin + v; delta = v | delta += v; hcopy = bf16(h);
+        //           the last of a step: z <- alpha z - beta h in place of h's store
         // EP_SKIP:  h = acc + bias [+ cached delta]; hcopy = bf16(h)
         // EP_PARTIAL: part s = acc (+ bias in range 0), as EP_SKIP into h + s * part_stride
         // Lane pairs (V = 2) or quads (V = 1) exchange rows, so a lane handles four neighbouring
@@ -420,6 +421,7 @@ __device__ __forceinline__ void epilogue(f32x16 (&acc)[C::TM][C::TN], const Gemm
         const bool resid = ep.kind == EP_RESID;
         const bool rd_delta = resid ? ep.delta_mode == 2 : ep.kind == EP_SKIP && ep.delta_mode == 1;
         float* const hdst = ep.kind == EP_PARTIAL ? ep.h + (long)split * ep.part_stride : ep.h;
+        const float* const hsrc = ep.hin ? ep.hin : ep.h;
         groups([&](auto jc, auto vc, int n) {
             constexpr int J = decltype(jc)::value, V = decltype(vc)::value;
             constexpr int RL = V;                     // rows per lane and register group
@@ -435,14 +437,15 @@ __device__ __forceinline__ void epilogue(f32x16 (&acc)[C::TM][C::TN], const Gemm
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int q0 = 0; q0 < 4; q0 += QB) {
-                    f32x4 hv[QB][RL], dv[QB][RL], gt[QB][RL];
+                    f32x4 hv[QB][RL], dv[QB][RL], gt[QB][RL], zv[QB][RL];
 #pragma unroll
                     for (int q = 0; q < QB; ++q)
 #pragma unroll
                         for (int w = 0; w < RL; ++w) {
                             const int row = min(lane_row(i, q0 + q, w), g.M - 1);
                             const long idx = (long)row * ep.d + nl;
-                            hv[q][w] = resid ? *(const f32x4*)(ep.h + idx) : f32x4{0.f, 0.f, 0.f, 0.f};
+                            hv[q][w] = resid ? *(const f32x4*)(hsrc + idx) : f32x4{0.f, 0.f, 0.f, 0.f};
+                            zv[q][w] = ep.z ? *(const f32x4*)(ep.z + idx) : f32x4{0.f, 0.f, 0.f, 0.f};
                             dv[q][w] = rd_delta ? *(const f32x4*)(ep.delta + idx) : f32x4{0.f, 0.f, 0.f, 0.f};
                             gt[q][w] = ep.gate ? *(const f32x4*)(ep.gate + (long)sample_of(row) * ep.gate_ld + nl)
                                                : f32x4{1.f, 1.f, 1.f, 1.f};
@@ -481,7 +484,12 @@ __device__ __forceinline__ void epilogue(f32x16 (&acc)[C::TM][C::TN], const Gemm
                             if (ep.gate) xx = xx * gt[q][w];
                             const f32x4 dn = dv[q][w] + xx;
                             hn = resid ? hv[q][w] + xx : rd_delta ? dn : xx;
-                            *(f32x4*)(hdst + idx) = hn;
+                            if (!ep.z) {
+                                *(f32x4*)(hdst + idx) = hn;
+                            } else {
+                                const int tok = row - sample_of(row) * ep.ntok;
+                                if (tok >= ep.r0 && tok < ep.r1) *(f32x4*)(ep.z + idx) = zv[q][w] * ep.alpha - hn * ep.beta;
+                            }
                             if (resid && ep.delta_mode == 1) *(f32x4*)(ep.delta + idx) = xx;
                             if (resid && ep.delta_mode == 2) *(f32x4*)(ep.delta + idx) = dn;
                             if (ep.hcopy) {
@@ -1089,7 +1097,7 @@ bool gemm_bf16_shape_ok(const GemmArgs& g, const EpiParams& e, int tile) {
     // vector accesses of the loader and the epilogue: 16-byte operand rows and fp32 vectors,
     // 8-byte bf16 output groups
     if (!aligned(g.A0, 16) || !aligned(g.A1, 16) || !aligned(g.B, 16) || !aligned(e.bias, 16) ||
-        !aligned(e.gate, 16) || e.gate_ld % 4 || !aligned(e.h, 16) || !aligned(e.delta, 16) ||
+        !aligned(e.gate, 16) || e.gate_ld % 4 || !aligned(e.h, 16) || !aligned(e.hin, 16) || !aligned(e.z, 16) || !aligned(e.delta, 16) ||
         !aligned(e.out, 8) || !aligned(e.hcopy, 8) || !aligned(e.q, 8) || !aligned(e.k, 8) || !aligned(e.vt, 2))
         return false;
     const Shape s = tile_shape(tile);

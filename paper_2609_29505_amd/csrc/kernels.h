@@ -46,6 +46,11 @@ struct EpiParams {
     // (EP_SKIP: 1 = add the cached delta to the skip output); gate[b * gate_ld + n]
     float* h = nullptr; float* delta = nullptr; int delta_mode = 0;
     const float* gate = nullptr; long gate_ld = 0; void* hcopy = nullptr;
+    // EP_RESID: the stream is read from hin (NULL: h), the step's first residual projection from the
+    // state itself.  z != NULL: the last one of a step; instead of storing h it ends the step on the
+    // state, z <- alpha z - beta h on rows [r0, r1) of every sample (z may be hin)
+    const float* hin = nullptr; float* z = nullptr;
+    float alpha = 0.f, beta = 0.f; int r0 = 0, r1 = 0;
     // EP_ACT: per-sample additive bias rowbias[sample * rowbias_ld + n] (sample = row / ntok)
     const float* rowbias = nullptr; long rowbias_ld = 0;
     // EP_PARTIAL: K range s of a split product, fp32, to h + s * part_stride ([M x d]); the bias
@@ -83,13 +88,14 @@ constexpr int kMaxRun = 32;  // frozen units fused into one pass at most
 // kind 0: RMSNorm(w), 1: LayerNorm(w, b), 2: LayerNorm (no affine) * (1 + scale_b) + shift_b.
 // nfold > 0: x is the fp32 stream h of the rows and a run of frozen units ends here: the kernel
 // first forms h <- ((h + fold[0]) + fold[1]) + ... (the frozen-run update, same order), writes
-// it back to x, then normalises it.
+// it to xo, then normalises it.
 struct NormArgs {
     const float* x; void* y; int M, d, kind; float eps;
     const float* w; const float* b;
     const float* shift; const float* scale; long mod_ld; int ntok;
     int nfold = 0;
     const float* fold[kMaxRun] = {};
+    float* xo = nullptr;  // where the folded rows go (nfold > 0; may be x)
 };
 // parts: the fold holds the partial products of a split residual GEMM rather than a frozen
 // run's cached updates (the same additions, a kernel of its own name)
@@ -108,6 +114,7 @@ hipError_t launch_group_norm_silu(int in_bf16, const GroupNormArgs& a, void* scr
 // ---------------------------------------------------------------- elementwise
 struct FrozenRun {
     float* h; long n;  // elements
+    const float* src;  // the stream before the run (may be h)
     int r;
     int snap_bf16;  // snapshot dtype: 1 bf16, 0 fp32
     const float* delta[kMaxRun];

@@ -85,7 +85,7 @@ __device__ __forceinline__ void norm_body(const NormArgs& a) {
 #pragma unroll
         for (int i = 0; i < VPL; ++i) {
             const int c = t + i * TPR;
-            if (c < nvec) ((float4*)x)[c] = v[i];
+            if (c < nvec) ((float4*)(a.xo + (long)row * a.d))[c] = v[i];
         }
     }
     // every multiply-add below is an explicit fmaf (or an explicit plain product): the compiler
@@ -183,7 +183,7 @@ hipError_t launch_norm(int dtype, const NormArgs& a, hipStream_t st, bool parts)
     // few rows (LLaDA: 1024): four waves per row.  Many rows: two waves per row when the row's
     // float4 groups split evenly over 128 lanes (U-ViT, d = 1024: 13.9 -> 12.5 us), else one
     // (DiT d = 1152 and SDXL d = 1280 measured slower with two: uneven lanes)
-    if (parts && a.nfold < 1) return hipErrorInvalidValue;
+    if ((parts && a.nfold < 1) || (a.nfold > 0 && !a.xo)) return hipErrorInvalidValue;
     if (a.M < 4096) return launch_norm_wpr<4>(dtype, a, parts, st);
     return (a.d / 4) % 128 == 0 ? launch_norm_wpr<2>(dtype, a, parts, st) : launch_norm_wpr<1>(dtype, a, parts, st);
 }
