@@ -641,6 +641,115 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_kernel(AttnArgs a, float sca
         }
 }
 
+// The same for few queries, on v_mfma_f32_16x16x4_f32: a workgroup owns 16 queries and its eight
+// waves take alternate blocks of 32 keys, so 256 keys are one round of loads.  MFMA step t of a score
+// tile contracts dims (l / 16) HD + t (each lane reads one contiguous quarter of a K row and of its
+// query); lane l then holds query l % 16 and keys 4 (l / 16) + r, which is the B operand of the output
+// product's step r over V^T float4s.  The waves' states meet in LDS and each 16-dim block is merged and
+// stored by one wave, in wave order.
+template <int DHP>
+__global__ __launch_bounds__(512) void attn_f32_small_kernel(AttnArgs a, float scale_log2) {
+    constexpr int NW = 8, HD = DHP / 4, DB = DHP / 16;
+    __shared__ f32x4 so[NW][DB][64];
+    __shared__ float sm[NW][16], sl[NW][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = lane & 15, grp = lane >> 4;
+    const int bh = blockIdx.y, b = bh / a.H, hh = bh - b * a.H;
+    const int dh = a.dh;
+    const int q0 = blockIdx.x * 16;
+    const float* Q = (const float*)a.q + (long)bh * a.npq * dh;
+    const float* K = (const float*)a.k + (long)bh * a.npk * dh;
+    const float* VT = (const float*)a.vt + (long)bh * dh * a.npk;
+    const f32x4 zero{0.f, 0.f, 0.f, 0.f};
+    // dims grp * HD + t of the lane's query row (rows past nq read the last query; dims past dh are
+    // zero: dh % 8 == 0 and HD % 8 == 0, so a float4 group is wholly inside or outside)
+    f32x4 qv[HD / 4];
+    const float* qr = Q + (long)min(q0 + col, a.nq - 1) * dh + grp * HD;
+#pragma unroll
+    for (int t = 0; t < HD / 4; ++t) qv[t] = grp * HD + t * 4 < dh ? *(const f32x4*)(qr + t * 4) : zero;
+    f32x4 o[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) o[db] = zero;
+    float m = -INFINITY, l = 0.f;
+    const int nkb = (a.nk + 31) / 32;  // npk is a multiple of 64: whole blocks can be read
+    for (int kb = wave; kb < nkb; kb += NW) {
+        f32x4 sc[2], vv[2][DB];
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const int k0 = kb * 32 + x * 16;
+            const float* kr = K + (long)(k0 + col) * dh + grp * HD;
+            f32x4 kv[HD / 4];
+#pragma unroll
+            for (int t = 0; t < HD / 4; ++t) kv[t] = grp * HD + t * 4 < dh ? *(const f32x4*)(kr + t * 4) : zero;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                const int dim = db * 16 + col;
+                vv[x][db] = dim < dh ? *(const f32x4*)(VT + (long)dim * a.npk + k0 + grp * 4) : zero;
+            }
+            sc[x] = zero;
+#pragma unroll
+            for (int t = 0; t < HD / 4; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sc[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[t][e], qv[t][e], sc[x], 0, 0, 0);
+        }
+        float bm = -INFINITY;
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                sc[x][r] = kb * 32 + x * 16 + grp * 4 + r < a.nk ? sc[x][r] * scale_log2 : -INFINITY;
+                bm = fmaxf(bm, sc[x][r]);
+            }
+        bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
+        bm = fmaxf(bm, __shfl_xor(bm, 32, 64));  // key 0 of the block is valid: bm is finite
+        const float mn = fmaxf(m, bm);
+        const float alpha = __builtin_amdgcn_exp2f(m - mn);
+        m = mn;
+        l *= alpha;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) o[db] = o[db] * alpha;
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float p = __builtin_amdgcn_exp2f(sc[x][r] - mn);
+                l += p;
+                // masked keys have p = 0, but their V^T entries may be any value (NaN included)
+                const bool in = kb * 32 + x * 16 + grp * 4 + r < a.nk;
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+                    o[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? vv[x][db][r] : 0.f, p, o[db], 0, 0, 0);
+            }
+    }
+#pragma unroll
+    for (int db = 0; db < DB; ++db) so[wave][db][lane] = o[db];
+    if (grp == 0) sm[wave][col] = m;
+    sl[wave][lane] = l;
+    __syncthreads();
+    if (wave >= DB) return;
+    float mn = sm[0][col];  // wave 0 holds key block 0: finite
+#pragma unroll
+    for (int w = 1; w < NW; ++w) mn = fmaxf(mn, sm[w][col]);
+    float aw[NW], lt = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        aw[w] = __builtin_amdgcn_exp2f(sm[w][col] - mn);  // a wave without keys: m = -inf, weight 0
+        lt += aw[w] * sl[w][lane];
+    }
+    lt += __shfl_xor(lt, 16, 64);
+    lt += __shfl_xor(lt, 32, 64);
+    const float inv = 1.0f / lt;
+    if (q0 + col >= a.nq) return;
+    float* O = (float*)a.o + ((long)b * a.nq + q0 + col) * ((long)a.H * dh) + (long)hh * dh;
+    for (int db = wave; db < DB; db += NW) {
+        const int d0 = db * 16 + grp * 4;
+        f32x4 t = so[0][db][lane] * aw[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) t = t + so[w][db][lane] * aw[w];
+        if (d0 < dh) *(f32x4*)(O + d0) = t * inv;
+    }
+}
+
 // bf16 launch for one head dim (every loader index and padding bound a compile-time constant)
 template <int DH>
 static void launch_attention_bf16(const AttnArgs& a, hipStream_t st) {
@@ -648,9 +757,17 @@ static void launch_attention_bf16(const AttnArgs& a, hipStream_t st) {
     const float sl2 = (float)(1.4426950408889634 / sqrt((double)DH));
     const long qg128 = (long)((a.nq + 127) / 128) * BH;  // 128-query workgroups
     const int nkb = (a.nk + 63) / 64;
-    if (nkb >= 8 && qg128 < 1024) {
-        // long key range, few query groups: split the keys between two wave halves
-        if (qg128 >= 256)
+    // Few query groups and more than one key block: split the keys between two wave halves.  The split
+    // kernel's LDS (two buffers per half) lets one workgroup of head dims above 64 onto a CU, two of
+    // smaller ones: 64-query workgroups where they are one round of the CUs, else 128-query ones (dh 128,
+    // 24 heads of 1024 keys: 23.6 us against 41.7; dh 72, 384 groups of 256 keys: 15.3 against 20.4).
+    // Small heads with short key ranges gain only in the first case (dh 64, 256 keys: 160 groups 7.4 us
+    // against 11.0 unsplit; 640 groups of 1024 queries and 77 keys 17.3 against 16.4), long key ranges
+    // always.
+    constexpr bool wide = DH > 64;
+    const bool round64 = (long)((a.nq + 63) / 64) * BH <= (wide ? 256 : 512);
+    if (qg128 < 1024 && nkb >= 2 && (nkb >= 8 || wide || round64)) {
+        if (wide ? !round64 : qg128 >= 256)
             hipLaunchKernelGGL((attn_split_bf16_kernel<DH, 4>), dim3((a.nq + 127) / 128, BH), dim3(512), 0, st, a, sl2);
         else
             hipLaunchKernelGGL((attn_split_bf16_kernel<DH, 2>), dim3((a.nq + 63) / 64, BH), dim3(256), 0, st, a, sl2);
@@ -687,6 +804,16 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t st) {
     } else {
         const float sl2 = (float)(1.4426950408889634 / sqrt((double)a.dh));
         dim3 grid((a.nq + 31) / 32, BH), block(4 * 64);
+        // 16-query workgroups while the 32-query ones are few (32 of them, 256 keys, dh 64: 8.2 us
+        // against 12.3; 312: 26.6 against 29.5; 512: 33.6 against 27.4)
+        if ((long)grid.x * BH <= 320) {
+            grid.x = (a.nq + 15) / 16;
+            if (a.dh <= 32) hipLaunchKernelGGL(attn_f32_small_kernel<32>, grid, dim3(512), 0, st, a, sl2);
+            else if (a.dh <= 64) hipLaunchKernelGGL(attn_f32_small_kernel<64>, grid, dim3(512), 0, st, a, sl2);
+            else if (a.dh <= 96) hipLaunchKernelGGL(attn_f32_small_kernel<96>, grid, dim3(512), 0, st, a, sl2);
+            else hipLaunchKernelGGL(attn_f32_small_kernel<128>, grid, dim3(512), 0, st, a, sl2);
+            return hipGetLastError();
+        }
         if (a.dh <= 32) hipLaunchKernelGGL((attn_f32_kernel<32, 4>), grid, block, 0, st, a, sl2);
         else if (a.dh <= 64) hipLaunchKernelGGL((attn_f32_kernel<64, 4>), grid, block, 0, st, a, sl2);
         else if (a.dh <= 96) hipLaunchKernelGGL((attn_f32_kernel<96, 4>), grid, block, 0, st, a, sl2);

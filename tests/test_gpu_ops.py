@@ -487,3 +487,15 @@ def test_small_products_bf16(P, M, N, K):
     th, td = dev(h0), dev(np.zeros_like(h0))
     P.op_residual(dev(A), dev(W), th, bias=dev(b), delta=td, delta_mode=1)
     assert relmax(host(td), z) <= 1e-5 and relmax(host(th), h0 + z) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,H,nq,nk,dh", [(1, 1, 1, 65, 8), (1, 3, 17, 31, 40), (2, 2, 200, 129, 96),
+                                          (1, 2, 100, 300, 104),
+                                          # last of the 64-query split grids and the first past them
+                                          (2, 64, 128, 128, 72), (2, 43, 130, 130, 72), (8, 16, 200, 100, 64),
+                                          (2, 43, 180, 70, 64),
+                                          # last of the fp32 16-query grids and the first past them
+                                          (2, 32, 160, 96, 32), (1, 107, 90, 200, 24)])
+def test_attention_few_queries(P, dtype, B, H, nq, nk, dh):
+    test_attention(P, dtype, B, H, nq, nk, dh)
