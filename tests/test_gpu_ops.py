@@ -499,3 +499,21 @@ def test_small_products_bf16(P, M, N, K):
                                           (2, 32, 160, 96, 32), (1, 107, 90, 200, 24)])
 def test_attention_few_queries(P, dtype, B, H, nq, nk, dh):
     test_attention(P, dtype, B, H, nq, nk, dh)
+
+
+# 16 x 16 tiles (up to 128 tiles of 32 x 32), 32 x 32 tiles with eight and sixteen waves; K of fewer
+# units than waves, ragged K passes and rows
+@pytest.mark.parametrize("M,N,K", [(1, 64, 16), (33, 128, 80), (255, 512, 272), (250, 512, 1040), (260, 512, 48),
+                                   (257, 1024, 2064), (31, 8256, 144)])
+def test_small_products_f32(P, M, N, K):
+    rng = np.random.default_rng(M + N + K)
+    A = rng.standard_normal((M, K)).astype(np.float32)
+    W = (rng.standard_normal((N, K)) / np.sqrt(K)).astype(np.float32)
+    b = (0.1 * rng.standard_normal(N)).astype(np.float32)
+    h0 = rng.standard_normal((M, N)).astype(np.float32)
+    z = A.astype(np.float64) @ W.astype(np.float64).T + b
+    th, out = dev(h0), empty((M, N), "f32")
+    P.op_residual(dev(A), dev(W), th, bias=dev(b))
+    P.op_linear(dev(A), dev(W), out, bias=dev(b), act=3)
+    assert relmax(host(th), h0 + z) <= 1e-5
+    assert relmax(host(out), om.silu(z)) <= 1e-5
