@@ -194,7 +194,7 @@ int sgd_budget_layer_steps(int32_t pct, int32_t L, int32_t T, int64_t* n_star);
 int sgd_schedule_workspace_bytes(const sgd_unit* units, int32_t L, int32_t workers, size_t* bytes);
 
 /* Alg. 1: score every matrix of every unit on the GPU (fp64 Gram of the short side,
- * Householder tridiagonalisation, the k largest eigenvalues by bisection), then set lifetimes.
+ * Householder tridiagonalisation, its eigenvalues by bisection), then set lifetimes.
  * Offline, once per model.  As many matrices are scored at once as the workspace holds, in
  * batches on hip_stream; the workspace must hold at least one.  units may be NULL for SGD_RULE_DEPTH and SGD_RULE_RANDOM (then L
  * alone sizes the schedule and nothing runs on the GPU).  Synchronises hip_stream before

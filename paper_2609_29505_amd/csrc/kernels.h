@@ -160,7 +160,7 @@ hipError_t launch_sumsq_finish(const double* partial, int count, double* out, hi
 
 // ---------------------------------------------------------------- spectra (fp64)
 // One scored matrix of a batch: X rows x cols; its Gram matrix is X^T X (trans = 0, n = cols) or
-// X X^T (trans = 1, n = rows); k eigenvalues are wanted; tile0 is the first of its tiles in the
+// X X^T (trans = 1, n = rows); k is the spectral rank of its score; tile0 is the first of its tiles in the
 // Gram launch.
 struct SpectralJob {
     const void* X;
@@ -183,7 +183,7 @@ struct SpectralBatch {
 __host__ __device__ inline int spectral_lda(int n) { return (n + 1) & ~1; }
 // largest short side whose three work vectors fit the LDS (160 KB); a batch lies on one side of it
 constexpr int kSpectralMax = 6600;
-// Gram matrices, tridiagonal forms and largest eigenvalues of a batch (host_jobs: the host's copy of
+// Gram matrices, tridiagonal forms and eigenvalues of a batch (host_jobs: the host's copy of
 // sb.jobs)
 hipError_t launch_spectra(const SpectralBatch& sb, const SpectralJob* host_jobs, hipStream_t st);
 

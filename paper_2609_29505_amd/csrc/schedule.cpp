@@ -1,7 +1,7 @@
 // Schedule construction (Alg. 1, Sec. 4.1) behind sgd_schedule_build.
 //
 // Per scored matrix W (m x n, d = min(m, n)), all on the GPU and for many matrices at once: the
-// fp64 Gram matrix of the short side, its Householder tridiagonal form and the k largest
+// fp64 Gram matrix of the short side, its Householder tridiagonal form and the
 // eigenvalues of that form by bisection.  They are squared singular values sigma_i^2, from which
 //   E_k = sum_{i<=k} sigma_i^2, k = min(d, max(1, floor(d/10)))
 //   SCR_eta = log((E_k + eta F) / (tail + eta F)), F = ||W||_F^2 = trace of the Gram
@@ -32,16 +32,14 @@ static int rank_k(long m, long n) {
     return (int)std::min<long>(d, std::max<long>(1, d / 10));
 }
 
-// Statistics from the tridiagonal form's diagonal and its k largest eigenvalues (descending): the
-// tail energy is what they leave of its trace (nothing when they are all of the eigenvalues), summed
-// in extended precision, so that it carries the roundings of the eigenvalues and none of the sums.
-static MatStats stats_from_eigs(const double* diag, const double* lam, double frob, int k, int n, double eta) {
+// Statistics from the eigenvalues (descending), summed in extended precision.
+static MatStats stats_from_eigs(const double* lam, double frob, int k, int n, double eta) {
     MatStats s;
-    long double top = 0.0L, trace = 0.0L;
+    long double top = 0.0L, tail = 0.0L;
     for (int i = 0; i < k; ++i) top += std::max(lam[i], 0.0);
-    for (int i = 0; i < n; ++i) trace += diag[i];
+    for (int i = n - 1; i >= k; --i) tail += std::max(lam[i], 0.0);
     s.e_top = (double)top;
-    s.e_tail = k < n ? std::max((double)(trace - top), 0.0) : 0.0;
+    s.e_tail = (double)tail;
     s.frob = frob;
     const double A = s.e_top + eta * frob, B = s.e_tail + eta * frob;
     s.scr = B > 0 ? std::log(A / B) : std::numeric_limits<double>::infinity();
@@ -135,9 +133,9 @@ static int run_stats(std::vector<MatJob>& jobs, double eta, char* ws, size_t ws_
             for (int i = 0; i < n; ++i) frob += o[2 * nmax + i];
             bool finite = std::isfinite(frob);
             for (int i = 0; i < n; ++i) finite = finite && std::isfinite(o[i]) && (i + 1 >= n || std::isfinite(o[nmax + i]));
-            for (int i = 0; i < k; ++i) finite = finite && std::isfinite(o[3 * nmax + i]);
+            for (int i = 0; i < n; ++i) finite = finite && std::isfinite(o[3 * nmax + i]);
             if (!finite) return fail(SGD_E_NUMERIC, "non-finite weights in a scored matrix");
-            jobs[order[done + b]].out = stats_from_eigs(o, o + 3 * nmax, frob, k, n, eta);
+            jobs[order[done + b]].out = stats_from_eigs(o + 3 * nmax, frob, k, n, eta);
         }
         done += count;
     }

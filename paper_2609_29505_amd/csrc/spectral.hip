@@ -1,6 +1,6 @@
 // Offline spectra of the scored weight matrices (fp64): the Gram matrix of the short side, a
-// Householder reduction of that symmetric matrix to tridiagonal form and the largest eigenvalues
-// of that form, the squared singular values the spectral concentration ratio needs.
+// Householder reduction of that symmetric matrix to tridiagonal form and the eigenvalues of that
+// form, the squared singular values the spectral concentration ratio needs.
 #include <algorithm>
 
 #include "common.h"
@@ -12,13 +12,20 @@ namespace sgd {
 // G[i][j] = sum_t E(t, i) E(t, j) with E(t, i) = X[t][i] (trans = 0) or X[i][t] (trans = 1), for
 // every matrix of a batch in one launch.  64 x 64 output tiles on and below the diagonal; each is
 // mirrored on store, rows are lda = n rounded up to even apart, and the padding column is zero.
-template <typename T>
-__device__ __forceinline__ double ld64(const T* p) { return (double)ElemIO<T>::load(p); }
+//
+// On the matrix cores (v_mfma_f64_16x16x4_f64: lane l holds row l % 16 and k = l / 16 of either operand,
+// and of the product column l % 16 and row 4 r + l / 16 in register r): the same fp64 products and
+// sums at the same peak rate as vector FMAs, but a wave's 32 x 32 tile reads 4 values a lane from the
+// LDS for 4096 FMAs; a 4 x 4 patch a thread read 8 for 1024 and was bound by the LDS.  The next k chunk
+// is on its way while one is multiplied.  24 fp32 matrices of 256 x 256 to 1024 x 256 264 -> 85 us; bf16
+// 4 of 1152 x 1152 and 2 of 4608 x 1152 1401 -> 681 us.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kGramKB = 16, kGramLD = 66;  // k depth of a chunk; LDS row pitch (rows 16 bytes apart in the banks)
 
 template <typename T>
-__device__ __forceinline__ void gram_tile(const SpectralJob& jb, double* G, int idx, double (*si)[65], double (*sj)[65],
-                                          double (&acc)[4][4], int& i0, int& j0) {
-    constexpr int TB = 64, KB = 16;
+__device__ __forceinline__ void gram_tile(const SpectralJob& jb, int idx, double (*si)[kGramLD], double (*sj)[kGramLD],
+                                          f64x4 (&acc)[2][2], int& i0, int& j0) {
+    constexpr int TB = 64, KB = kGramKB, E = KB * TB / 256;
     const T* X = (const T*)jb.X;
     int ti = 0;  // lower-triangle tile index -> (ti, tj), tj <= ti
     while (idx >= ti + 1) { idx -= ti + 1; ++ti; }
@@ -26,67 +33,90 @@ __device__ __forceinline__ void gram_tile(const SpectralJob& jb, double* G, int 
     j0 = idx * TB;
     const long cols = jb.cols, tlen = jb.trans ? cols : jb.rows;
     const int n = jb.n, trans = jb.trans;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    for (long t0 = 0; t0 < tlen; t0 += KB) {
-        __syncthreads();
-        for (int e = tid; e < KB * TB; e += 256) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wi = (wave >> 1) * 32, wj = (wave & 1) * 32, fr = lane & 15, fk = lane >> 4;
+    // consecutive threads walk X's contiguous dimension
+    auto place = [&](int u, int& kk, int& c) {
+        const int e = tid + u * 256;
+        if (trans) { c = e / KB; kk = e % KB; }
+        else { kk = e / TB; c = e % TB; }
+    };
+    T ri[E], rj[E];
+    auto load = [&](long t0) {
+#pragma unroll
+        for (int u = 0; u < E; ++u) {
             int kk, c;
-            if (trans) { c = e / KB; kk = e % KB; }  // consecutive threads walk t (contiguous in X)
-            else { kk = e / TB; c = e % TB; }       // consecutive threads walk i (contiguous in X)
+            place(u, kk, c);
             const long t = t0 + kk;
             const int gi = i0 + c, gj = j0 + c;
-            double vi = 0.0, vj = 0.0;
-            if (t < tlen) {
-                if (gi < n) vi = trans ? ld64(X + (long)gi * cols + t) : ld64(X + t * cols + gi);
-                if (gj < n) vj = trans ? ld64(X + (long)gj * cols + t) : ld64(X + t * cols + gj);
-            }
-            si[kk][c] = vi;
-            sj[kk][c] = vj;
+            ri[u] = t < tlen && gi < n ? X[trans ? (long)gi * cols + t : t * cols + gi] : T(0.f);
+            rj[u] = t < tlen && gj < n ? X[trans ? (long)gj * cols + t : t * cols + gj] : T(0.f);
         }
+    };
+    load(0);
+    for (long t0 = 0; t0 < tlen; t0 += KB) {
         __syncthreads();
 #pragma unroll
-        for (int kk = 0; kk < KB; ++kk) {
-            double a[4], b[4];
+        for (int u = 0; u < E; ++u) {
+            int kk, c;
+            place(u, kk, c);
+            si[kk][c] = (double)ElemIO<T>::load(&ri[u]);
+            sj[kk][c] = (double)ElemIO<T>::load(&rj[u]);
+        }
+        __syncthreads();
+        if (t0 + KB < tlen) load(t0 + KB);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) a[r] = si[kk][ty + 16 * r];
+        for (int k = 0; k < KB; k += 4) {
+            double a[2], b[2];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) b[c] = sj[kk][tx + 16 * c];
+            for (int x = 0; x < 2; ++x) {
+                a[x] = si[k + fk][wi + x * 16 + fr];
+                b[x] = sj[k + fk][wj + x * 16 + fr];
+            }
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
+            for (int x = 0; x < 2; ++x)
 #pragma unroll
-                for (int c = 0; c < 4; ++c) acc[r][c] = fma(a[r], b[c], acc[r][c]);
+                for (int y = 0; y < 2; ++y) acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[x], b[y], acc[x][y], 0, 0, 0);
         }
     }
 }
 
 __global__ __launch_bounds__(256) void gram_kernel(SpectralBatch sb) {
-    __shared__ double si[16][65];
-    __shared__ double sj[16][65];
+    __shared__ double si[kGramKB][kGramLD];
+    __shared__ double sj[kGramKB][kGramLD];
     const int bi = blockIdx.x, tid = threadIdx.x;
     int b = 0;
     while (b + 1 < sb.count && sb.jobs[b + 1].tile0 <= bi) ++b;
     const SpectralJob jb = sb.jobs[b];
     double* G = sb.gram(b);
-    double acc[4][4] = {};
+    f64x4 acc[2][2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
     int i0, j0;
-    if (jb.dtype == 1) gram_tile<bf16>(jb, G, bi - jb.tile0, si, sj, acc, i0, j0);
-    else gram_tile<float>(jb, G, bi - jb.tile0, si, sj, acc, i0, j0);
-    const int n = jb.n, lda = spectral_lda(n), tx = tid & 15, ty = tid >> 4;
+    if (jb.dtype == 1) gram_tile<bf16>(jb, bi - jb.tile0, si, sj, acc, i0, j0);
+    else gram_tile<float>(jb, bi - jb.tile0, si, sj, acc, i0, j0);
+    const int n = jb.n, lda = spectral_lda(n), lane = tid & 63, wave = tid >> 6;
     double* trace = sb.out(b) + 2 * (long)sb.nmax;
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int x = 0; x < 2; ++x)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int gi = i0 + ty + 16 * r, gj = j0 + tx + 16 * c;
-            if (gi < n && gj < n) {
-                G[(long)gi * lda + gj] = acc[r][c];
-                G[(long)gj * lda + gi] = acc[r][c];
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int gi = i0 + (wave >> 1) * 32 + x * 16 + 4 * r + (lane >> 4);
+                const int gj = j0 + (wave & 1) * 32 + y * 16 + (lane & 15);
+                // a diagonal tile stores its lower half both ways, so that the matrix is symmetric
+                if (gi >= n || gj >= n || gj > gi) continue;
+                const double v = acc[x][y][r];
+                G[(long)gi * lda + gj] = v;
+                G[(long)gj * lda + gi] = v;
                 if (gi == gj) {
-                    trace[gi] = acc[r][c];
+                    trace[gi] = v;
                     if (lda > n) G[(long)gi * lda + n] = 0.0;
                 }
             }
-        }
 }
 
 // ---------------------------------------------------------------------------- tridiagonal
@@ -102,9 +132,39 @@ __global__ __launch_bounds__(256) void gram_kernel(SpectralBatch sb) {
 // of its own, took 4-5 us each and were bound by the launches (24 matrices of 256 x 256 to
 // 1024 x 256: 21.3 ms; 4 of 1152 x 1152 and 2 of 4608 x 1152: 62.9 ms, both with the host's QR).
 
+// x of the lane that the DPP control CTRL names
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = __builtin_amdgcn_mov_dpp((uint32_t)u, CTRL, 0xF, 0xF, true);
+    const uint32_t hi = __builtin_amdgcn_mov_dpp((uint32_t)(u >> 32), CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+// x + x of lane ^ 16 / ^ 32 (register swaps between rows of 16 and halves of the wave)
+__device__ __forceinline__ double add_xor16(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const auto a = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+    return __builtin_bit_cast(double, (uint64_t)b[0] << 32 | a[0]) + __builtin_bit_cast(double, (uint64_t)b[1] << 32 | a[1]);
+}
+__device__ __forceinline__ double add_xor32(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const auto a = __builtin_amdgcn_permlane32_swap((uint32_t)u, (uint32_t)u, false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+    return __builtin_bit_cast(double, (uint64_t)b[0] << 32 | a[0]) + __builtin_bit_cast(double, (uint64_t)b[1] << 32 | a[1]);
+}
+// sum over the wave in every lane, without the LDS round trips of a shuffle (a step is a chain of sums)
+__device__ __forceinline__ double wave_sum_d(double x) {
+    x += dpp_d<0xB1>(x);   // lane ^ 1
+    x += dpp_d<0x4E>(x);   // lane ^ 2
+    x += dpp_d<0x141>(x);  // the other quad of eight lanes
+    x += dpp_d<0x140>(x);  // the other eight lanes of sixteen
+    return add_xor32(add_xor16(x));
+}
+
 // sum over the workgroup through red (one double per wave, used once per call)
 __device__ __forceinline__ double block_sum_d(double v, double* red) {
-    v = warp_sum(v);
+    v = wave_sum_d(v);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     if (lane == 0) red[w] = v;
     __syncthreads();
@@ -115,6 +175,10 @@ __device__ __forceinline__ double block_sum_d(double v, double* red) {
 }
 
 constexpr int kTriThreads = 256, kTriRows = 16;  // rows per workgroup pass: four per wave
+// The last trailing block, of up to kTail rows, fits one CU's registers and is reduced by tri_tail_kernel:
+// from step tail_step(n) on
+constexpr int kTail = 192;
+__host__ __device__ inline int tail_step(int n) { return n - 1 > kTail ? n - 1 - kTail : 0; }
 
 // FIRST: the reflector of column 0 and its p (no update).  Otherwise step j: consumes v_j, p_j,
 // tau_j and leaves v_{j+1}, p_{j+1}, tau_{j+1} (ping-pong buffers: other workgroups of the launch
@@ -132,7 +196,7 @@ __global__ __launch_bounds__(kTriThreads) void tri_step_kernel(SpectralBatch sb,
         }
         return;
     }
-    if (!FIRST && j > n - 3) return;
+    if (!FIRST && j >= tail_step(n)) return;
     const int lda = spectral_lda(n);
     double* A = sb.gram(b);
     double *diag = sb.out(b), *offd = diag + sb.nmax;
@@ -189,15 +253,6 @@ __global__ __launch_bounds__(kTriThreads) void tri_step_kernel(SpectralBatch sb,
         k = 0.5 * tau * (block_sum_d(s, red) + p0);
         w0 = p0 - k;
         alpha = alpha - v1 * w0 - (p1 - k * v1);
-        if (m == 2) {
-            // last step: the trailing 2 x 2 block after its update is the end of T
-            if (blockIdx.x == 0 && tid == 0) {
-                diag[j + 1] = arow[0] - 2.0 * w0;
-                offd[j + 1] = alpha;
-                diag[j + 2] = A[(long)(j + 2) * lda + (j + 2)] - 2.0 * v1 * (p1 - k * v1);
-            }
-            return;
-        }
     }
     // w, the updated column 0 below the diagonal, x[i] = A22[1+i][0] - v[1+i] w[0] - w[1+i] v[0], and its
     // reflector (x[0] is alpha)
@@ -283,9 +338,143 @@ __global__ __launch_bounds__(kTriThreads) void tri_step_kernel(SpectralBatch sb,
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const double t = warp_sum(acc[r]);
+            const double t = wave_sum_d(acc[r]);
             if (lane == 0 && i0 + r < m) pn[i0 + r - 1] = taun * t;
         }
+    }
+}
+
+// The last steps, from tail_step(n) on: the trailing block stays in the registers of one workgroup
+// (thread (ty, tx) of 16 x 32 owns rows ty + 16 a and columns tx + 32 c, so work shrinks evenly as rows
+// and columns are finished) and the vectors in LDS, two barriers a step.  A step takes 2.8 us (two wave
+// sums, a square root and two divisions in sequence) instead of the 5.4-6 us that a launch and its round
+// trips through L2 take at these sizes: the last 192 of 256 steps 1100 -> 540 us.
+constexpr int kTailTY = 16, kTailTX = 32, kTailA = kTail / kTailTY, kTailC = kTail / kTailTX;
+__global__ __launch_bounds__(kTailTY * kTailTX) void tri_tail_kernel(SpectralBatch sb) {
+    __shared__ double sv[kTail], sp[kTail], sx[kTail], sy[kTail];
+    static_assert(kTail % 64 == 0 && kTailA % 4 == 0, "tail shape");
+    const int b = blockIdx.x, n = sb.jobs[b].n, tid = threadIdx.x, lane = tid & 63;
+    if (n < 3) return;  // the first launch has written T
+    const int tx = tid & (kTailTX - 1), ty = tid / kTailTX;
+    const int js = tail_step(n), m0 = n - js - 1, lda = spectral_lda(n);
+    const double* A = sb.gram(b) + (long)(js + 1) * lda + (js + 1);
+    double *diag = sb.out(b) + js + 1, *offd = diag + sb.nmax;
+    const double* work = sb.work(b);
+    // rows, columns and vector entries past the block are zero and stay zero
+    double acc[kTailA][kTailC];
+#pragma unroll
+    for (int a = 0; a < kTailA; ++a)
+#pragma unroll
+        for (int c = 0; c < kTailC; ++c) {
+            const int i = ty + kTailTY * a, k = tx + kTailTX * c;
+            const double x = A[(long)min(i, m0 - 1) * lda + min(k, m0 - 1)];
+            acc[a][c] = max(i, k) < m0 ? x : 0.0;
+        }
+    for (int i = tid; i < kTail; i += kTailTY * kTailTX) {
+        sv[i] = i < m0 ? work[(long)(js & 1) * sb.nmax + i] : 0.0;
+        sp[i] = i < m0 ? work[(long)(2 + (js & 1)) * sb.nmax + i] : 0.0;
+    }
+    double tau = work[4 * (long)sb.nmax + (js & 1)];
+    __syncthreads();
+    for (int o = 0;; ++o) {  // the block's first row; v, p are zero before it
+        // w = p - (tau / 2) (p . v) v and A -= v w^T + w v^T
+        double s = 0.0;
+#pragma unroll
+        for (int u = 0; u < kTail / 64; ++u) s += sp[lane + 64 * u] * sv[lane + 64 * u];
+        const double k = 0.5 * tau * wave_sum_d(s);
+        {
+            double vc[kTailC], wc[kTailC];
+#pragma unroll
+            for (int c = 0; c < kTailC; ++c) {
+                vc[c] = sv[tx + kTailTX * c];
+                wc[c] = sp[tx + kTailTX * c] - k * vc[c];
+            }
+#pragma unroll
+            for (int a = 0; a < kTailA; ++a) {
+                if (kTailTY * (a + 1) <= o || kTailTY * a >= m0) continue;  // finished or past the block
+                const double vr = sv[ty + kTailTY * a], wr = sp[ty + kTailTY * a] - k * vr;
+#pragma unroll
+                for (int c = 0; c < kTailC; ++c) acc[a][c] -= vr * wc[c] + wr * vc[c];
+            }
+        }
+        // column o
+#pragma unroll
+        for (int c = 0; c < kTailC; ++c)
+            if (c == o / kTailTX && tx == o % kTailTX)
+#pragma unroll
+                for (int a = 0; a < kTailA; ++a) sx[ty + kTailTY * a] = acc[a][c];
+        const bool last = m0 - o == 2;  // the trailing 2 x 2 block is the end of T
+        if (last) {
+#pragma unroll
+            for (int c = 0; c < kTailC; ++c)
+                if (c == (o + 1) / kTailTX && tx == (o + 1) % kTailTX)
+#pragma unroll
+                    for (int a = 0; a < kTailA; ++a) sy[ty + kTailTY * a] = acc[a][c];
+        }
+        __syncthreads();
+        const double alpha = sx[o + 1];
+        if (last) {
+            if (tid == 0) {
+                diag[o] = sx[o];
+                offd[o] = alpha;
+                diag[o + 1] = sy[o + 1];
+            }
+            return;
+        }
+        // the reflector of column o below the diagonal
+        s = 0.0;
+#pragma unroll
+        for (int u = 0; u < kTail / 64; ++u) {
+            const int i = lane + 64 * u;
+            const double x = sx[i];
+            if (i > o + 1) s += x * x;
+        }
+        const double sigma = wave_sum_d(s);
+        double beta = alpha, scale = 0.0;
+        tau = 0.0;
+        if (sigma != 0.0) {
+            const double mu = sqrt(alpha * alpha + sigma);
+            beta = alpha <= 0.0 ? mu : -mu;
+            tau = (beta - alpha) / beta;
+            scale = 1.0 / (alpha - beta);
+        }
+        auto v_at = [&](int i) { return i > o + 1 ? sx[i] * scale : i == o + 1 ? 1.0 : 0.0; };
+        if (tid == 0) {
+            diag[o] = sx[o];
+            offd[o] = beta;
+        }
+        if (tid < kTail) sv[tid] = v_at(tid);
+        // p = tau A v
+        double p[kTailA];
+        {
+            double vc[kTailC];
+#pragma unroll
+            for (int c = 0; c < kTailC; ++c) vc[c] = v_at(tx + kTailTX * c);
+#pragma unroll
+            for (int a = 0; a < kTailA; ++a) {
+                p[a] = 0.0;
+                if (kTailTY * (a + 1) <= o || kTailTY * a >= m0) continue;
+#pragma unroll
+                for (int c = 0; c < kTailC; ++c) p[a] += acc[a][c] * vc[c];
+            }
+        }
+        // row sums over the 32 lanes of a row: lanes exchange halves of their rows twice, after which
+        // lane tx holds the quad's sums of rows 4 g + tx % 4, then add over the eight quads
+        const bool o1 = tx & 1, o2 = tx & 2;
+#pragma unroll
+        for (int g = 0; g < kTailA / 4; ++g) {
+            double u0 = o1 ? p[4 * g + 1] : p[4 * g], u1 = o1 ? p[4 * g + 3] : p[4 * g + 2];
+            u0 += dpp_d<0xB1>(o1 ? p[4 * g] : p[4 * g + 1]);
+            u1 += dpp_d<0xB1>(o1 ? p[4 * g + 2] : p[4 * g + 3]);
+            double t = o2 ? u1 : u0;
+            t += dpp_d<0x4E>(o2 ? u0 : u1);
+            t += dpp_d<0x128>(t);  // eight lanes on
+            t += dpp_d<0x124>(t);  // four lanes on
+            t = add_xor16(t);
+            const int i = ty + kTailTY * (4 * g + tx);
+            if (tx < 4) sp[i] = i > o ? tau * t : 0.0;
+        }
+        __syncthreads();
     }
 }
 
@@ -418,26 +607,28 @@ static void tridiagonalize_large(const SpectralBatch& sb, int b, int n, hipStrea
     }
 }
 
-// The largest eigenvalues of each tridiagonal matrix, by bisection on the count of negative pivots
-// of T - x I (Golub & Van Loan, Sec. 8.4.1): eigenvalue i < k_b of matrix b per wave.  The 64 lanes
-// evaluate 64 points of the current interval at once, so ten passes shrink it by 65^10 > 2^60.
-// Only the top k = n / 10 are needed (the tail is the trace minus them); the host's QR over all of
-// them took longer than the reduction.
+// The eigenvalues of each tridiagonal matrix, by bisection on the number of sign changes in the
+// sequence of leading principal minors of T - x I (Golub & Van Loan, Sec. 8.4.1), p_i = (d_i - x) p_{i-1} -
+// e_{i-1}^2 p_{i-2}: sixteen lanes per eigenvalue evaluate sixteen points of its interval at once, so sixteen
+// passes shrink it by 17^16 > 2^65.  All of them are found, not the largest k alone: the tail energy is
+// then a sum of small values, where the trace minus the k largest leaves their roundings behind.
+// A step of the sequence is one dependent fma (the quotient of neighbouring minors instead, with its
+// reciprocal, took 115 cycles); the pair is scaled back every eight steps, T is scaled to norm one by a
+// power of two.
 constexpr int kSturmChunk = 1024;
 __global__ __launch_bounds__(256) void sturm_kernel(SpectralBatch sb) {
     __shared__ __attribute__((aligned(16))) double2 de[kSturmChunk];  // diagonal, squared off-diagonal above it
     __shared__ double red[8];
-    const int b = blockIdx.y, n = sb.jobs[b].n, kb = sb.jobs[b].k, tid = threadIdx.x, lane = tid & 63;
-    if ((int)blockIdx.x * 4 >= kb) return;
-    const int i = blockIdx.x * 4 + (tid >> 6);  // i-th largest (past kb: computed, not stored)
+    const int b = blockIdx.y, n = sb.jobs[b].n, tid = threadIdx.x, lane = tid & 63;
+    if ((int)blockIdx.x * 16 >= n) return;
+    const int i = blockIdx.x * 16 + (tid >> 4);  // i-th largest (past n: computed, not stored)
     const double *d = sb.out(b), *e = d + sb.nmax;
-    // Gershgorin bounds and the smallest pivot magnitude allowed
-    double lo = 1e308, hi = -1e308, emax = 0.0;
+    // Gershgorin bounds
+    double lo = 1e308, hi = -1e308;
     for (int c = tid; c < n; c += 256) {
         const double r = (c > 0 ? fabs(e[c - 1]) : 0.0) + (c + 1 < n ? fabs(e[c]) : 0.0);
         lo = fmin(lo, d[c] - r);
         hi = fmax(hi, d[c] + r);
-        if (c + 1 < n) emax = fmax(emax, e[c] * e[c]);
     }
     auto block = [&](double v, bool mx) {
         for (int o = 32; o > 0; o >>= 1) { const double u = __shfl_xor(v, o, 64); v = mx ? fmax(v, u) : fmin(v, u); }
@@ -449,52 +640,58 @@ __global__ __launch_bounds__(256) void sturm_kernel(SpectralBatch sb) {
     };
     lo = block(lo, false);
     hi = block(hi, true);
-    emax = block(emax, true);
-    const double pivmin = 2.2250738585072014e-308 * fmax(1.0, emax) * 4.0;
-    const double pad = 4.4408920985006262e-16 * fmax(fabs(lo), fabs(hi)) * n + pivmin;
-    lo -= pad;
-    hi += pad;
+    const double norm = fmax(fabs(lo), fabs(hi));
+    int ex = 0;
+    if (norm > 0.0 && norm < 1e308) frexp(norm, &ex);
+    const double pad = 4.4408920985006262e-16 * n;
+    lo = ldexp(lo, -ex) - pad;
+    hi = ldexp(hi, -ex) + pad;
     const int want = n - i;  // count(x) >= want: at least n - i eigenvalues below x, so x > lambda_i
-    for (int pass = 0; pass < 10; ++pass) {
-        const double step = (hi - lo) * (1.0 / 65.0);
-        const double x = lo + step * (lane + 1);
+    for (int pass = 0; pass < 16; ++pass) {
+        const double step = (hi - lo) * (1.0 / 17.0);
+        const double x = lo + step * ((lane & 15) + 1);
         int cnt = 0;
-        double q = 1.0;
+        double p0 = 0.0, p1 = 1.0;
         for (int c0 = 0; c0 < n; c0 += kSturmChunk) {
             const int cn = min(kSturmChunk, n - c0);
             __syncthreads();
-            for (int c = tid; c < cn; c += 256) {
-                const double u = c0 + c > 0 ? e[c0 + c - 1] : 0.0;
-                de[c] = make_double2(d[c0 + c], u * u);
+            for (int c = tid; c < kSturmChunk; c += 256) {
+                // past n: positive multiples of the last minor (no sign change)
+                const double u = c0 + c > 0 && c < cn ? ldexp(e[c0 + c - 1], -ex) : 0.0;
+                de[c] = make_double2(c < cn ? ldexp(d[c0 + c], -ex) : 4.0, u * u);
             }
             __syncthreads();
-#pragma unroll 4
-            for (int c = 0; c < cn; ++c) {
-                // 1 / q to full precision: the hardware estimate and two Newton steps
-                double r = __builtin_amdgcn_rcp(q);
-                r = fma(fma(-q, r, 1.0), r, r);
-                r = fma(fma(-q, r, 1.0), r, r);
-                q = fma(-de[c].y, r, de[c].x - x);
-                if (fabs(q) <= pivmin) q = -pivmin;
-                cnt += q < 0.0;
+            for (int c = 0; c < cn; c += 8) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const double2 t = de[c + u];
+                    double q = fma(t.x - x, p1, -(t.y * p0));
+                    // a zero minor takes the sign that makes the step a change
+                    if (q == 0.0) q = -1e-30 * p1;
+                    cnt += (int)((__builtin_bit_cast(uint64_t, q) ^ __builtin_bit_cast(uint64_t, p1)) >> 63);
+                    p0 = p1;
+                    p1 = q;
+                }
+                const int s = -__builtin_amdgcn_frexp_exp(fmax(fabs(p0), fabs(p1)));
+                p0 = ldexp(p0, s);
+                p1 = ldexp(p1, s);
             }
         }
-        const unsigned long long above = __ballot(cnt >= want);
-        const int f = above ? __ffsll((long long)above) - 1 : 64;  // first point above lambda_i
-        const double nlo = f == 0 ? lo : lo + step * f, nhi = f == 64 ? hi : lo + step * (f + 1);
+        const unsigned above = (unsigned)(__ballot(cnt >= want) >> (lane & 48)) & 0xFFFFu;
+        const int f = above ? __ffs(above) - 1 : 16;  // first point above lambda_i
+        const double nlo = f == 0 ? lo : lo + step * f, nhi = f == 16 ? hi : lo + step * (f + 1);
         lo = nlo;
         hi = nhi;
     }
-    if (lane == 0 && i < kb) sb.out(b)[3 * (long)sb.nmax + i] = 0.5 * (lo + hi);
+    if ((lane & 15) == 0 && i < n) sb.out(b)[3 * (long)sb.nmax + i] = norm == 0.0 ? 0.0 : ldexp(0.5 * (lo + hi), ex);
 }
 
 hipError_t launch_spectra(const SpectralBatch& sb, const SpectralJob* host_jobs, hipStream_t st) {
-    int tiles = 0, nb = 1, kmax = 1;
+    int tiles = 0, nb = 1;
     for (int b = 0; b < sb.count; ++b) {
         const int nt = (host_jobs[b].n + 63) / 64;
         tiles = host_jobs[b].tile0 + nt * (nt + 1) / 2;
         nb = std::max(nb, (int)host_jobs[b].n);
-        kmax = std::max(kmax, (int)host_jobs[b].k);
     }
     hipLaunchKernelGGL(gram_kernel, dim3(tiles), dim3(256), 0, st, sb);
     if (nb > kSpectralMax) {
@@ -505,7 +702,7 @@ hipError_t launch_spectra(const SpectralBatch& sb, const SpectralJob* host_jobs,
                 const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 256);
                 if (e != hipSuccess) return e;
             }
-        for (int j = -1; j == -1 || j <= nb - 3; ++j) {
+        for (int j = -1; j < tail_step(nb); ++j) {
             // workgroups per matrix: one pass of 16 rows each while that stays near 2048 in all
             // (eight per CU); beyond, a workgroup loops over its rows and the O(n) vectors are
             // formed fewer times
@@ -517,8 +714,9 @@ hipError_t launch_spectra(const SpectralBatch& sb, const SpectralJob* host_jobs,
             else
                 hipLaunchKernelGGL(tri_step_kernel<false>, dim3(wgs, sb.count), dim3(kTriThreads), bytes, st, sb, j);
         }
+        hipLaunchKernelGGL(tri_tail_kernel, dim3(sb.count), dim3(kTailTY * kTailTX), 0, st, sb);
     }
-    hipLaunchKernelGGL(sturm_kernel, dim3((kmax + 3) / 4, sb.count), dim3(256), 0, st, sb);
+    hipLaunchKernelGGL(sturm_kernel, dim3((nb + 15) / 16, sb.count), dim3(256), 0, st, sb);
     return hipGetLastError();
 }
 

@@ -87,6 +87,32 @@ def test_schedule_build_mixed_sizes(P):
         assert got[i, 5] == pytest.approx(ref.sigma1_sq, rel=1e-13)
 
 
+@pytest.mark.parametrize("n", [64, 192, 193, 194, 195, 385])
+def test_matrix_stats_tail_block(P, n):
+    """Short sides around the block that is reduced in registers (192 rows, all steps up to 193), graded so
+    that the tail holds ~1e-4 of the energy: it has to keep its own relative accuracy.  A Gram matrix is
+    exact to ~n 2^-53 of its norm and so are its eigenvalues."""
+    rng = np.random.default_rng(n)
+    w = (rng.standard_normal((n + 70, n)) * np.arange(1, n + 1) ** -1.3).astype(np.float32)
+    ref = osp.matrix_stats(w.astype(np.float64), eta=1e-6)
+    got = P.matrix_stats(_dev(w), eta=1e-6)
+    assert got[0] == pytest.approx(ref.energy_top, rel=n * 2.0 ** -52)
+    assert abs(got[1] - ref.energy_tail) <= n * 2.0 ** -52 * ref.sigma1_sq
+    assert got[5] == pytest.approx(ref.sigma1_sq, rel=n * 2.0 ** -52)
+
+
+def test_matrix_stats_decoupled(P):
+    """Diagonal weights (every off-diagonal of the tridiagonal form zero), repeated and zero singular values,
+    and the zero matrix."""
+    s = np.zeros(230, np.float32)
+    s[:7], s[7:120] = 2.0, 0.5
+    got = P.matrix_stats(_dev(np.diag(s)), eta=1e-6)
+    assert got[0] == pytest.approx(7 * 4.0 + 16 * 0.25, rel=1e-14)
+    assert got[1] == pytest.approx(97 * 0.25, rel=1e-14)
+    got = P.matrix_stats(_dev(np.zeros((30, 200), np.float32)), eta=1e-6)
+    assert got[0] == got[1] == got[2] == got[4] == got[5] == 0.0 and np.isinf(got[3])
+
+
 @pytest.mark.parametrize("n", [6592, 6720])
 def test_matrix_stats_large(P, n):
     """The last short sides whose reduction keeps its vectors in LDS and the first that does not:
