@@ -333,28 +333,32 @@ __global__ __launch_bounds__(256) void adaln_mod_kernel(const float* x, ModBatch
 // hi + mid + lo == x exactly), and bf16 x bf16 products are exact in fp32: the MFMAs sum the
 // fp32 products of the FMA kernel above, in another order.  A workgroup owns 32 features x 32
 // samples (v_mfma_f32_32x32x16_bf16: A = the x parts, one sample per lane row; B = the weight
-// rows, one feature per lane column) and walks k in chunks of 256: the chunk's 32 weight rows
+// rows, one feature per lane column) and walks k in chunks of 16 per wave: the chunk's 32 weight rows
 // and 32 x rows are read with 16-byte loads in which every wave covers whole 128-byte lines
 // (reading the MFMA layout straight from memory touches 32 lines per load instruction, and the
 // kernel was bound by that request rate), stored to LDS, and wave w takes the chunk's k step w.
 // A thread issues the loads of up to kModG chunks before storing the first (one memory round
-// trip for d <= 1536).  The partial tiles of the sixteen waves are summed in LDS in wave order
-// (deterministic).
-constexpr int kModWaves = 16, kModKC = 16 * kModWaves, kModG = 6;
-constexpr int kModWS = kModKC * 2 + 16, kModXS = kModKC * 4 + 16;  // padded LDS row bytes
+// trip for d <= 1536 with sixteen waves, d <= 768 with eight, two workgroups a CU).  The partial tiles
+// of the waves are summed in LDS in wave order (deterministic).
+constexpr int kModG = 6;
+template <int kModWaves>
 __global__ __launch_bounds__(kModWaves * 64) void adaln_mod_mfma_kernel(const float* x, ModBatch mb, int B, int d,
                                                                         int n_out) {
     const bf16* W = (const bf16*)mb.W[blockIdx.z];
     const float* bias = mb.bias[blockIdx.z];
     float* mod = mb.mod[blockIdx.z];
-    __shared__ __attribute__((aligned(16))) char sw[32 * kModWS];
-    __shared__ __attribute__((aligned(16))) char sx[32 * kModXS];
-    __shared__ float red[kModWaves][32 * 32];
+    constexpr int kModKC = 16 * kModWaves, WT = 2 * kModWaves;         // chunk depth, threads per weight row
+    constexpr int kModWS = kModKC * 2 + 16, kModXS = kModKC * 4 + 16;  // padded LDS row bytes
+    // the operand chunks, then the partial tiles
+    constexpr int OPS = 32 * (kModWS + kModXS), RED = kModWaves * 4096;
+    __shared__ __attribute__((aligned(16))) char smem[OPS > RED ? OPS : RED];
+    char *const sw = smem, *const sx = smem + 32 * kModWS;
+    float* const red = (float*)smem;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int j0 = blockIdx.x * 32, b0 = blockIdx.y * 32;
-    // loads of a chunk: weight row tid / 32, bytes 16 (tid % 32) of its 512; x rows tid / 64
-    // and tid / 64 + 16, bytes 16 (tid % 64) of their 1024
-    const int wr = tid >> 5, wc = (tid & 31) * 16, xr = tid >> 6, xc = (tid & 63) * 16;
+    // loads of a chunk: weight row tid / WT, bytes 16 (tid % WT) of its 2 KC; x rows tid / (2 WT)
+    // and tid / (2 WT) + 16, bytes 16 (tid % (2 WT)) of their 4 KC
+    const int wr = tid / WT, wc = tid % WT * 16, xr = tid / (2 * WT), xc = tid % (2 * WT) * 16;
     const bool win = j0 + wr < n_out, xin0 = b0 + xr < B, xin1 = b0 + xr + 16 < B;
     const char* wsrc = (const char*)(W + (long)(win ? j0 + wr : 0) * d) + wc;
     const char* xsrc0 = (const char*)(x + (long)(xin0 ? b0 + xr : 0) * d) + xc;
@@ -406,17 +410,21 @@ __global__ __launch_bounds__(kModWaves * 64) void adaln_mod_mfma_kernel(const fl
     }
     // lane l holds feature column l % 32 and, for register r, sample row
     // (r / 4) * 8 + (l / 32) * 4 + r % 4 of the tile
+    __syncthreads();  // every wave has read the last chunk's fragments
 #pragma unroll
-    for (int r = 0; r < 16; ++r) red[wave][((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * 32 + col] = acc[r];
+    for (int r = 0; r < 16; ++r) red[wave * 1024 + ((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * 32 + col] = acc[r];
     __syncthreads();
-    const int i = tid >> 5, j = tid & 31;  // one output per thread: sample i, feature j
-    float v = red[0][tid];
 #pragma unroll
-    for (int w = 1; w < kModWaves; ++w) v += red[w][tid];
-    if (b0 + i < B && j0 + j < n_out) mod[(long)(b0 + i) * n_out + j0 + j] = v + (bias ? bias[j0 + j] : 0.f);
+    for (int t = tid; t < 1024; t += kModWaves * 64) {
+        const int i = t >> 5, j = t & 31;  // sample i, feature j
+        float v = red[t];
+#pragma unroll
+        for (int w = 1; w < kModWaves; ++w) v += red[w * 1024 + t];
+        if (b0 + i < B && j0 + j < n_out) mod[(long)(b0 + i) * n_out + j0 + j] = v + (bias ? bias[j0 + j] : 0.f);
+    }
 }
 
-// Wide variant for many output features (the DiT modulation, 6 d outputs per block): a
+// Wide variant for many output features and samples: a
 // workgroup owns 32 samples x 32 WV features and each of its WV waves owns 32 features over
 // the whole k range, so no partial tiles are exchanged and SiLU(c) is read once per 32 WV
 // features.  k goes in 64-deep chunks through LDS: x split once into its three bf16 parts by
@@ -529,7 +537,13 @@ hipError_t launch_adaln_mod_batch(int dtype, const float* x, const ModBatch& mb,
                                   hipStream_t st) {
     if (d % 64) return hipErrorInvalidValue;  // whole 64-deep k chunks (the model requires d % 128 == 0)
     if (mb.n < 1 || mb.n > kMaxModUnits) return hipErrorInvalidValue;
-    if (dtype == 1 && n_out >= 2048) {
+    // bf16: the K-split kernel up to 1024 workgroups, with eight waves, or with sixteen where they are one
+    // round of the CUs and k is deep (d 1152, one block's 6912 features 9.1 us, eight waves 9.7, wide 21.4; four
+    // blocks 20.6 against 29.3 and 24.2; 128 samples 22.5 with eight waves, wide 26.6).  Many features of
+    // shallow k keep the wide kernel, whose sums are the same for every number of samples (d 256, 8192
+    // features 6.8 us, K-split 4.2); past 1024 workgroups it is the one measured.
+    const long wgs = (long)((n_out + 31) / 32) * ((B + 31) / 32) * mb.n;
+    if (dtype == 1 && n_out >= 2048 && (d < 384 || wgs > 1024)) {
         // many features (DiT: 6 d per block): the widest workgroups that still give two per CU
         const long tiles = (long)((B + 31) / 32) * mb.n;
         const auto groups = [&](int wv) { return (long)((n_out + 32 * wv - 1) / (32 * wv)) * tiles; };
@@ -544,8 +558,11 @@ hipError_t launch_adaln_mod_batch(int dtype, const float* x, const ModBatch& mb,
             hipLaunchKernelGGL(adaln_mod_wide_kernel<2>, grid, dim3(128), 0, st, x, mb, B, d, n_out);
         }
     } else if (dtype == 1) {
-        dim3 grid((n_out + 31) / 32, (B + 31) / 32, mb.n), block(kModWaves * 64);
-        hipLaunchKernelGGL(adaln_mod_mfma_kernel, grid, block, 0, st, x, mb, B, d, n_out);
+        dim3 grid((n_out + 31) / 32, (B + 31) / 32, mb.n);
+        if (wgs <= 256 && d >= 768)
+            hipLaunchKernelGGL(adaln_mod_mfma_kernel<16>, grid, dim3(1024), 0, st, x, mb, B, d, n_out);
+        else
+            hipLaunchKernelGGL(adaln_mod_mfma_kernel<8>, grid, dim3(512), 0, st, x, mb, B, d, n_out);
     } else {
         dim3 grid((n_out + 63) / 64, (B + 31) / 32, mb.n), block(256);
         hipLaunchKernelGGL(adaln_mod_kernel<float>, grid, block, 0, st, x, mb, B, d, n_out);

@@ -517,3 +517,11 @@ def test_small_products_f32(P, M, N, K):
     P.op_linear(dev(A), dev(W), out, bias=dev(b), act=3)
     assert relmax(host(th), h0 + z) <= 1e-5
     assert relmax(host(out), om.silu(z)) <= 1e-5
+
+
+# eight-wave K-split modulation (over 256 workgroups, or shallow k), its last grid and the wide kernel's
+# first, one and two rounds of loads, a partial last chunk and ragged features
+@pytest.mark.parametrize("B,d,n_out", [(2, 384, 2304), (33, 832, 4100), (130, 448, 6500), (161, 384, 5440),
+                                       (161, 384, 5500), (2, 320, 2048), (70, 1600, 3000)])
+def test_adaln_mod_ksplit(P, B, d, n_out):
+    test_adaln_mod(P, "bf16", B, d, n_out)
