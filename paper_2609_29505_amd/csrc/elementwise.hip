@@ -1,5 +1,7 @@
 // Bandwidth-bound kernels of the step: the frozen-run residual update, stream set-up,
 // the sampler update and the DiT conditioning path.
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -333,32 +335,28 @@ __global__ __launch_bounds__(256) void adaln_mod_kernel(const float* x, ModBatch
 // hi + mid + lo == x exactly), and bf16 x bf16 products are exact in fp32: the MFMAs sum the
 // fp32 products of the FMA kernel above, in another order.  A workgroup owns 32 features x 32
 // samples (v_mfma_f32_32x32x16_bf16: A = the x parts, one sample per lane row; B = the weight
-// rows, one feature per lane column) and walks k in chunks of 16 per wave: the chunk's 32 weight rows
+// rows, one feature per lane column) and walks k in chunks of 256: the chunk's 32 weight rows
 // and 32 x rows are read with 16-byte loads in which every wave covers whole 128-byte lines
 // (reading the MFMA layout straight from memory touches 32 lines per load instruction, and the
 // kernel was bound by that request rate), stored to LDS, and wave w takes the chunk's k step w.
 // A thread issues the loads of up to kModG chunks before storing the first (one memory round
-// trip for d <= 1536 with sixteen waves, d <= 768 with eight, two workgroups a CU).  The partial tiles
-// of the waves are summed in LDS in wave order (deterministic).
-constexpr int kModG = 6;
-template <int kModWaves>
+// trip for d <= 1536).  The partial tiles of the sixteen waves are summed in LDS in wave order
+// (deterministic).
+constexpr int kModWaves = 16, kModKC = 16 * kModWaves, kModG = 6;
+constexpr int kModWS = kModKC * 2 + 16, kModXS = kModKC * 4 + 16;  // padded LDS row bytes
 __global__ __launch_bounds__(kModWaves * 64) void adaln_mod_mfma_kernel(const float* x, ModBatch mb, int B, int d,
                                                                         int n_out) {
     const bf16* W = (const bf16*)mb.W[blockIdx.z];
     const float* bias = mb.bias[blockIdx.z];
     float* mod = mb.mod[blockIdx.z];
-    constexpr int kModKC = 16 * kModWaves, WT = 2 * kModWaves;         // chunk depth, threads per weight row
-    constexpr int kModWS = kModKC * 2 + 16, kModXS = kModKC * 4 + 16;  // padded LDS row bytes
-    // the operand chunks, then the partial tiles
-    constexpr int OPS = 32 * (kModWS + kModXS), RED = kModWaves * 4096;
-    __shared__ __attribute__((aligned(16))) char smem[OPS > RED ? OPS : RED];
-    char *const sw = smem, *const sx = smem + 32 * kModWS;
-    float* const red = (float*)smem;
+    __shared__ __attribute__((aligned(16))) char sw[32 * kModWS];
+    __shared__ __attribute__((aligned(16))) char sx[32 * kModXS];
+    __shared__ float red[kModWaves][32 * 32];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int j0 = blockIdx.x * 32, b0 = blockIdx.y * 32;
-    // loads of a chunk: weight row tid / WT, bytes 16 (tid % WT) of its 2 KC; x rows tid / (2 WT)
-    // and tid / (2 WT) + 16, bytes 16 (tid % (2 WT)) of their 4 KC
-    const int wr = tid / WT, wc = tid % WT * 16, xr = tid / (2 * WT), xc = tid % (2 * WT) * 16;
+    // loads of a chunk: weight row tid / 32, bytes 16 (tid % 32) of its 512; x rows tid / 64
+    // and tid / 64 + 16, bytes 16 (tid % 64) of their 1024
+    const int wr = tid >> 5, wc = (tid & 31) * 16, xr = tid >> 6, xc = (tid & 63) * 16;
     const bool win = j0 + wr < n_out, xin0 = b0 + xr < B, xin1 = b0 + xr + 16 < B;
     const char* wsrc = (const char*)(W + (long)(win ? j0 + wr : 0) * d) + wc;
     const char* xsrc0 = (const char*)(x + (long)(xin0 ? b0 + xr : 0) * d) + xc;
@@ -410,21 +408,17 @@ __global__ __launch_bounds__(kModWaves * 64) void adaln_mod_mfma_kernel(const fl
     }
     // lane l holds feature column l % 32 and, for register r, sample row
     // (r / 4) * 8 + (l / 32) * 4 + r % 4 of the tile
-    __syncthreads();  // every wave has read the last chunk's fragments
 #pragma unroll
-    for (int r = 0; r < 16; ++r) red[wave * 1024 + ((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * 32 + col] = acc[r];
+    for (int r = 0; r < 16; ++r) red[wave][((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3)) * 32 + col] = acc[r];
     __syncthreads();
+    const int i = tid >> 5, j = tid & 31;  // one output per thread: sample i, feature j
+    float v = red[0][tid];
 #pragma unroll
-    for (int t = tid; t < 1024; t += kModWaves * 64) {
-        const int i = t >> 5, j = t & 31;  // sample i, feature j
-        float v = red[t];
-#pragma unroll
-        for (int w = 1; w < kModWaves; ++w) v += red[w * 1024 + t];
-        if (b0 + i < B && j0 + j < n_out) mod[(long)(b0 + i) * n_out + j0 + j] = v + (bias ? bias[j0 + j] : 0.f);
-    }
+    for (int w = 1; w < kModWaves; ++w) v += red[w][tid];
+    if (b0 + i < B && j0 + j < n_out) mod[(long)(b0 + i) * n_out + j0 + j] = v + (bias ? bias[j0 + j] : 0.f);
 }
 
-// Wide variant for many output features and samples: a
+// Wide variant for many output features (the DiT modulation, 6 d outputs per block): a
 // workgroup owns 32 samples x 32 WV features and each of its WV waves owns 32 features over
 // the whole k range, so no partial tiles are exchanged and SiLU(c) is read once per 32 WV
 // features.  k goes in 64-deep chunks through LDS: x split once into its three bf16 parts by
@@ -533,21 +527,121 @@ __global__ __launch_bounds__(WV * 64) void adaln_mod_wide_kernel(const float* x,
     }
 }
 
+// The wide kernel's sums for grids too small to hide its rounds of loads: a workgroup owns 32 features x
+// 32 samples, its first wave holds the one accumulator and the other eight load and split.  A loader
+// has the loads of kTallG chunks in flight and the chunks pass through two LDS buffers, one
+// barrier each, so the first wave multiplies one while the next is split and stored.  The products enter
+// the accumulator in the wide kernel's order (k step by k step, lo, mid, hi): the same bits.  Bound by
+// that one chain of MFMAs: two workgroups on a CU take twice as long as one.
+constexpr int kTallKC = 128, kTallG = 5, kTallLoaders = 512;
+constexpr int kTallRS = kTallKC * 2 + 16;  // padded LDS row bytes
+__global__ __launch_bounds__(64 + kTallLoaders) void adaln_mod_tall_kernel(const float* x, ModBatch mb, int B, int d,
+                                                                           int n_out) {
+    constexpr int BUF = 4 * 32 * kTallRS;  // weight rows, then the three x parts
+    __shared__ __attribute__((aligned(16))) char sh[2 * BUF];
+    const bf16* W = (const bf16*)mb.W[blockIdx.z];
+    const float* bias = mb.bias[blockIdx.z];
+    float* mod = mb.mod[blockIdx.z];
+    const int j0 = blockIdx.x * 32, b0 = blockIdx.y * 32;
+    const int nch = (d + kTallKC - 1) / kTallKC;
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) > 0) {
+        // loads of a chunk: weight row t / 16, bf16 8 (t % 16) .. + 7 of its 128; x rows t / 32 and
+        // t / 32 + 16, floats 4 (t % 32) .. + 3 of their 128.  Past n_out, B and d the last ones again:
+        // such features and samples are not stored, such k steps not multiplied
+        const int t = threadIdx.x - 64;
+        const int wr = t >> 4, we = (t & 15) * 8, xr = t >> 5, xe = (t & 31) * 4;
+        const bf16* const wsrc = W + (long)min(j0 + wr, n_out - 1) * d;
+        const float* xsrc[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) xsrc[p] = x + (long)min(b0 + xr + 16 * p, B - 1) * d;
+        for (int c0 = 0; c0 < nch; c0 += kTallG) {
+            u32x4 rw[kTallG];
+            f32x4 rx[kTallG][2];
+#pragma unroll
+            for (int g = 0; g < kTallG; ++g) {
+                const int k = (c0 + g) * kTallKC;
+                rw[g] = *(const u32x4*)(wsrc + min(k + we, d - 8));
+#pragma unroll
+                for (int p = 0; p < 2; ++p) rx[g][p] = *(const f32x4*)(xsrc[p] + min(k + xe, d - 4));
+            }
+#pragma unroll
+            for (int g = 0; g < kTallG; ++g) {
+                if (c0 + g < nch) {
+                    char* const buf = sh + ((c0 + g) & 1) * BUF;
+                    *(u32x4*)(buf + wr * kTallRS + we * 2) = rw[g];
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        bf16x4 hi, mid, lo;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float v = rx[g][p][e];
+                            hi[e] = f2bf(v);
+                            const float r1 = v - bf2f(hi[e]);
+                            mid[e] = f2bf(r1);
+                            lo[e] = f2bf(r1 - bf2f(mid[e]));
+                        }
+                        char* const xd = buf + (32 + xr + 16 * p) * kTallRS + xe * 2;
+                        *(bf16x4*)xd = hi;
+                        *(bf16x4*)(xd + 32 * kTallRS) = mid;
+                        *(bf16x4*)(xd + 64 * kTallRS) = lo;
+                    }
+                    __syncthreads();
+                }
+            }
+        }
+        return;
+    }
+    const int lane = threadIdx.x, col = lane & 31;
+    const char* const fr = sh + col * kTallRS + (lane >> 5) * 16;
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    for (int c = 0; c < nch; ++c) {
+        __syncthreads();  // chunk c is in place; the other buffer, read before this barrier, is free
+        const char* const buf = fr + (c & 1) * BUF;
+        auto steps = [&](auto n) {
+#pragma unroll
+            for (int q = 0; q < decltype(n)::value; ++q) {
+                const bf16x8 wf = *(const bf16x8*)(buf + q * 32);
+                const bf16x8 xh = *(const bf16x8*)(buf + 32 * kTallRS + q * 32);
+                const bf16x8 xm = *(const bf16x8*)(buf + 64 * kTallRS + q * 32);
+                const bf16x8 xl = *(const bf16x8*)(buf + 96 * kTallRS + q * 32);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl, wf, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xm, wf, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh, wf, acc, 0, 0, 0);
+            }
+        };
+        // d is a multiple of 64: the last chunk is whole or half
+        if ((c + 1) * kTallKC <= d) steps(std::integral_constant<int, kTallKC / 16>{});
+        else steps(std::integral_constant<int, kTallKC / 32>{});
+    }
+    const int j = j0 + col;
+    if (j >= n_out) return;
+    const float bj = bias ? bias[j] : 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int i = (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+        if (b0 + i < B) mod[(long)(b0 + i) * n_out + j] = acc[r] + bj;
+    }
+}
+
 hipError_t launch_adaln_mod_batch(int dtype, const float* x, const ModBatch& mb, int B, int d, int n_out,
                                   hipStream_t st) {
     if (d % 64) return hipErrorInvalidValue;  // whole 64-deep k chunks (the model requires d % 128 == 0)
     if (mb.n < 1 || mb.n > kMaxModUnits) return hipErrorInvalidValue;
-    // bf16: the K-split kernel up to 1024 workgroups, with eight waves, or with sixteen where they are one
-    // round of the CUs and k is deep (d 1152, one block's 6912 features 9.1 us, eight waves 9.7, wide 21.4; four
-    // blocks 20.6 against 29.3 and 24.2; 128 samples 22.5 with eight waves, wide 26.6).  Many features of
-    // shallow k keep the wide kernel, whose sums are the same for every number of samples (d 256, 8192
-    // features 6.8 us, K-split 4.2); past 1024 workgroups it is the one measured.
-    const long wgs = (long)((n_out + 31) / 32) * ((B + 31) / 32) * mb.n;
-    if (dtype == 1 && n_out >= 2048 && (d < 384 || wgs > 1024)) {
-        // many features (DiT: 6 d per block): the widest workgroups that still give two per CU
+    // bf16: the order of an output's sum depends on the number of features alone (2048: the K-split
+    // kernel below, the wide kernel's order from there), never on the samples or on how many units share
+    // the launch, so a block's modulation does not change with the batch or with the other blocks' activity
+    if (dtype == 1 && n_out >= 2048) {
+        // many features (DiT: 6 d per block): the tall kernel while its workgroups are about seven for four
+        // CUs (d 1152: 216 of them 11.2 us against 21.5, 432 19.6 against 22.2, 648 27.5 against 25.2; d 384:
+        // 288 8.2 against 8.4, 576 11.9 against 10.4), then the widest wide ones that still give two per CU
         const long tiles = (long)((B + 31) / 32) * mb.n;
         const auto groups = [&](int wv) { return (long)((n_out + 32 * wv - 1) / (32 * wv)) * tiles; };
-        if (groups(8) >= 512) {
+        if (groups(1) <= 448) {
+            dim3 grid((n_out + 31) / 32, (B + 31) / 32, mb.n);
+            hipLaunchKernelGGL(adaln_mod_tall_kernel, grid, dim3(64 + kTallLoaders), 0, st, x, mb, B, d, n_out);
+        } else if (groups(8) >= 512) {
             dim3 grid((n_out + 255) / 256, (B + 31) / 32, mb.n);
             hipLaunchKernelGGL(adaln_mod_wide_kernel<8>, grid, dim3(512), 0, st, x, mb, B, d, n_out);
         } else if (groups(4) >= 512) {
@@ -558,11 +652,8 @@ hipError_t launch_adaln_mod_batch(int dtype, const float* x, const ModBatch& mb,
             hipLaunchKernelGGL(adaln_mod_wide_kernel<2>, grid, dim3(128), 0, st, x, mb, B, d, n_out);
         }
     } else if (dtype == 1) {
-        dim3 grid((n_out + 31) / 32, (B + 31) / 32, mb.n);
-        if (wgs <= 256 && d >= 768)
-            hipLaunchKernelGGL(adaln_mod_mfma_kernel<16>, grid, dim3(1024), 0, st, x, mb, B, d, n_out);
-        else
-            hipLaunchKernelGGL(adaln_mod_mfma_kernel<8>, grid, dim3(512), 0, st, x, mb, B, d, n_out);
+        dim3 grid((n_out + 31) / 32, (B + 31) / 32, mb.n), block(kModWaves * 64);
+        hipLaunchKernelGGL(adaln_mod_mfma_kernel, grid, block, 0, st, x, mb, B, d, n_out);
     } else {
         dim3 grid((n_out + 63) / 64, (B + 31) / 32, mb.n), block(256);
         hipLaunchKernelGGL(adaln_mod_kernel<float>, grid, block, 0, st, x, mb, B, d, n_out);

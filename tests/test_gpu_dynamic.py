@@ -210,3 +210,27 @@ def test_replay_search_bf16(P, name):
     print(name, "step-2 deviations gpu", got, "oracle", want)
     assert np.allclose(got, want, rtol=0.1, atol=1e-3)
     dm.close()
+
+
+def test_active_block_does_not_depend_on_others_activity(P):
+    """DiT: the modulations of all of a step's active blocks are one launch.  With every block but the
+    first inert (zero output projections, hence updates of exactly zero), a step with all of them active
+    and one with them frozen leave the same bits: the first block's modulation is summed in one order."""
+    import torch
+    cfg = synth.get_config("dit_mini", L=6, T=3)
+    w, x = [dict(u) for u in synth.model_weights(cfg)], synth.inputs(cfg)
+    for u in w[1:]:
+        for key in ("w_o", "b_o", "w2", "b2"):
+            u[key] = np.zeros_like(u[key])
+    dm = P.DeviceModel(cfg, w, x)
+    out = []
+    for others in (1, 0):
+        z = torch.from_numpy(x["z"].copy()).cuda()
+        cache = P.Cache(dm)
+        cache.reset()
+        dm.step_masked(z, 1, np.ones(cfg.L, np.uint8), cache)
+        dm.step_masked(z, 2, np.array([1] + [others] * (cfg.L - 1), np.uint8), cache)
+        out.append(z.cpu().numpy())
+    assert np.isfinite(out[0]).all()
+    assert np.array_equal(out[0], out[1])
+    dm.close()

@@ -289,7 +289,7 @@ def test_adaln_mod_wide_widths_bitwise(P):
     """The wide modulation kernel (2048 outputs or more) takes workgroups of eight, four or two
     waves as the grid size allows, and computes every output in the same order whatever the
     width: the rows of a 512-sample problem (eight-wave workgroups) equal those of its 256- and
-    32-sample slices (four- and two-wave workgroups) bit for bit."""
+    32-sample slices (four-wave workgroups and the tall kernel, which keeps the order) bit for bit."""
     rng = np.random.default_rng(5)
     B, d, n_out = 512, 256, 8192
     x = om.silu(rng.standard_normal((B, d))).astype(np.float32)
@@ -519,9 +519,27 @@ def test_small_products_f32(P, M, N, K):
     assert relmax(host(out), om.silu(z)) <= 1e-5
 
 
-# eight-wave K-split modulation (over 256 workgroups, or shallow k), its last grid and the wide kernel's
-# first, one and two rounds of loads, a partial last chunk and ragged features
+# many features: last of the tall kernel's grids (448 workgroups) and the first past them, whole and half
+# last chunks, one and several groups of loads, ragged features and samples; few features: the K-split kernel
 @pytest.mark.parametrize("B,d,n_out", [(2, 384, 2304), (33, 832, 4100), (130, 448, 6500), (161, 384, 5440),
-                                       (161, 384, 5500), (2, 320, 2048), (70, 1600, 3000)])
+                                       (161, 384, 5500), (2, 320, 2048), (70, 1600, 3000), (33, 64, 7168),
+                                       (33, 192, 7169), (5, 704, 14300), (70, 1600, 1300)])
 def test_adaln_mod_ksplit(P, B, d, n_out):
     test_adaln_mod(P, "bf16", B, d, n_out)
+
+
+# (d, n_out) of DiT blocks and of a UNet time projection: the tall kernel at 1 and 32 samples, the wide one at
+# 128 and 512; sixteen-wave K-split at every batch
+@pytest.mark.parametrize("d,n_out", [(1152, 6912), (768, 4608), (1280, 1280), (640, 640)])
+def test_adaln_mod_rows_do_not_depend_on_batch(P, d, n_out):
+    """The bits of a sample's modulation are the same alone, in a small and in a large batch."""
+    rng = np.random.default_rng(d)
+    x = om.silu(rng.standard_normal((512, d))).astype(np.float32)
+    W = dev(synth.store(rng.standard_normal((n_out, d)) / np.sqrt(d), "bf16"))
+    outs = []
+    for nb in (512, 128, 32, 1):
+        mod = empty((nb, n_out), "f32")
+        P.op_adaln_mod(dev(np.ascontiguousarray(x[:nb])), W, mod)
+        outs.append(host(mod))
+    for o in outs[1:]:
+        assert np.array_equal(outs[0][:len(o)], o), len(o)
