@@ -600,7 +600,7 @@ int run_step(sgd_model* m, void* state, int step, const StepPlan& plan, const sg
             // its pre-norm, and this step has no gate, cached-update store, copy or drift record
             const bool next_norm = u + 1 < nu && act[u + 1] && !out_start(u + 1) &&
                                    !(unet && (nb == 1 || branch_of(u + 1) == BR_RESNET));
-            if (m->w2_ksplit > 1 && !gate2 && !dm2 && !copy2 && !dr && next_norm) {
+            if (m->w2_ksplit > 1 && plan.split && !gate2 && !dm2 && !copy2 && !dr && next_norm) {
                 GemmArgs g2;
                 g2.A0 = hid; g2.lda0 = F; g2.B = w.w2; g2.ldb = F; g2.M = (int)M; g2.N = dd; g2.K = F;
                 g2.ksplit = m->w2_ksplit;

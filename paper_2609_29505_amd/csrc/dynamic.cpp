@@ -177,6 +177,7 @@ extern "C" int sgd_replay_search(sgd_model* m, const void* z1, const sgd_replay_
         full.ckv_fill = s == 1;
         full.h = href;
         full.sampler = false;
+        full.split = false;  // as the candidates': an inert unit's deviation is exactly zero
         if ((rc = run_step(m, z, s, full, args, st))) return rc;
         ++evals;
         // 2. greedy growth of the cumulative frozen set (no cache exists at step 1)
@@ -198,6 +199,7 @@ extern "C" int sgd_replay_search(sgd_model* m, const void* z1, const sgd_replay_
                 pl.ckv = arch_cross(d.arch) ? base + lay.ckv : nullptr;
                 pl.h = hcand;
                 pl.sampler = false;
+                pl.split = false;
                 if ((rc = run_step(m, z, s, pl, args, st))) return rc;
                 ++evals;
                 SGD_HIP_TRY(launch_sumsq(href, hcand, nullptr, d.B, d.N, d.d, r0, r1, 1,

@@ -74,6 +74,9 @@ struct StepPlan {
     float* h = nullptr;                   // residual stream buffer (NULL: the workspace's); holds h_L at the end
     bool sampler = true;                  // z <- alpha z - beta h_L on the update rows
     const DriftRec* drift = nullptr;      // record drift (NULL: no)
+    // a split MLP output GEMM where the shape takes one.  Which units of a step take it depends on what
+    // they store and on the next unit, so outputs compared with each other are computed without
+    bool split = true;
 };
 
 int check_step_shapes(const sgd_model* m);

@@ -90,3 +90,23 @@ def test_split_output_gemm_graph_replays_equal_eager(P, wide):
         torch.cuda.synchronize()
     g.close()
     dm.close()
+
+
+def test_replay_inert_units_where_outputs_split(P, wide):
+    """Oracle replay on a shape whose MLP outputs split: the reference evaluation stores every unit's
+    update and the candidates store none, yet units whose branches are identically zero freeze at a
+    deviation of exactly 0 (tau = 0)."""
+    import torch
+    from dataclasses import replace
+    cfg, w, x = wide
+    cfg = replace(cfg, T=3)
+    w = [dict(u) for u in w]
+    for l in (0, 2):
+        for key in ("w_o", "w2"):
+            w[l][key] = np.zeros_like(w[l][key])
+    dm = P.DeviceModel(cfg, w, x)
+    life, _, dlog = dm.replay_search(torch.from_numpy(x["z"].copy()).cuda(), tau_agree=0.0, log=True)
+    dm.close()
+    assert dlog[1, 0, 0] == 0.0 and dlog[1, 0, 2] == 0.0
+    assert dlog[1, 0, 1] > 0 and dlog[1, 0, 3] > 0
+    assert life.tolist() == [1, cfg.T, 1, cfg.T]
