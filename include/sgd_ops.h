@@ -21,8 +21,8 @@ enum sgd_act { SGD_ACT_NONE = 0, SGD_ACT_GELU_ERF = 1, SGD_ACT_GELU_TANH = 2, SG
 /* out[M x N] = act(A[M x K] W[N x K]^T + bias) in dtype (the branch GEMM of an MLP input
  * projection).  gated != 0: W is [2N x K] = [W_gate; W_up] and out = act(A W_gate^T +
  * b[:N]) * (A W_up^T + b[N:]).  lda/ldw/ldo are row strides in elements.  tile selects a
- * bf16 kernel variant (0 auto; 1..5 fixed block tiles, for tests and sweeps: 1 256x256,
- * 2 256x128, 3 128x256, 4 128x128, 5 256x192, rows x columns).  Shape limits (bf16): K % 64 == 0,
+ * bf16 kernel variant (0 auto; 1..7 fixed block tiles, for tests and sweeps: 1 256x256,
+ * 2 256x128, 3 128x256, 4 128x128, 5 256x192, 6 128x64, 7 64x64, rows x columns).  Shape limits (bf16): K % 64 == 0,
  * N % 4 == 0, gated N a multiple of the tile width, operand rows and bias 16-byte aligned;
  * (fp32): K % 16 == 0, N % 64 == 0. */
 int sgd_op_linear(int32_t dtype, const void* A, int64_t lda, const void* W, int64_t ldw, const float* bias,
@@ -80,6 +80,10 @@ int sgd_op_residual(int32_t dtype, const void* A, int64_t lda, const void* W, co
  * K a multiple of 64 ksplit, 2 <= ksplit <= 8, part_stride >= M N (a multiple of 4). */
 int sgd_op_linear_split(int32_t dtype, const void* A, const void* W, const float* bias, float* parts,
                         int64_t part_stride, int32_t M, int32_t N, int32_t K, int32_t ksplit, void* hip_stream);
+/* The same on a fixed block tile: 0 auto, or 2, 4, 6, 7 (numbered as for sgd_op_linear). */
+int sgd_op_linear_split_tile(int32_t dtype, const void* A, const void* W, const float* bias, float* parts,
+                             int64_t part_stride, int32_t M, int32_t N, int32_t K, int32_t ksplit, int32_t tile,
+                             void* hip_stream);
 
 /* h <- h + delta[0] + ... + delta[r-1] elementwise over n fp32 values (n % 4 == 0), in
  * that order (the frozen-unit update of Sec. 3.1 for a run of r frozen units). */
@@ -109,7 +113,7 @@ int sgd_op_group_norm_silu(int32_t in_dtype, const void* x, void* y, int32_t B, 
  * (3 ky + kx) Cin + c multiplies channel c at grid offset (ky - 1, kx - 1)), as an implicit
  * GEMM on the matrix cores.  h == NULL: out [M x N] bf16 = conv + bias + rowbias[sample]
  * (rowbias fp32 [M / side^2 x N] or NULL); h != NULL: h [M x N] fp32 += conv + bias.
- * Cin % 64 == 0, N % 4 == 0.  tile: 0 auto, or 2 (256x128), 4 (128x128), 5 (256x192). */
+ * Cin % 64 == 0, N % 4 == 0.  tile: 0 auto, or 2, 4, 5, 6, 7 (numbered as for sgd_op_linear). */
 int sgd_op_conv3x3(const void* A, const void* W, const float* bias, const float* rowbias, int32_t side, void* out,
                    float* h, int32_t M, int32_t N, int32_t Cin, int32_t tile, void* hip_stream);
 

@@ -94,7 +94,8 @@ EXPORTS = ["sgd_last_error", "sgd_version", "sgd_s_min_default", "sgd_budget_lay
            "sgd_cache_bytes", "sgd_cache_bind", "sgd_cache_reset", "sgd_cache_destroy", "sgd_denoise_step",
            "sgd_denoise_step_noalloc", "sgd_graph_capture", "sgd_graph_launch", "sgd_graph_destroy",
            "sgd_denoise_step_masked", "sgd_drift_bytes", "sgd_drift_step", "sgd_replay_bytes", "sgd_replay_search",
-           "sgd_profile_begin", "sgd_profile_end", "sgd_op_linear", "sgd_op_linear_split", "sgd_op_attention", "sgd_op_norm", "sgd_op_norm_fold",
+           "sgd_profile_begin", "sgd_profile_end", "sgd_op_linear", "sgd_op_linear_split",
+           "sgd_op_linear_split_tile", "sgd_op_attention", "sgd_op_norm", "sgd_op_norm_fold",
            "sgd_op_frozen_run", "sgd_op_heads", "sgd_op_residual", "sgd_op_adaln_mod", "sgd_op_group_norm_silu",
            "sgd_op_group_norm_scratch_bytes", "sgd_op_conv3x3"]
 
@@ -144,6 +145,7 @@ def lib() -> C.CDLL:
             "sgd_profile_end": [vp, C.POINTER(C.c_double), C.POINTER(i64)],
             "sgd_op_linear": [i32, vp, i64, vp, i64, vp, vp, i64, i32, i32, i32, i32, i32, i32, vp],
             "sgd_op_linear_split": [i32, vp, vp, vp, vp, i64, i32, i32, i32, i32, vp],
+            "sgd_op_linear_split_tile": [i32, vp, vp, vp, vp, i64, i32, i32, i32, i32, i32, vp],
             "sgd_op_attention": [i32, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, vp],
             "sgd_op_norm": [i32, i32, vp, vp, i32, i32, C.c_float, vp, vp, vp, vp, i64, i32, vp],
             "sgd_op_norm_fold": [i32, i32, vp, vp, i32, i32, C.c_float, vp, vp, vp, vp, i64, i32,
@@ -363,13 +365,13 @@ def op_linear(A, W, out, bias=None, act=0, gated=False, tile=0, stream=None) -> 
                                out.stride(0), M, N, K, act, int(gated), tile, C.c_void_p(_stream_ptr(stream))))
 
 
-def op_linear_split(A, W, parts, bias=None, stream=None) -> None:
+def op_linear_split(A, W, parts, bias=None, stream=None, tile=0) -> None:
     """parts[s] = A[:, K_s] W[:, K_s]^T (+ bias for s = 0) over ksplit = parts.shape[0] K ranges;
     A [M, K], W [N, K] bf16, parts [ksplit, M, N] fp32, contiguous device tensors."""
     M, K = A.shape
     ks, _, N = parts.shape
-    _check(lib().sgd_op_linear_split(_dtype_code(A), _p(A), _p(W), _p(bias), _p(parts), parts.stride(0), M, N, K,
-                                     ks, C.c_void_p(_stream_ptr(stream))))
+    _check(lib().sgd_op_linear_split_tile(_dtype_code(A), _p(A), _p(W), _p(bias), _p(parts), parts.stride(0), M, N,
+                                          K, ks, tile, C.c_void_p(_stream_ptr(stream))))
 
 
 def op_attention(q, k, vt, o, B, H, dh, nq, nk, stream=None) -> None:

@@ -847,7 +847,7 @@ extern "C" int sgd_op_linear(int32_t dtype, const void* A, int64_t lda, const vo
                              int32_t act, int32_t gated, int32_t tile, void* hip_stream) {
     if (!A || !W || !out) return fail(SGD_E_ARG, "NULL argument");
     if (dtype != SGD_F32 && dtype != SGD_BF16) return fail(SGD_E_DTYPE, "dtype must be F32 or BF16");
-    if (act < 0 || act > 3 || tile < 0 || tile > kGemmOpTiles) return fail(SGD_E_ARG, "bad act or tile");
+    if (act < 0 || act > 3 || tile < 0 || tile > kGemmTiles) return fail(SGD_E_ARG, "bad act or tile");
     if (gated && dtype != SGD_BF16) return fail(SGD_E_DTYPE, "gated GEMMs are bf16 only");
     GemmArgs g;
     g.A0 = A; g.lda0 = lda; g.B = W; g.ldb = ldw; g.M = M; g.N = gated ? 2 * N : N; g.K = K;
@@ -859,9 +859,10 @@ extern "C" int sgd_op_linear(int32_t dtype, const void* A, int64_t lda, const vo
     return SGD_OK;
 }
 
-extern "C" int sgd_op_linear_split(int32_t dtype, const void* A, const void* W, const float* bias, float* parts,
-                                   int64_t part_stride, int32_t M, int32_t N, int32_t K, int32_t ksplit,
-                                   void* hip_stream) {
+extern "C" int sgd_op_linear_split_tile(int32_t dtype, const void* A, const void* W, const float* bias, float* parts,
+                                        int64_t part_stride, int32_t M, int32_t N, int32_t K, int32_t ksplit,
+                                        int32_t tile, void* hip_stream) {
+    if (tile < 0 || tile > kGemmTiles) return fail(SGD_E_ARG, "bad tile");
     if (!A || !W || !parts) return fail(SGD_E_ARG, "NULL argument");
     if (dtype != SGD_BF16) return fail(SGD_E_DTYPE, "split products are bf16 only");
     if (ksplit < 2 || ksplit > 8) return fail(SGD_E_ARG, "2 <= ksplit <= 8");
@@ -869,15 +870,21 @@ extern "C" int sgd_op_linear_split(int32_t dtype, const void* A, const void* W, 
     g.A0 = A; g.lda0 = K; g.B = W; g.ldb = K; g.M = M; g.N = N; g.K = K; g.ksplit = ksplit;
     EpiParams e;
     e.kind = EP_PARTIAL; e.bias = bias; e.h = parts; e.d = N; e.part_stride = part_stride;
-    if (!gemm_shape_ok(1, g, e)) return fail(SGD_E_SHAPE, "GEMM shape not supported");
-    SGD_HIP_TRY(launch_gemm(1, g, e, (hipStream_t)hip_stream));
+    if (!gemm_shape_ok(1, g, e, tile)) return fail(SGD_E_SHAPE, "GEMM shape not supported");
+    SGD_HIP_TRY(launch_gemm(1, g, e, (hipStream_t)hip_stream, tile));
     return SGD_OK;
+}
+
+extern "C" int sgd_op_linear_split(int32_t dtype, const void* A, const void* W, const float* bias, float* parts,
+                                   int64_t part_stride, int32_t M, int32_t N, int32_t K, int32_t ksplit,
+                                   void* hip_stream) {
+    return sgd_op_linear_split_tile(dtype, A, W, bias, parts, part_stride, M, N, K, ksplit, 0, hip_stream);
 }
 
 extern "C" int sgd_op_heads(int32_t dtype, const void* A, const void* W, const float* bias, void* q, void* k,
                             void* vt, int32_t M, int32_t K, int32_t n_proj, int32_t which0, int32_t ntok, int32_t np,
                             int32_t H, int32_t dh, int32_t rope, int32_t tile, void* hip_stream) {
-    if (tile < 0 || tile > kGemmOpTiles) return fail(SGD_E_ARG, "bad tile");
+    if (tile < 0 || tile > kGemmTiles) return fail(SGD_E_ARG, "bad tile");
     if (!A || !W || (which0 == 0 && !q) || (which0 + n_proj > 1 && !k) || (which0 + n_proj > 2 && !vt))
         return fail(SGD_E_ARG, "NULL argument");
     if (dtype != SGD_F32 && dtype != SGD_BF16) return fail(SGD_E_DTYPE, "dtype must be F32 or BF16");
@@ -897,7 +904,7 @@ extern "C" int sgd_op_heads(int32_t dtype, const void* A, const void* W, const f
 extern "C" int sgd_op_residual(int32_t dtype, const void* A, int64_t lda, const void* W, const float* bias, float* h,
                                float* delta, int32_t delta_mode, const float* gate, int64_t gate_ld, int32_t ntok,
                                int32_t M, int32_t N, int32_t K, int32_t tile, void* hip_stream) {
-    if (tile < 0 || tile > kGemmOpTiles) return fail(SGD_E_ARG, "bad tile");
+    if (tile < 0 || tile > kGemmTiles) return fail(SGD_E_ARG, "bad tile");
     if (!A || !W || !h || (delta_mode && !delta)) return fail(SGD_E_ARG, "NULL argument");
     if (dtype != SGD_F32 && dtype != SGD_BF16) return fail(SGD_E_DTYPE, "dtype must be F32 or BF16");
     if (delta_mode < 0 || delta_mode > 2 || ntok < 1) return fail(SGD_E_ARG, "bad delta_mode or ntok");
@@ -1013,7 +1020,7 @@ extern "C" int sgd_op_conv3x3(const void* A, const void* W, const float* bias, c
                               void* out, float* h, int32_t M, int32_t N, int32_t Cin, int32_t tile, void* hip_stream) {
     if (!A || !W || (!out && !h)) return fail(SGD_E_ARG, "NULL argument");
     if (side < 1 || M < 1 || N < 1 || Cin < 1) return fail(SGD_E_SHAPE, "bad convolution shape");
-    if (tile < 0 || tile > kGemmOpTiles) return fail(SGD_E_ARG, "bad tile");
+    if (tile < 0 || tile > kGemmTiles) return fail(SGD_E_ARG, "bad tile");
     GemmArgs g;
     g.A0 = A; g.lda0 = Cin; g.B = W; g.ldb = 9L * Cin; g.M = M; g.N = N; g.K = 9 * Cin;
     g.conv_side = side; g.conv_c = Cin;

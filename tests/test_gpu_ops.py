@@ -43,8 +43,8 @@ def relmax(x, ref):
     return float(np.max(np.abs(x - ref)) / np.max(np.abs(ref)))
 
 
-TILES = [0, 1, 2, 3, 4, 5]
-TILE_WIDTH = {1: 256, 2: 128, 3: 256, 4: 128, 5: 192}
+TILES = [0, 1, 2, 3, 4, 5, 6, 7]
+TILE_WIDTH = {1: 256, 2: 128, 3: 256, 4: 128, 5: 192, 6: 64, 7: 64}
 
 
 @pytest.mark.parametrize("tile", TILES)
@@ -388,18 +388,22 @@ def test_residual(P, dtype, tile, M, N, K, gated_rows, mode):
         assert np.array_equal(host(td), d0.astype(np.float64))
 
 
+@pytest.mark.parametrize("tile", [0, 2, 4, 6, 7])
 @pytest.mark.parametrize("M,N,K,ks", [(1024, 4096, 12288, 2), (200, 256, 8192, 2), (300, 520, 1024, 4),
-                                      (64, 128, 512, 8)])
-def test_linear_split(P, M, N, K, ks):
+                                      (64, 128, 512, 8), (129, 196, 384, 2)])
+def test_linear_split(P, M, N, K, ks, tile):
     """K ranges of a residual projection (the split MLP output GEMM): part s is the exact-product
     fp32 sum over columns [s K / ks, (s + 1) K / ks), the bias in part 0 only; the LLaDA-8B
-    shape, ragged rows and columns, four and eight ranges."""
+    shape, ragged rows and columns, four and eight ranges, an odd number of k tiles a range, on every
+    tile that takes K ranges and on the automatic choice."""
+    if tile and M == 1024:
+        pytest.skip("the large shape on the automatic choice only")
     rng = np.random.default_rng(M + N + K + ks)
     A = synth.store(rng.standard_normal((M, K)), "bf16")
     W = synth.store(rng.standard_normal((N, K)) / np.sqrt(K), "bf16")
     b = synth.representable(0.1 * rng.standard_normal(N), "f32")
     parts = empty((ks, M, N), "f32")
-    P.op_linear_split(dev(A), dev(W), parts, bias=dev(b))
+    P.op_linear_split(dev(A), dev(W), parts, bias=dev(b), tile=tile)
     got = host(parts)
     a64, w64 = decode(A, "bf16"), decode(W, "bf16")
     kr = K // ks
@@ -416,6 +420,10 @@ def test_linear_split_refuses_bad_ranges(P):
         parts = torch.zeros((ks, 64, 128), dtype=torch.float32, device="cuda")
         with pytest.raises(P.SgdError):
             P.op_linear_split(A, W, parts)
+    parts = torch.zeros((2, 64, 128), dtype=torch.float32, device="cuda")
+    for tile in (-1, 1, 3, 5, 8):  # tiles without a K-range variant, unknown tiles
+        with pytest.raises(P.SgdError):
+            P.op_linear_split(A, W, parts, tile=tile)
 
 
 @pytest.mark.parametrize("rope", [False, True])
@@ -465,27 +473,30 @@ def test_heads_short_dims(P, tile, H, dh):
         assert np.max(np.abs(g - r)) <= 2 ** -7 * np.max(np.abs(r))
 
 
-@pytest.mark.parametrize("M,N,K", [(300, 4608, 192), (1, 2304, 64), (129, 2560, 128), (65, 64, 64), (64, 4096, 576)])
-def test_small_products_bf16(P, M, N, K):
-    """Products the automatic choice gives to 128 x 64 and 64 x 64 tiles, whose two wave groups take
-    alternate k tiles: one, two, three and nine of them (an odd count leaves the second group a tile
-    of zeros), one row, one row past a tile, a single tile; plain, gated and residual epilogues."""
+@pytest.mark.parametrize("tile", [0, 4, 6, 7])
+@pytest.mark.parametrize("M,N,K", [(300, 4608, 192), (1, 2304, 64), (129, 2560, 128), (65, 64, 64), (64, 4096, 576),
+                                   (193, 452, 320)])
+def test_small_products_bf16(P, M, N, K, tile):
+    """Products of few tiles, on each of the small tiles (128 x 128, 128 x 64, 64 x 64), whose two wave
+    groups take alternate k tiles, and on the automatic choice: one, two, three, five and nine k tiles (an
+    odd count leaves the second group a tile of zeros), one row, one row past a tile, a single tile, ragged
+    columns; plain, gated and residual epilogues."""
     rng = np.random.default_rng(M + N + K)
     A = synth.store(rng.standard_normal((M, K)), "bf16")
     W = synth.store(rng.standard_normal((N, K)) / np.sqrt(K), "bf16")
     b = synth.representable(0.1 * rng.standard_normal(N), "bf16")
     z = decode(A, "bf16") @ decode(W, "bf16").T + b
     out = empty((M, N), "bf16")
-    P.op_linear(dev(A), dev(W), out, bias=dev(b))
+    P.op_linear(dev(A), dev(W), out, bias=dev(b), tile=tile)
     assert np.max(np.abs(host(out) - round_bf16(z))) <= 2 ** -7 * np.max(np.abs(z))
     if N % 128 == 0:
         F = N // 2
         out = empty((M, F), "bf16")
-        P.op_linear(dev(A), dev(W), out, bias=dev(b), act=3, gated=True)
+        P.op_linear(dev(A), dev(W), out, bias=dev(b), act=3, gated=True, tile=tile)
         assert relmax(host(out), om.silu(z[:, :F]) * z[:, F:]) <= 1e-2
     h0 = rng.standard_normal((M, N)).astype(np.float32)
     th, td = dev(h0), dev(np.zeros_like(h0))
-    P.op_residual(dev(A), dev(W), th, bias=dev(b), delta=td, delta_mode=1)
+    P.op_residual(dev(A), dev(W), th, bias=dev(b), delta=td, delta_mode=1, tile=tile)
     assert relmax(host(td), z) <= 1e-5 and relmax(host(th), h0 + z) <= 1e-5
 
 

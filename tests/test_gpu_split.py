@@ -1,9 +1,9 @@
-"""GPU parity of the split MLP output GEMM: where one round of 128 x 128 tiles is the best unsplit
-plan of a long-K output GEMM (K >= 8192; the LLaDA-8B shape), the launcher runs it in two K
-ranges into fp32 partial products and the next unit's pre-norm adds them to the stream, unless
-the next unit is frozen or the step stores the unit's cached update.  A LLaDA-shaped stack with
-an 8192-wide MLP takes that path; teacher-forced against the oracle and all-active against the
-unscheduled forward bit for bit."""
+"""GPU parity of the split MLP output GEMM: where two K ranges cost less than the whole product by more
+than their fp32 partials do, the launcher runs it so and the next unit's pre-norm adds the partials to
+the stream, unless the next unit is frozen or the step stores the unit's cached update.  LLaDA-shaped
+stacks with an 8192-wide MLP take that path; teacher-forced against the oracle and all-active against
+the unscheduled forward bit for bit.  (The LLaDA-8B shape itself, on 256 x 128 tiles, is in
+test_gpu_fullsize.py.)"""
 import numpy as np
 import pytest
 
@@ -27,8 +27,7 @@ def P():
 
 @pytest.fixture(scope="module")
 def wide():
-    # 200 tokens x d = 256: the 256 x 8192 output GEMM's best unsplit plan is one round of
-    # 128 x 128 tiles, so it runs as two K ranges of 256 x 128 tiles
+    # 200 tokens x d = 256: sixteen 64 x 64 tiles with 128 k tiles each, halved by two K ranges
     cfg = synth.get_config("llada_mini", F=8192, T=6)
     return cfg, synth.model_weights(cfg), synth.inputs(cfg)
 
@@ -50,6 +49,20 @@ def test_split_output_gemm_teacher_forced(P, wide, granularity):
     print(granularity, "split output GEMM, teacher-forced per-step error", ["%.2e" % e for e in errs])
     assert max(errs) <= TOL["bf16"], errs
     dm.close()
+
+
+def test_split_output_gemm_large_tiles(P):
+    """1030 tokens x d = 1024: 72 tiles of 128 x 128, 144 of them in two K ranges; both steps unscheduled-like
+    (no unit stores an update), so the first unit's output is split at each."""
+    cfg = synth.get_config("llada_mini", N=1030, d=1024, H=8, F=8192, L=2, T=2, prompt_rows=515)
+    w, x = synth.model_weights(cfg), synth.inputs(cfg)
+    dm = P.DeviceModel(cfg, w, x)
+    S = [cfg.T] * cfg.L
+    ref = oracle_trajectory(cfg, w, x, osch.active_mask(np.array(S), cfg.T))
+    got = gpu_teacher_forced(dm, cfg, ref.z, x["z"], P.schedule_from_lifetimes(S, cfg.T))
+    dm.close()
+    errs = [rel_err(g, r) for g, r in zip(got, ref.z)]
+    assert max(errs) <= TOL["bf16"], errs
 
 
 def test_split_output_gemm_all_active_is_unscheduled(P, wide):

@@ -67,7 +67,7 @@ def _conv_case(rng, B, side, cin, cout):
     return decode(synth.store(x, "bf16"), "bf16"), decode(synth.store(w, "bf16"), "bf16")
 
 
-@pytest.mark.parametrize("tile", [0, 2, 4, 5])
+@pytest.mark.parametrize("tile", [0, 2, 4, 5, 6, 7])
 @pytest.mark.parametrize("B,side,cin,cout", [(2, 10, 256, 256), (1, 5, 64, 128), (3, 9, 128, 192)])
 def test_conv3x3(P, tile, B, side, cin, cout):
     """bf16 output of conv + bias + per-sample bias against the oracle's convolution (fp64 on
