@@ -479,9 +479,28 @@ __global__ __launch_bounds__(kTailTY * kTailTX) void tri_tail_kernel(SpectralBat
 }
 
 // Short sides past kSpectralMax (three vectors no longer fit the LDS): the same steps as two kernels,
-// one workgroup for the vectors (w, the next column, the next reflector) and a wide one that applies
-// the rank-2 update and forms the next p, one matrix at a time.
+// one workgroup a matrix for the vectors (w, the next column, the next reflector) and a wide one that
+// applies the rank-2 update and forms the next p, each launched once per step for the whole batch: the
+// vector kernels of all matrices run side by side (24 matrices of 6656 x 6656: 10.7 s, one matrix after
+// another 11.7).
 // work layout (doubles): v[2][nmax], p[nmax], w[nmax], xbuf[nmax], tau[2]
+struct LargeWork {
+    double *A, *diag, *offd, *vs, *p, *w, *xbuf, *scal;
+    long ld;
+    __device__ __forceinline__ double* v(int j) const { return vs + (j & 1) * ld; }
+    __device__ __forceinline__ LargeWork(const SpectralBatch& sb, int b) {
+        double* work = sb.work(b);
+        ld = sb.nmax;
+        A = sb.gram(b);
+        diag = sb.out(b);
+        offd = diag + ld;
+        vs = work;
+        p = work + 2 * ld;
+        w = work + 3 * ld;
+        xbuf = work + 4 * ld;
+        scal = work + 5 * ld;
+    }
+};
 
 constexpr int kHouseThreads = 1024;
 
@@ -509,76 +528,78 @@ __device__ double house(const double* x, int len, double* vout, double* beta_out
 }
 
 // first reflector (step 0): x = A[0][1..n-1] (row 0 == column 0)
-__global__ __launch_bounds__(kHouseThreads) void tri_init_kernel(const double* A, int n, double* v0,
-                                                                 double* scal, double* diag, double* offd) {
+__global__ __launch_bounds__(kHouseThreads) void tri_init_kernel(SpectralBatch sb) {
     __shared__ double red[16];
+    const LargeWork W(sb, blockIdx.x);
     double beta;
-    const double tau = house(A + 1, n - 1, v0, &beta, red);
+    const double tau = house(W.A + 1, sb.jobs[blockIdx.x].n - 1, W.v(0), &beta, red);
     if (threadIdx.x == 0) {
-        scal[0] = tau;
-        diag[0] = A[0];
-        offd[0] = beta;
+        W.scal[0] = tau;
+        W.diag[0] = W.A[0];
+        W.offd[0] = beta;
     }
 }
 
 // p = tau A22 v for step 0 (A22 = A[1:, 1:]); one wave per row
-__global__ __launch_bounds__(256) void tri_symv0_kernel(const double* A, int n, const double* v,
-                                                        const double* scal, double* p) {
-    const int m = n - 1;
+__global__ __launch_bounds__(256) void tri_symv0_kernel(SpectralBatch sb) {
+    const LargeWork W(sb, blockIdx.y);
+    const int n = sb.jobs[blockIdx.y].n, m = n - 1;
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (row >= m) return;
-    const double* ar = A + (long)(1 + row) * spectral_lda(n) + 1;
+    const double* ar = W.A + (long)(1 + row) * spectral_lda(n) + 1;
     double acc = 0.0;
-    for (int c = lane; c < m; c += 64) acc += ar[c] * v[c];
+    for (int c = lane; c < m; c += 64) acc += ar[c] * W.v(0)[c];
     acc = warp_sum(acc);
-    if (lane == 0) p[row] = scal[0] * acc;
+    if (lane == 0) W.p[row] = W.scal[0] * acc;
 }
 
 // Step j: w = p - (tau/2)(p.v) v; the updated column j+1; the next reflector.
-__global__ __launch_bounds__(kHouseThreads) void tri_w_house_kernel(const double* A, int n, int j,
-                                                                    const double* v, double* vnext,
-                                                                    const double* p, double* w, double* xbuf,
-                                                                    double* scal, double* diag, double* offd) {
+__global__ __launch_bounds__(kHouseThreads) void tri_w_house_kernel(SpectralBatch sb, int j) {
     __shared__ double red[16];
+    const LargeWork W(sb, blockIdx.x);
+    const int n = sb.jobs[blockIdx.x].n;
     const int m = n - j - 1;  // size of A22
-    const double tau = scal[j & 1];
+    if (m < 2) return;        // this matrix is done
+    const double *v = W.v(j), *p = W.p;
+    double* const w = W.w;
+    const double tau = W.scal[j & 1];
     double s = 0.0;
     for (int i = threadIdx.x; i < m; i += blockDim.x) s += p[i] * v[i];
     const double pv = block_sum_d(s, red);
     const double k = 0.5 * tau * pv;
     for (int i = threadIdx.x; i < m; i += blockDim.x) w[i] = p[i] - k * v[i];
     __syncthreads();
-    const double* arow = A + (long)(j + 1) * spectral_lda(n) + (j + 1);  // row 0 of A22 (== column 0)
+    const double* arow = W.A + (long)(j + 1) * spectral_lda(n) + (j + 1);  // row 0 of A22 (== column 0)
     if (m == 2) {
         // last step: the trailing 2 x 2 block after its update is the end of T
         if (threadIdx.x == 0) {
-            diag[j + 1] = arow[0] - 2.0 * v[0] * w[0];
-            offd[j + 1] = arow[1] - v[1] * w[0] - w[1] * v[0];
-            diag[j + 2] = A[(long)(j + 2) * spectral_lda(n) + (j + 2)] - 2.0 * v[1] * w[1];
+            W.diag[j + 1] = arow[0] - 2.0 * v[0] * w[0];
+            W.offd[j + 1] = arow[1] - v[1] * w[0] - w[1] * v[0];
+            W.diag[j + 2] = W.A[(long)(j + 2) * spectral_lda(n) + (j + 2)] - 2.0 * v[1] * w[1];
         }
         return;
     }
     // updated column 0 of A22 below the diagonal: x'[i] = A22[1+i][0] - v[1+i] w[0] - w[1+i] v[0]
-    for (int i = threadIdx.x; i < m - 1; i += blockDim.x) xbuf[i] = arow[1 + i] - v[1 + i] * w[0] - w[1 + i] * v[0];
+    for (int i = threadIdx.x; i < m - 1; i += blockDim.x) W.xbuf[i] = arow[1 + i] - v[1 + i] * w[0] - w[1 + i] * v[0];
     __syncthreads();
     double beta;
-    const double taun = house(xbuf, m - 1, vnext, &beta, red);
+    const double taun = house(W.xbuf, m - 1, W.v(j + 1), &beta, red);
     if (threadIdx.x == 0) {
-        diag[j + 1] = arow[0] - 2.0 * v[0] * w[0];
-        offd[j + 1] = beta;
-        scal[(j + 1) & 1] = taun;
+        W.diag[j + 1] = arow[0] - 2.0 * v[0] * w[0];
+        W.offd[j + 1] = beta;
+        W.scal[(j + 1) & 1] = taun;
     }
 }
 
 // Step j: A22[i][c] -= v[i] w[c] + w[i] v[c] for i, c >= 1, and the next p:
 // pnext[i-1] = tau' sum_{c >= 1} A22[i][c] vnext[c-1].  One wave per row.
-__global__ __launch_bounds__(256) void tri_update_kernel(double* A, int n, int j, const double* v,
-                                                         const double* w, const double* vnext, const double* scal,
-                                                         double* pnext) {
-    const int m = n - j - 1;
+__global__ __launch_bounds__(256) void tri_update_kernel(SpectralBatch sb, int j) {
+    const LargeWork W(sb, blockIdx.y);
+    const int n = sb.jobs[blockIdx.y].n, m = n - j - 1;
     const int i = 1 + blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (i >= m) return;
-    double* ar = A + (long)(j + 1 + i) * spectral_lda(n) + (j + 1);
+    if (i >= m || m < 3) return;
+    const double *v = W.v(j), *w = W.w, *vnext = W.v(j + 1);
+    double* ar = W.A + (long)(j + 1 + i) * spectral_lda(n) + (j + 1);
     const double vi = v[i], wi = w[i];
     double acc = 0.0;
     for (int c = 1 + lane; c < m; c += 64) {
@@ -587,23 +608,17 @@ __global__ __launch_bounds__(256) void tri_update_kernel(double* A, int n, int j
         acc += a * vnext[c - 1];
     }
     acc = warp_sum(acc);
-    if (lane == 0) pnext[i - 1] = scal[(j + 1) & 1] * acc;
+    if (lane == 0) W.p[i - 1] = W.scal[(j + 1) & 1] * acc;
 }
 
-static void tridiagonalize_large(const SpectralBatch& sb, int b, int n, hipStream_t st) {
-    double *A = sb.gram(b), *diag = sb.out(b), *offd = diag + sb.nmax, *work = sb.work(b);
-    const long ld = sb.nmax;
-    double* v[2] = {work, work + ld};
-    double *p = work + 2 * ld, *w = work + 3 * ld, *xbuf = work + 4 * ld, *scal = work + 5 * ld;
-    hipLaunchKernelGGL(tri_init_kernel, dim3(1), dim3(kHouseThreads), 0, st, A, n, v[0], scal, diag, offd);
-    hipLaunchKernelGGL(tri_symv0_kernel, dim3((n - 1 + 3) / 4), dim3(256), 0, st, A, n, v[0], scal, p);
-    for (int j = 0; j <= n - 3; ++j) {
-        const int m = n - j - 1;
-        hipLaunchKernelGGL(tri_w_house_kernel, dim3(1), dim3(kHouseThreads), 0, st, A, n, j, v[j & 1],
-                           v[(j + 1) & 1], p, w, xbuf, scal, diag, offd);
-        if (m > 2)
-            hipLaunchKernelGGL(tri_update_kernel, dim3((m - 1 + 3) / 4), dim3(256), 0, st, A, n, j, v[j & 1], w,
-                               v[(j + 1) & 1], scal, p);
+// every matrix of the batch past kSpectralMax, nb the largest short side
+static void tridiagonalize_large(const SpectralBatch& sb, int nb, hipStream_t st) {
+    hipLaunchKernelGGL(tri_init_kernel, dim3(sb.count), dim3(kHouseThreads), 0, st, sb);
+    hipLaunchKernelGGL(tri_symv0_kernel, dim3((nb - 1 + 3) / 4, sb.count), dim3(256), 0, st, sb);
+    for (int j = 0; j <= nb - 3; ++j) {
+        const int m = nb - j - 1;
+        hipLaunchKernelGGL(tri_w_house_kernel, dim3(sb.count), dim3(kHouseThreads), 0, st, sb, j);
+        if (m > 2) hipLaunchKernelGGL(tri_update_kernel, dim3((m - 1 + 3) / 4, sb.count), dim3(256), 0, st, sb, j);
     }
 }
 
@@ -695,7 +710,7 @@ hipError_t launch_spectra(const SpectralBatch& sb, const SpectralJob* host_jobs,
     }
     hipLaunchKernelGGL(gram_kernel, dim3(tiles), dim3(256), 0, st, sb);
     if (nb > kSpectralMax) {
-        for (int b = 0; b < sb.count; ++b) tridiagonalize_large(sb, b, host_jobs[b].n, st);
+        tridiagonalize_large(sb, nb, st);
     } else {
         if (3 * (size_t)(nb + 2) * sizeof(double) > 64 * 1024)
             for (auto f : {(const void*)tri_step_kernel<true>, (const void*)tri_step_kernel<false>}) {

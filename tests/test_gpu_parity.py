@@ -136,6 +136,20 @@ def test_matrix_stats_large(P, n):
     assert got[5] == pytest.approx(lam[0], rel=1e-13)
 
 
+def test_large_matrices_share_a_batch(P):
+    """Short sides past the LDS limit are reduced side by side, one launch per step for all: matrices of
+    different sizes and storage types in one batch, each with the bits of a batch of its own."""
+    import torch
+    torch.manual_seed(6656)
+    mats = [torch.randn(6720, 6656, device="cuda").bfloat16(), torch.randn(6605, 6700, device="cuda"),
+            torch.randn(6720, 6720, device="cuda").bfloat16()]
+    got = P.schedule_build([[("conv", m) for m in mats]], [64], 10, budget_pct=50).mat_stats
+    for i, m in enumerate(mats):
+        assert np.array_equal(got[i], P.matrix_stats(m, eta=1e-6)), i
+        assert got[i, 2] == pytest.approx(float((m.double() ** 2).sum()), rel=1e-12)
+        assert got[i, 0] + got[i, 1] == pytest.approx(got[i, 2], rel=1e-12)
+
+
 @pytest.mark.parametrize("name", MINIS + ["tiny"])
 def test_schedule_bit_exact(P, name):
     cfg, w, x = workload(name)
