@@ -760,15 +760,21 @@ static void launch_attention_bf16(const AttnArgs& a, hipStream_t st) {
     const int nkb = (a.nk + 63) / 64;
     // Few query groups and more than one key block: split the keys between two wave halves.  The split
     // kernel's LDS (two buffers per half) lets one workgroup of head dims above 64 onto a CU, two of
-    // smaller ones: 64-query workgroups where they are one round of the CUs, else 128-query ones (dh 128,
-    // 24 heads of 1024 keys: 23.6 us against 41.7; dh 72, 384 groups of 256 keys: 15.3 against 20.4).
-    // Small heads with short key ranges gain only in the first case (dh 64, 256 keys: 160 groups 7.4 us
-    // against 11.0 unsplit; 640 groups of 1024 queries and 77 keys 17.3 against 16.4), long key ranges
-    // always.
+    // smaller ones.  64-query workgroups where they are one round of the CUs (dh 64, 160 groups of 256 keys
+    // 7.4 us against 11.0 unsplit; 330 heads of 64 queries and 77 keys 6.8 against 8.2, 128-query ones 9.8).
+    // Else 128-query ones: for long key ranges always; for short ones only of wide heads (dh 64 gains
+    // nothing: 640 groups of 1024 queries and 77 keys 17.3 against 16.4), while they take no more rounds
+    // of one per CU than the unsplit 64-query workgroups take of two (dh 72, 384 groups of 256 keys: 15.3
+    // against 20.4; dh 128, 175 heads of 256 queries and keys 25.2 against 28.6, but 330 heads of 64 queries,
+    // two rounds against one, 20.2 against 16.6).  With four key blocks heads of
+    // up to 96 dims win even so (1.04-1.3), and with two, heads above 96 lose past two rounds (0.93-1.09).
     constexpr bool wide = DH > 64;
-    const bool round64 = (long)((a.nq + 63) / 64) * BH <= (wide ? 256 : 512);
-    if (qg128 < 1024 && nkb >= 2 && (nkb >= 8 || wide || round64)) {
-        if (wide ? !round64 : qg128 >= 256)
+    const long qg64 = (long)((a.nq + 63) / 64) * BH;
+    const bool round64 = wide ? qg64 <= 256 && qg128 < 256 : qg64 <= 512;
+    const long r128 = (qg128 + 255) / 256, r64 = (qg64 + 511) / 512;
+    const bool wide_split = r128 <= r64 ? DH <= 96 || nkb > 2 || r64 <= 2 : DH <= 96 && nkb >= 4;
+    if (qg128 < 1024 && nkb >= 2 && (nkb >= 8 || round64 || (wide && wide_split))) {
+        if (!round64)
             hipLaunchKernelGGL((attn_split_bf16_kernel<DH, 4>), dim3((a.nq + 127) / 128, BH), dim3(512), 0, st, a, sl2);
         else
             hipLaunchKernelGGL((attn_split_bf16_kernel<DH, 2>), dim3((a.nq + 63) / 64, BH), dim3(256), 0, st, a, sl2);

@@ -506,6 +506,13 @@ def test_small_products_bf16(P, M, N, K, tile):
                                           # last of the 64-query split grids and the first past them
                                           (2, 64, 128, 128, 72), (2, 43, 130, 130, 72), (8, 16, 200, 100, 64),
                                           (2, 43, 180, 70, 64),
+                                          # 256 heads of 64 queries (128-query groups), wide heads whose
+                                          # 128-query workgroups take a round more than the unsplit ones (two
+                                          # key blocks unsplit, four split) and no more, narrow heads of long
+                                          # key ranges at the last 64-query grid and past it
+                                          (8, 32, 64, 77, 72), (8, 33, 60, 77, 128), (8, 33, 60, 250, 72),
+                                          (8, 33, 60, 250, 128), (4, 70, 190, 130, 128), (8, 64, 50, 520, 64),
+                                          (9, 57, 50, 520, 64),
                                           # last of the fp32 16-query grids and the first past them
                                           (2, 32, 160, 96, 32), (1, 107, 90, 200, 24)])
 def test_attention_few_queries(P, dtype, B, H, nq, nk, dh):
