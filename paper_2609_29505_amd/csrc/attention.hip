@@ -811,9 +811,15 @@ hipError_t launch_attention(int dtype, const AttnArgs& a, hipStream_t st) {
     } else {
         const float sl2 = (float)(1.4426950408889634 / sqrt((double)a.dh));
         dim3 grid((a.nq + 31) / 32, BH), block(4 * 64);
-        // 16-query workgroups while the 32-query ones are few (32 of them, 256 keys, dh 64: 8.2 us
-        // against 12.3; 312: 26.6 against 29.5; 512: 33.6 against 27.4)
-        if ((long)grid.x * BH <= 320) {
+        // 16-query workgroups while they are one round of one per CU (32 workgroups of 32 queries, 256 keys,
+        // dh 64: 8.2 us against 12.3; at two per CU, 160 workgroups of 32 queries, 100 keys, dh 72: 11.8
+        // against 10.4).  Longer key ranges of up to 96 dims also at two per CU (156 workgroups of 32 queries,
+        // 400 keys, dh 72 23.5 against 26.5, but dh 128 40.0 against 39.2), and where the 32-query ones
+        // just start a second round (286 of them, 700 keys, dh 64 37.9 against 42.7, dh 128 86 against
+        // 108; 400 of them lose by a tenth)
+        const long wg32 = (long)grid.x * BH, wg16 = (long)((a.nq + 15) / 16) * BH;
+        const bool second = wg32 > 256 && wg32 <= 320 && a.nk > 192;
+        if (wg16 <= 256 || second || (wg32 <= 256 && a.dh <= 96 && a.nk > 128)) {
             grid.x = (a.nq + 15) / 16;
             if (a.dh <= 32) hipLaunchKernelGGL(attn_f32_small_kernel<32>, grid, dim3(512), 0, st, a, sl2);
             else if (a.dh <= 64) hipLaunchKernelGGL(attn_f32_small_kernel<64>, grid, dim3(512), 0, st, a, sl2);

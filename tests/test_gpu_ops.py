@@ -513,8 +513,11 @@ def test_small_products_bf16(P, M, N, K, tile):
                                           (8, 32, 64, 77, 72), (8, 33, 60, 77, 128), (8, 33, 60, 250, 72),
                                           (8, 33, 60, 250, 128), (4, 70, 190, 130, 128), (8, 64, 50, 520, 64),
                                           (9, 57, 50, 520, 64),
-                                          # last of the fp32 16-query grids and the first past them
-                                          (2, 32, 160, 96, 32), (1, 107, 90, 200, 24)])
+                                          # last of the fp32 16-query grids and the first past them (one
+                                          # round; two for longer key ranges; the 32-query second round)
+                                          (2, 32, 160, 96, 32), (1, 107, 90, 200, 24), (1, 64, 64, 100, 72),
+                                          (1, 65, 64, 100, 72), (1, 64, 128, 129, 72), (1, 64, 128, 128, 72),
+                                          (2, 32, 160, 193, 128), (2, 32, 161, 193, 128)])
 def test_attention_few_queries(P, dtype, B, H, nq, nk, dh):
     test_attention(P, dtype, B, H, nq, nk, dh)
 
