@@ -237,17 +237,24 @@ hipError_t launch_gemm(int dtype, const GemmArgs& g, const EpiParams& e, hipStre
     const int nt_m = (g.M + 31) / 32, nt_n = g.N / 32;
     // What a launch takes is a start plus its round trips of loads per CU.  16 x 16 tiles while two
     // of them a CU cover the product (256 x 256 x 1024: 6.4 us against 11.8; 400 x 512 x 512, 208 tiles
-    // of 32 x 32: 10.0 against 7.8).  Past that 32 x 32 tiles with eight waves (256 x 1024 x 256 5.2 us,
-    // 6.1 with four; 1200 x 4096 x 512 95, 103), sixteen for long chains (1200 x 512 x 4096 112 and 118).
+    // of 32 x 32: 10.0 against 7.8).  Past that 32 x 32 tiles: eight waves up to one tile a CU (256 x 1024
+    // x 256 5.2 us, four waves 6.1), four where K is deep (224 x 640 x 2560 28.2, sixteen 29.4).  With more
+    // tiles the waves of several share a CU, and a pass of 32 values of K a wave that K does not fill
+    // costs more than more waves give: four (400 x 1536 x 384 15.6, eight 17.0), eight for many tiles
+    // whose K is whole passes (1040 x 1536 x 512 37.8, four 40.0), sixteen for many tiles of deep
+    // K (912 x 1152 x 4608 215, four 245; but 416 x 1152 x 2304, 468 tiles, 48.2, four 45.9).
     if (nt_m * nt_n <= 128) {
         const dim3 grid(((g.M + 15) / 16) * (g.N / 16));
         if (g.K > 256) hipLaunchKernelGGL(gemm_f32_small_kernel<8>, grid, dim3(512), 0, st, g, e);
         else hipLaunchKernelGGL(gemm_f32_small_kernel<4>, grid, dim3(256), 0, st, g, e);
         return hipGetLastError();
     }
-    const dim3 grid(nt_m * nt_n);
-    if (g.K >= 2048) hipLaunchKernelGGL(gemm_f32_kernel<16>, grid, dim3(1024), 0, st, g, e);
-    else hipLaunchKernelGGL(gemm_f32_kernel<8>, grid, dim3(512), 0, st, g, e);
+    const int n = nt_m * nt_n;
+    const dim3 grid(n);
+    const int nw = g.K >= 2048 ? (n >= 512 ? 16 : 4) : n <= 256 || (n >= 1024 && g.K % 256 == 0) ? 8 : 4;
+    if (nw == 16) hipLaunchKernelGGL(gemm_f32_kernel<16>, grid, dim3(1024), 0, st, g, e);
+    else if (nw == 8) hipLaunchKernelGGL(gemm_f32_kernel<8>, grid, dim3(512), 0, st, g, e);
+    else hipLaunchKernelGGL(gemm_f32_kernel<4>, grid, dim3(256), 0, st, g, e);
     return hipGetLastError();
 }
 

@@ -522,10 +522,11 @@ def test_attention_few_queries(P, dtype, B, H, nq, nk, dh):
     test_attention(P, dtype, B, H, nq, nk, dh)
 
 
-# 16 x 16 tiles (up to 128 tiles of 32 x 32), 32 x 32 tiles with eight and sixteen waves; K of fewer
+# 16 x 16 tiles (up to 128 tiles of 32 x 32), 32 x 32 tiles with four, eight and sixteen waves; K of fewer
 # units than waves, ragged K passes and rows
 @pytest.mark.parametrize("M,N,K", [(1, 64, 16), (33, 128, 80), (255, 512, 272), (250, 512, 1040), (260, 512, 48),
-                                   (257, 1024, 2064), (31, 8256, 144)])
+                                   (257, 1024, 2064), (31, 8256, 144), (510, 1024, 2048), (512, 1024, 1024),
+                                   (1000, 1024, 256), (1025, 1024, 240)])
 def test_small_products_f32(P, M, N, K):
     rng = np.random.default_rng(M + N + K)
     A = rng.standard_normal((M, K)).astype(np.float32)
