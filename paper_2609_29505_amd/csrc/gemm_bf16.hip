@@ -8,6 +8,7 @@
 //
 // Epilogue.  Straight from the accumulators: the loader orders the weight rows so that what a
 // store or a pair of columns needs sits in one lane (see the epilogue).
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -760,8 +761,8 @@ __global__ __launch_bounds__(C::NT, 2) void gemm_pp_kernel(GemmArgs g, EpiParams
 // MFMAs.  At the end the groups exchange halves of their sums through LDS and each finishes its own
 // half of the rows (64-row tiles: group 0 finishes all).
 //
-// A step's length is the LDS's: 128 x 128 tiles take 0.38 us per 64-deep k tile on their own (64 KB
-// of fragment reads, 32 KB of loads landing at 64 bytes a cycle), 64 x 64 0.18.  The 128 x 128
+// A step's length is the LDS's: a 128 x 128 tile takes 0.37 us per 64-deep k tile on its own (64 KB
+// of fragment reads, 32 KB of loads landing at 64 bytes a cycle), 64 x 64 0.17.  The 128 x 128
 // kernel with register-staged loads that it replaced took 0.37-0.46.  Residual products, before ->
 // after (weights cold): 200 x 4096 x 12288 100 -> 46 us, 512 x 1152 x 4608 34 -> 19, 625 x 1280 x 5120
 // 40 -> 21; 3 x 3 convolution on 625 positions of 1280 channels 100 -> 38.
@@ -985,10 +986,12 @@ using T64x64 = PKCfg<64, 64, 4>;
 
 // tile id -> block shape and what a tile takes: us per 64-deep k tile with the chip nearly empty and
 // with every CU busy, and us for its start and epilogue.  Fitted to 62 products (64 to 8256 rows, 640
-// to 24576 columns, K 640 to 12288, weights cold) timed with every tile; the choice made from
-// them is within 0.2 % of the fastest tile on average and 7 % at worst.  An empty chip is bound by
-// the LDS (fragment reads at ~200 bytes and direct loads at 64 bytes a cycle), a full one by power
-// and the memory side.
+// to 24576 columns, K 640 to 12288, weights cold) timed with every tile, where the choice made from
+// them is within 0.2 % of the fastest tile on average and 7 % at worst; over 480 other products (1 to
+// 8300 rows, 256 to 24576 columns, K 256 to 12288) it is within 2.2 % on average and 27 % at worst.  They rank
+// tiles and are no model of a launch's time: small cold products take up to twice the cost (2 x 2048 x
+// 8192 on 64 x 64 tiles 28.6 us, cost 15.2), and t0 of the small tiles is below what one takes on its own
+// (0.37 us for 128 x 128, 0.25 for 128 x 64, 0.17 for 64 x 64, bound by the LDS).
 struct Shape { int bm, bn; double t0, t1, fix; };
 Shape tile_shape(int tile) {
     switch (tile) {
@@ -1003,32 +1006,45 @@ Shape tile_shape(int tile) {
     }
 }
 // a second launch for the tail rows
-constexpr double kTailLaunch = 4.0;
+constexpr double kTailLaunch = 5.5;
 }  // namespace
 
 static bool conv_tile(int tile) { return tile == 2 || (tile >= 4 && tile <= 7); }
 
 // Time (us) of one launch of `tile` over `rows` rows: one workgroup per CU, so n tiles take n / 256
 // full rounds and a last one whose k tiles are faster the emptier it is.  Infinite when the epilogue
-// cannot use the tile.
+// cannot use the tile.  Past one round, one or two row tiles are bound by the weights, read once from HBM at
+// kHbm in all and kCuHbm a CU (64 x 24576 x 4096: 384 tiles of 64 x 64 52 us, 192 of 128 x 128 45).
+// And a grid that the XCDs do not divide keeps no neighbouring tiles on one XCD (tile_order.h): where the
+// activations are past two L2s, tiles of up to 128 columns, which read the most operand bytes, pay for it (2560 x
+// 2560 weights, 256 x 128 tiles: 7680 rows, 600 tiles, 123 us, 7936, 620 tiles, 162).
+constexpr double kHbm = 5e6, kCuHbm = 25e3;  // bytes a us
+constexpr double kUneven = 1.2;
 static double tile_cost(int tile, long rows, const GemmArgs& g, const EpiParams& e, int ks = 1) {
     const Shape s = tile_shape(tile);
     if (!s.bm) return 1e300;
     if (g.conv_side > 0 && !conv_tile(tile)) return 1e300;
     if (e.kind == EP_GATED && g.N % s.bn) return 1e300;
-    const long tiles = ((rows + s.bm - 1) / s.bm) * ((g.N + s.bn - 1) / s.bn) * ks;
+    const long nm = (rows + s.bm - 1) / s.bm, nn = (g.N + s.bn - 1) / s.bn, tiles = nm * nn * ks;
     const long full = tiles / 256, rem = tiles % 256;
     const double kt = g.K / (64.0 * ks);
-    double t = full * (kt * s.t1 + s.fix);
-    if (rem) t += kt * (s.t0 + (s.t1 - s.t0) * (double)rem / 256.0) + s.fix;
-    return t;
+    auto round = [&](long n) {  // n workgroups side by side
+        double t = s.t0 + (s.t1 - s.t0) * (double)n / 256.0;
+        if (full && nm <= 2) t = std::max(t, s.bn * 128.0 / nm / std::min(kCuHbm, kHbm / (double)n));
+        return kt * t + s.fix;
+    };
+    double t = full * round(256);
+    if (rem) t += round(rem);
+    return (nm * nn) % kXcds && s.bn <= 128 && rows * g.K * 2 > (8L << 20) ? t * kUneven : t;
 }
 
 // Automatic choice: the tile with the least cost (200 x 4096 x 12288: 64 x 64 tiles, 256 of them, 45 us
 // against 99 with 64 of 128 x 128; 1024 x 4096 x 4096: one round of 128 x 128).  When the rows leave a
 // short tail past the last whole 256-row tile (U-ViT: 32 x 258 = 8256 = 32 x 256 + 64 rows), the tail
 // can go to a second launch of small tiles, so the main launch fills whole rounds instead of starting
-// a third one for 64 rows (8256 x 4096 x 1024: 90 us against 100).
+// a third one for 64 rows (8256 x 4096 x 1024: 90 us against 100).  The tail reads the weights once more
+// (545 x 15360 x 2560: 62 us split, 52 on 256 x 192 tiles; 1088 x 7680 x 2560 64 and 59; but 1298 x 12288
+// x 4096 135 and 166).
 GemmPlan gemm_bf16_plan(const GemmArgs& g, const EpiParams& e) {
     GemmPlan best{1, g.M, 0};
     double best_t = 1e300;
@@ -1043,8 +1059,8 @@ GemmPlan gemm_bf16_plan(const GemmArgs& g, const EpiParams& e) {
             const double tm = tile_cost(tile, g.M - tail, g, e);
             for (int tt = 1; tt <= kGemmTiles; ++tt) {
                 if (tile_shape(tt).bm > 128) continue;
-                const double t = tm + tile_cost(tt, tail, g, e) + kTailLaunch;
-                if (t < best_t * 0.97) { best_t = t; best = GemmPlan{tile, g.M - tail, tt}; }
+                const double t = tm + std::max(tile_cost(tt, tail, g, e), 2.0 * g.N * g.K / kHbm) + kTailLaunch;
+                if (t < best_t * 0.99) { best_t = t; best = GemmPlan{tile, g.M - tail, tt}; }
             }
         }
     }
