@@ -369,7 +369,7 @@ int run_step(sgd_model* m, void* state, int step, const StepPlan& plan, const sg
     // token written over the state's)
     const float* hs = (const float*)state;
     if (uvit) {
-        S.run(SGD_K_STATE, [&] { return launch_stream_init((const float*)state, h, d.B, N, dd, 1, t, S.st); });
+        S.run(SGD_K_STATE, [&] { return launch_stream_init((const float*)state, h, d.B, N, dd, t, S.st); });
         hs = h;
     }
     if (dit || unet)

@@ -144,33 +144,27 @@ __device__ __forceinline__ float temb(float t, int k, int dim) {
     return (float)(k < half ? cos(arg) : sin(arg));
 }
 
-__global__ __launch_bounds__(256) void stream_init_kernel(const float* z, float* h, int B, int N, int d,
-                                                          int time_token, float t) {
+__global__ __launch_bounds__(256) void stream_init_kernel(const float* z, float* h, int B, int N, int d, float t) {
     const long n4 = (long)B * N * d / 4;
     for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n4; i += (long)gridDim.x * 256) {
         float4 v = ((const float4*)z)[i];
-        if (time_token) {
-            const long e = i * 4;
-            const long tok = (e / d) % N;
-            if (tok == 0) {
-                const int c = (int)(e % d);
-                v.x = temb(t, c, d);
-                v.y = temb(t, c + 1, d);
-                v.z = temb(t, c + 2, d);
-                v.w = temb(t, c + 3, d);
-            }
+        const long e = i * 4;
+        if ((e / d) % N == 0) {
+            const int c = (int)(e % d);
+            v.x = temb(t, c, d);
+            v.y = temb(t, c + 1, d);
+            v.z = temb(t, c + 2, d);
+            v.w = temb(t, c + 3, d);
         }
         ((float4*)h)[i] = v;
     }
 }
 
-hipError_t launch_stream_init(const float* z, float* h, int B, int N, int d, int time_token, float t,
-                              hipStream_t st) {
+hipError_t launch_stream_init(const float* z, float* h, int B, int N, int d, float t, hipStream_t st) {
     const long n4 = (long)B * N * d / 4;
     long blocks = (n4 + 255) / 256;
     if (blocks > 8192) blocks = 8192;
-    hipLaunchKernelGGL(stream_init_kernel, dim3((unsigned)blocks), dim3(256), 0, st, z, h, B, N, d,
-                       time_token, t);
+    hipLaunchKernelGGL(stream_init_kernel, dim3((unsigned)blocks), dim3(256), 0, st, z, h, B, N, d, t);
     return hipGetLastError();
 }
 

@@ -18,10 +18,6 @@
 
 namespace sgd {
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* base, unsigned bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
-}
-
 // Rotary head projections: the q and k product columns of each head are taken in the order
 // (0, dh/2, 1, dh/2 + 1, ...), so the two dims of every rotary pair are adjacent columns and a
 // block tile of any even width holds whole pairs.  Column n of the product is weight row (and
@@ -1066,8 +1062,6 @@ GemmPlan gemm_bf16_plan(const GemmArgs& g, const EpiParams& e) {
     }
     return best;
 }
-
-int gemm_bf16_auto_tile(const GemmArgs& g, const EpiParams& e) { return gemm_bf16_plan(g, e).tile; }
 
 // Tiles of a product in K ranges (EP_PARTIAL)
 static bool split_tile(int tile) { return tile == 2 || tile == 4 || tile == 6 || tile == 7; }

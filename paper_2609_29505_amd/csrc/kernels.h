@@ -65,7 +65,6 @@ hipError_t launch_gemm(int dtype, const GemmArgs& g, const EpiParams& e, hipStre
 bool gemm_shape_ok(int dtype, const GemmArgs& g, const EpiParams& e, int tile = 0);
 hipError_t launch_gemm_bf16(const GemmArgs& g, const EpiParams& e, hipStream_t st, int tile);
 bool gemm_bf16_shape_ok(const GemmArgs& g, const EpiParams& e, int tile);
-int gemm_bf16_auto_tile(const GemmArgs& g, const EpiParams& e);
 // automatic tiling: rows [0, m_split) with `tile`, rows [m_split, M) (if any) with tail_tile
 struct GemmPlan { int tile, m_split, tail_tile; };
 GemmPlan gemm_bf16_plan(const GemmArgs& g, const EpiParams& e);
@@ -121,9 +120,8 @@ struct FrozenRun {
 };
 hipError_t launch_frozen_run(const FrozenRun& f, hipStream_t st);
 
-// h = z; U-ViT: token 0 of every sample = sinusoidal embedding of t
-hipError_t launch_stream_init(const float* z, float* h, int B, int N, int d, int time_token, float t,
-                              hipStream_t st);
+// U-ViT: h = z with token 0 of every sample the sinusoidal embedding of t
+hipError_t launch_stream_init(const float* z, float* h, int B, int N, int d, float t, hipStream_t st);
 // z = alpha z - beta h on rows [r0, r1) of every sample
 hipError_t launch_state_update(float* z, const float* h, int B, int N, int d, int r0, int r1,
                                float alpha, float beta, hipStream_t st);
