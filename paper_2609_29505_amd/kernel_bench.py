@@ -10,7 +10,9 @@ launch streams its weights from HBM, as the step does (each unit has its own wei
 default one weight matrix is reused and stays in the 256 MB Infinity Cache.  --copy-mib appends a device-to-device copy of that many MiB, a plain copy of known
 size that calibrates the FETCH_SIZE / WRITE_SIZE counters of a rocprofv3 --pmc pass run over
 the same command.  Kernels: gemm_qkv, gemm_o, gemm_w1, gemm_w2, gemm_w2_split (two K ranges
-of fp32 partials), attn, frozen (a run of --frozen-r cached updates).
+of fp32 partials), attn, frozen (a run of --frozen-r cached updates).  --tile runs a GEMM on a
+fixed block tile (numbered as in sgd_ops.h; 0, the default, is the automatic choice), --rows with
+that many rows of one sample instead of the workload's.
 """
 from __future__ import annotations
 
@@ -31,6 +33,8 @@ def main() -> int:
     ap.add_argument("--frozen-r", type=int, default=4)
     ap.add_argument("--copy-mib", type=int, default=0)
     ap.add_argument("--cold", action="store_true")
+    ap.add_argument("--tile", type=int, default=0)
+    ap.add_argument("--rows", type=int, default=0)
     args = ap.parse_args()
 
     import torch
@@ -45,6 +49,9 @@ def main() -> int:
     dev = "cuda"
     bf = torch.bfloat16
     M, d, F, H, dh, N, B = cfg.M, cfg.d, cfg.F, cfg.H, cfg.dh, cfg.N, cfg.B
+    if args.rows:
+        M, N, B = args.rows, args.rows, 1
+    tile = args.tile
     np_ = (N + 63) // 64 * 64
 
     def rnd(*shape, scale=1.0, dtype=bf):
@@ -69,25 +76,25 @@ def main() -> int:
         n1 = 2 * F if cfg.gated else F
         A, W, out = rnd(M, d), weights(n1, d, scale=d ** -0.5), torch.empty(M, F, device=dev, dtype=bf)
         act = {"llada": 3, "dit": 2}.get(cfg.arch, 1)
-        fn = lambda: P.op_linear(A, W(), out, act=act, gated=cfg.gated)  # noqa: E731
+        fn = lambda: P.op_linear(A, W(), out, act=act, gated=cfg.gated, tile=tile)  # noqa: E731
         flop = 2.0 * M * n1 * d
     elif k == "gemm_qkv":
         A, W = rnd(M, d), weights(3 * d, d, scale=d ** -0.5)
         q = torch.empty(B * H, np_, dh, device=dev, dtype=bf)
         kk = torch.empty_like(q)
         vt = torch.empty(B * H, dh, np_, device=dev, dtype=bf)
-        fn = lambda: P.op_heads(A, W(), q, kk, vt, 3, 0, N, H, dh, rope=cfg.arch == "llada")  # noqa: E731
+        fn = lambda: P.op_heads(A, W(), q, kk, vt, 3, 0, N, H, dh, rope=cfg.arch == "llada", tile=tile)  # noqa: E731
         flop = 2.0 * M * 3 * d * d
     elif k in ("gemm_o", "gemm_w2"):
         kd = d if k == "gemm_o" else F
         A, W, h = rnd(M, kd), weights(d, kd, scale=kd ** -0.5), torch.randn(M, d, device=dev)
-        fn = lambda: P.op_residual(A, W(), h)  # noqa: E731
+        fn = lambda: P.op_residual(A, W(), h, tile=tile)  # noqa: E731
         flop = 2.0 * M * d * kd
     elif k == "gemm_w2_split":
         # the MLP output GEMM in two K ranges of fp32 partial products (the step's split path)
         A, W = rnd(M, F), weights(d, F, scale=F ** -0.5)
         parts = torch.empty(2, M, d, device=dev)
-        fn = lambda: P.op_linear_split(A, W(), parts)  # noqa: E731
+        fn = lambda: P.op_linear_split(A, W(), parts, tile=tile)  # noqa: E731
         flop = 2.0 * M * d * F
     elif k == "attn":
         q = rnd(B * H, np_, dh)

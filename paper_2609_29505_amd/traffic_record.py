@@ -4,7 +4,7 @@
         python3 paper_2609_29505_amd/kernel_bench.py --workload llada --kernel gemm_w1 --reps 5 --cold --copy-mib 256
     rocprofv3 --pmc WRITE_SIZE --output-format csv -d <dir>/write -o p -- <same command>
     python -m paper_2609_29505_amd.traffic_record --fetch <dir>/fetch/p_counter_collection.csv \\
-        --write <dir>/write/p_counter_collection.csv --kernel gemm_bf16_kernel --copy-mib 256 \\
+        --write <dir>/write/p_counter_collection.csv --kernel gemm_p --copy-mib 256 \\
         --source paper_2609_29505_amd/csrc/gemm_bf16.hip --algorithmic-bytes <B> --out profiles/<k>_<w>_traffic.json
 
 FETCH_SIZE and WRITE_SIZE (KiB per dispatch) count traffic below the L2.  --group N sums
