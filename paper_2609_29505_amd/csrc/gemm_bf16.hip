@@ -981,22 +981,23 @@ using T128x64 = PKCfg<128, 64, 3>;
 using T64x64 = PKCfg<64, 64, 4>;
 
 // tile id -> block shape and what a tile takes: us per 64-deep k tile with the chip nearly empty and
-// with every CU busy, and us for its start and epilogue.  Fitted to 62 products (64 to 8256 rows, 640
-// to 24576 columns, K 640 to 12288, weights cold) timed with every tile, where the choice made from
-// them is within 0.2 % of the fastest tile on average and 7 % at worst; over 480 other products (1 to
-// 8300 rows, 256 to 24576 columns, K 256 to 12288) it is within 2.2 % on average and 27 % at worst.  They rank
-// tiles and are no model of a launch's time: small cold products take up to twice the cost (2 x 2048 x
-// 8192 on 64 x 64 tiles 28.6 us, cost 15.2), and t0 of the small tiles is below what one takes on its own
-// (0.37 us for 128 x 128, 0.25 for 128 x 64, 0.17 for 64 x 64, bound by the LDS).
+// with every CU busy, and us for its start and epilogue.  Fitted to 690 products (1 to 8300 rows, 256 to
+// 49152 columns, K 256 to 12288, weights cold) timed with every tile, where the choice made from them is
+// within 0.3 % of the fastest tile on average and 23 % at worst (742 x 5376 x 1024, gated: 20.4 us, 16.6);
+// fitted to either half of them, within 0.6 % on the other's average.  The values before them, from 62
+// products, chose 1.5 % slower on average (6592 x 4096 x 512, gated: 45 us, now 37.5; 896 x 384 x 384: 8.1,
+// now 6.8).  They rank tiles and are no model of a launch's time: small cold products take up to twice the
+// cost (2 x 2048 x 8192 on 64 x 64 tiles 28.6 us, cost 15.2), and t0 of two small tiles is below what one
+// takes on its own (0.37 us for 128 x 128, 0.17 for 64 x 64, bound by the LDS).
 struct Shape { int bm, bn; double t0, t1, fix; };
 Shape tile_shape(int tile) {
     switch (tile) {
-        case 1: return {256, 256, 0.87, 1.5, 7.5};
-        case 2: return {256, 128, 0.56, 0.89, 2.7};
-        case 3: return {128, 256, 0.65, 0.97, 1.9};
+        case 1: return {256, 256, 0.74, 1.5, 7.5};
+        case 2: return {256, 128, 0.58, 0.89, 2.7};
+        case 3: return {128, 256, 0.73, 0.97, 1.9};
         case 4: return {128, 128, 0.29, 0.59, 2.1};
-        case 5: return {256, 192, 0.78, 1.3, 4.9};
-        case 6: return {128, 64, 0.18, 0.38, 1.7};
+        case 5: return {256, 192, 0.61, 1.3, 4.9};
+        case 6: return {128, 64, 0.30, 0.41, 1.9};
         case 7: return {64, 64, 0.10, 0.245, 2.4};
         default: return {0, 0, 0.0, 0.0, 0.0};
     }
@@ -1010,7 +1011,9 @@ static bool conv_tile(int tile) { return tile == 2 || (tile >= 4 && tile <= 7); 
 // Time (us) of one launch of `tile` over `rows` rows: one workgroup per CU, so n tiles take n / 256
 // full rounds and a last one whose k tiles are faster the emptier it is.  Infinite when the epilogue
 // cannot use the tile.  Past one round, one or two row tiles are bound by the weights, read once from HBM at
-// kHbm in all and kCuHbm a CU (64 x 24576 x 4096: 384 tiles of 64 x 64 52 us, 192 of 128 x 128 45).
+// kHbm in all and kCuHbm a CU (64 x 24576 x 4096: 384 tiles of 64 x 64 52 us, 192 of 128 x 128 45); one
+// round, even a whole one, has its rate in t1 (64 x 32768 x 3072: 256 tiles of 128 x 128 40 us, 128 of 128 x
+// 256 51; 64 x 16384 x 3072: 256 tiles of 64 x 64 21 us, 128 of 128 x 64 23).
 // And a grid that the XCDs do not divide keeps no neighbouring tiles on one XCD (tile_order.h): where the
 // activations are past two L2s, tiles of up to 128 columns, which read the most operand bytes, pay for it (2560 x
 // 2560 weights, 256 x 128 tiles: 7680 rows, 600 tiles, 123 us, 7936, 620 tiles, 162).
@@ -1026,7 +1029,7 @@ static double tile_cost(int tile, long rows, const GemmArgs& g, const EpiParams&
     const double kt = g.K / (64.0 * ks);
     auto round = [&](long n) {  // n workgroups side by side
         double t = s.t0 + (s.t1 - s.t0) * (double)n / 256.0;
-        if (full && nm <= 2) t = std::max(t, s.bn * 128.0 / nm / std::min(kCuHbm, kHbm / (double)n));
+        if (tiles > 256 && nm <= 2) t = std::max(t, s.bn * 128.0 / nm / std::min(kCuHbm, kHbm / (double)n));
         return kt * t + s.fix;
     };
     double t = full * round(256);
