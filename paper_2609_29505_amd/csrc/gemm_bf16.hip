@@ -983,7 +983,7 @@ using T64x64 = PKCfg<64, 64, 4>;
 // tile id -> block shape and what a tile takes: us per 64-deep k tile with the chip nearly empty and
 // with every CU busy, and us for its start and epilogue.  Fitted to 690 products (1 to 8300 rows, 256 to
 // 49152 columns, K 256 to 12288, weights cold) timed with every tile, where the choice made from them is
-// within 0.3 % of the fastest tile on average and 23 % at worst (742 x 5376 x 1024, gated: 20.4 us, 16.6);
+// within 0.3 % of the fastest tile on average and 20 % at worst (6572 x 1280 x 256, gated: 16.3 us, 13.7);
 // fitted to either half of them, within 0.6 % on the other's average.  The values before them, from 62
 // products, chose 1.5 % slower on average (6592 x 4096 x 512, gated: 45 us, now 37.5; 896 x 384 x 384: 8.1,
 // now 6.8).  They rank tiles and are no model of a launch's time: small cold products take up to twice the
